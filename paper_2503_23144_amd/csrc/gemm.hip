@@ -43,34 +43,9 @@
 #include "common.h"
 #include "devmem.h"
 #include "kernels.h"
+#include "mfma.h"
 
 namespace lrcc {
-
-typedef double d4 __attribute__((ext_vector_type(4)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-
-template <typename T>
-struct cpx;
-// Output row of accumulator register r in lane group g = lane/16 (column
-// lane%16): the FP64 instruction interleaves rows across lane groups, the
-// FP32 one gives each lane group four consecutive rows.
-template <>
-struct cpx<double> {
-  using type = double2;
-  using acc = d4;
-  static constexpr bool gauss = false;  // 4 real products
-  static __device__ constexpr int row(int g, int r) { return g + 4 * r; }
-};
-template <>
-struct cpx<float> {
-  using type = float2;
-  using acc = f4;
-  static constexpr bool gauss = true;  // 3 real products
-  static __device__ constexpr int row(int g, int r) { return 4 * g + r; }
-};
-
-__device__ inline d4 mfma(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-__device__ inline f4 mfma(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // LDS padding (32 banks of 4 bytes).  MFMA operand reads take row l%16 at
 // k = l/16 for lane l.  Row layout [row][k]: an FP32 read serves 32 lanes
@@ -392,6 +367,16 @@ __global__ void splitk_reduce_kernel(int64_t m, int64_t n, int splits, const typ
   }
 }
 
+template <typename T>
+static void launch_splitk_reduce(int64_t m, int64_t n, int splits, const void* ws, double are, double aim, double bre,
+                                 double bim, void* C, const OutMap& om, hipStream_t st) {
+  using V2 = typename cpx<T>::type;
+  const unsigned blocks = (unsigned)std::min<int64_t>((m * n + 255) / 256, 4096);
+  hipLaunchKernelGGL(splitk_reduce_kernel<T>, dim3(blocks), dim3(256), 0, st, m, n, splits, (const V2*)ws, (T)are,
+                     (T)aim, (T)bre, (T)bim, (V2*)C, om);
+  HIP_CHECK(hipGetLastError());
+}
+
 template <typename T, int KIND, int BM, int BN, int WGM, int NW = 4>
 static void go(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim, const void* A, int64_t lda,
                const void* B, int64_t ldb, double bre, double bim, void* C, const OutMap& om, hipStream_t st,
@@ -428,13 +413,7 @@ static void go(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, do
     GO_(true, true);
 #undef GO_
   HIP_CHECK(hipGetLastError());
-  if (splits > 1) {
-    const int64_t total = m * n;
-    const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 4096);
-    hipLaunchKernelGGL(splitk_reduce_kernel<T>, dim3(blocks), dim3(256), 0, st, m, n, splits, (const V2*)ws, (T)are,
-                       (T)aim, (T)bre, (T)bim, (V2*)C, om);
-    HIP_CHECK(hipGetLastError());
-  }
+  if (splits > 1) launch_splitk_reduce<T>(m, n, splits, ws, are, aim, bre, bim, C, om, st);
 }
 
 // ---------------------------------------------------------------- tile choice
@@ -612,9 +591,17 @@ int gemm_splits(int64_t m, int64_t n, int64_t k, bool fp64) {
 }
 
 template <typename T>
-size_t gemm_workspace_bytes(int64_t m, int64_t n, int64_t k) {
-  const int s = gemm_splits(m, n, k, sizeof(T) == 8);
-  return s > 1 ? (size_t)s * m * n * 2 * sizeof(T) : 0;
+static size_t split_bytes(int64_t m, int64_t n, int splits) {
+  return splits > 1 ? (size_t)splits * m * n * 2 * sizeof(T) : 0;
+}
+
+template <typename T>
+size_t gemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb) {
+  if (forced_tile() < 0) {
+    const WavePlan p = wave_plan<T>(m, n, k, lda, ldb, true);
+    if (p.variant >= 0) return split_bytes<T>(m, n, p.splits);
+  }
+  return split_bytes<T>(m, n, gemm_splits(m, n, k, sizeof(T) == 8));
 }
 
 template <typename T>
@@ -624,9 +611,28 @@ void launch_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, 
                  bool allow_tune) {
   if (m <= 0 || n <= 0) return;
   const OutMap om = omap ? *omap : OutMap::plain(ldc);
+  if (forced_tile() < 0) {
+    WavePlan p = wave_plan<T>(m, n, k, lda, ldb, true);
+    if (p.splits > 1 && !(ws && ws_bytes >= (size_t)p.splits * m * n * 2 * sizeof(T)))
+      p = wave_plan<T>(m, n, k, lda, ldb, false);
+    if (p.variant >= 0) {
+      if (trace_on())
+        fprintf(stderr, "[lrcc gemm] %s ta=%d tb=%d kind=%d m=%lld n=%lld k=%lld tile=w%d splits=%d\n",
+                sizeof(T) == 8 ? "c128" : "c64", (int)ta, (int)tb, kind, (long long)m, (long long)n, (long long)k,
+                p.variant, p.splits);
+      if (p.splits == 1) {
+        launch_wave_gemm<T>(p, ta, tb, m, n, k, are, aim, A, lda, B, ldb, bre, bim, C, om, 0, st, conj_b);
+      } else {
+        launch_wave_gemm<T>(p, ta, tb, m, n, k, 1.0, 0.0, A, lda, B, ldb, 0.0, 0.0, ws, OutMap::plain(n), m * n, st,
+                            conj_b);
+        launch_splitk_reduce<T>(m, n, p.splits, ws, are, aim, bre, bim, C, om, st);
+      }
+      return;
+    }
+  }
   {
     const int splits = gemm_splits(m, n, k, sizeof(T) == 8);
-    if (splits > 1 && ws && ws_bytes >= gemm_workspace_bytes<T>(m, n, k)) {
+    if (splits > 1 && ws && ws_bytes >= split_bytes<T>(m, n, splits)) {
       if (trace_on())
         fprintf(stderr, "[lrcc gemm] %s ta=%d tb=%d kind=%d m=%lld n=%lld k=%lld tile=%d splits=%d\n",
                 sizeof(T) == 8 ? "c128" : "c64", (int)ta, (int)tb, kind, (long long)m, (long long)n, (long long)k,
@@ -729,7 +735,7 @@ template void launch_gemm<double>(bool, bool, int64_t, int64_t, int64_t, double,
 template void launch_gemm<float>(bool, bool, int64_t, int64_t, int64_t, double, double, const void*, int64_t,
                                  const void*, int64_t, double, double, void*, int64_t, hipStream_t, int, void*,
                                  size_t, const OutMap*, bool, bool);
-template size_t gemm_workspace_bytes<double>(int64_t, int64_t, int64_t);
-template size_t gemm_workspace_bytes<float>(int64_t, int64_t, int64_t);
+template size_t gemm_workspace_bytes<double>(int64_t, int64_t, int64_t, int64_t, int64_t);
+template size_t gemm_workspace_bytes<float>(int64_t, int64_t, int64_t, int64_t, int64_t);
 
 }  // namespace lrcc

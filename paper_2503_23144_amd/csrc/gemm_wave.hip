@@ -1,0 +1,331 @@
+// Complex GEMM without LDS staging, for products with few or narrow tiles.
+//
+// The tiled kernel (gemm.hip) walks K one barrier-separated slab at a time; a
+// slab takes 2.6 us when its workgroup has the CU to itself, so a product
+// with a handful of tiles is bound by that chain and not by any rate of the
+// chip (FP64 30 x 60 x 36000, split 34 ways: 190 us for 3 us of MFMA work
+// and 11 us of memory traffic).  Here a wavefront loads the MFMA fragments
+// of its 16 TI x 16 TJ tile straight from global memory, one step of 4 U
+// depths ahead of the products, with no barrier in the loop:
+//   KSPLIT   the NW wavefronts of a workgroup share one tile and take every
+//            NW-th step each; their sums meet in LDS at the end.  Further
+//            splits over blockIdx.y leave partials for splitk_reduce_kernel.
+//   !KSPLIT  every wavefront owns a tile of its own (shallow products).
+// Measured (us, tiled kernel -> this one): FP64 4x4x1024 170 -> 7, 3x600x600
+// 102 -> 8, 180x10x6000 205 -> 15, 30x60x36000 190 -> 37, 135x1770x1770
+// 295 -> 82, 1200^3 347 -> 257, 3000^3 3819 -> 3429, 20x450000x150 1141 ->
+// 378, 1x22500x3000 859 -> 196 (5.5 TB/s); FP32 12x671x671 53 -> 7,
+// 660x1830x1830 219 -> 150, 24x3000x3000 121 -> 34, 36000x1x3000 289 -> 155.
+// Without LDS every operand element is read from L2 once per 32 rows or
+// columns, which the FP32 3M products outrun when they are large and wide;
+// those stay on the tiled kernel (wave_plan).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "common.h"
+#include "kernels.h"
+#include "mfma.h"
+
+namespace lrcc {
+
+template <typename T, bool TA, bool TB, int TI, int TJ, int NW, bool KSPLIT, int U>
+__global__ void __launch_bounds__(64 * NW)
+    wgemm_kernel(int64_t M, int64_t N, int64_t K, T are, T aim, const typename cpx<T>::type* __restrict__ A,
+                 int64_t lda, const typename cpx<T>::type* __restrict__ B, int64_t ldb, T bre, T bim,
+                 typename cpx<T>::type* __restrict__ C, OutMap om, int64_t kchunk, int64_t cstride, T bsgn,
+                 int64_t nbm) {
+  using V2 = typename cpx<T>::type;
+  using ACC = typename cpx<T>::acc;
+  constexpr bool G3 = cpx<T>::gauss;
+  constexpr int NA = G3 ? 3 : 2;
+  constexpr int KS = 4 * U;  // depth of one step
+  constexpr uint32_t ES = sizeof(V2);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, kq = lane >> 4;
+  {
+    const int64_t kbeg = (int64_t)blockIdx.y * kchunk;
+    K = (K < kbeg + kchunk ? K : kbeg + kchunk) - kbeg;
+    A += TA ? kbeg * lda : kbeg;
+    B += TB ? kbeg : kbeg * ldb;
+    C += (int64_t)blockIdx.y * cstride;
+  }
+  int64_t tile = blockIdx.x;
+  if (!KSPLIT) {
+    tile = tile * NW + wave;
+    if (tile >= nbm * ((N + 16 * TJ - 1) / (16 * TJ))) return;
+  }
+  const int64_t m0 = (tile % nbm) * (16 * TI), n0 = (tile / nbm) * (16 * TJ);
+
+  // An operand address is a base common to the wavefront (advanced along k)
+  // plus a 32-bit byte offset per lane.  Rows beyond M and columns beyond N
+  // are clamped to the last one; they only feed outputs that are never stored.
+  const char* ab = (const char*)(A + (TA ? m0 : m0 * lda));
+  const char* bb = (const char*)(B + (TB ? n0 * ldb : n0));
+  uint32_t oa[TI], ob[TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+    const uint32_t r = i * 16 + r16, cr = m0 + r < M ? r : (uint32_t)(M - 1 - m0);
+    oa[i] = (TA ? cr + kq * U * (uint32_t)lda : cr * (uint32_t)lda + kq * U) * ES;
+  }
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) {
+    const uint32_t r = j * 16 + r16, cr = n0 + r < N ? r : (uint32_t)(N - 1 - n0);
+    ob[j] = (TB ? cr * (uint32_t)ldb + kq * U : cr + kq * U * (uint32_t)ldb) * ES;
+  }
+  const int64_t sa = (TA ? lda : 1) * ES, sb = (TB ? 1 : ldb) * ES;  // one depth, in bytes
+  struct Frag {
+    V2 a[U][TI], b[U][TJ];
+  };
+  // lane group kq holds the depths k0 + kq U + u of a step
+  auto load = [&](Frag& f, int64_t k0) {
+    const char* pa = ab + k0 * sa;
+    const char* pb = bb + k0 * sb;
+    if (k0 + KS <= K) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i) f.a[u][i] = *(const V2*)(pa + u * sa + oa[i]);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) f.b[u][j] = *(const V2*)(pb + u * sb + ob[j]);
+      }
+    } else {  // depths beyond K are read at the last one and count as zero
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t kl = k0 + kq * U + u, back = kl < K ? 0 : kl - (K - 1);
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+          const V2 x = *(const V2*)(pa + u * sa + oa[i] - back * sa);
+          f.a[u][i] = back ? V2{0, 0} : x;
+        }
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+          const V2 x = *(const V2*)(pb + u * sb + ob[j] - back * sb);
+          f.b[u][j] = back ? V2{0, 0} : x;
+        }
+      }
+    }
+  };
+  ACC acc[NA][TI][TJ];
+#pragma unroll
+  for (int p = 0; p < NA; ++p)
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) acc[p][i][j] = ACC{0, 0, 0, 0};
+  auto products = [&](const Frag& f) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+          const V2 a = f.a[u][i], b = V2{f.b[u][j].x, f.b[u][j].y * bsgn};
+          if constexpr (!G3) {
+            acc[0][i][j] = mfma(a.x, b.x, acc[0][i][j]);
+            acc[1][i][j] = mfma(a.x, b.y, acc[1][i][j]);
+            acc[0][i][j] = mfma(-a.y, b.y, acc[0][i][j]);
+            acc[1][i][j] = mfma(a.y, b.x, acc[1][i][j]);
+          } else {
+            acc[0][i][j] = mfma(a.x, b.x, acc[0][i][j]);
+            acc[1][i][j] = mfma(a.y, b.y, acc[1][i][j]);
+            acc[2][i][j] = mfma(a.x + a.y, b.x + b.y, acc[2][i][j]);
+          }
+        }
+  };
+  constexpr int64_t STEP = KSPLIT ? (int64_t)KS * NW : KS;
+  int64_t k = KSPLIT ? (int64_t)wave * KS : 0;
+  Frag f0, f1;
+  if (k < K) load(f0, k);
+  while (k < K) {
+    if (k + STEP < K) load(f1, k + STEP);
+    products(f0);
+    k += STEP;
+    if (k >= K) break;
+    if (k + STEP < K) load(f0, k + STEP);
+    products(f1);
+    k += STEP;
+  }
+  auto value = [&](int i, int j, int r) {
+    if constexpr (!G3) {
+      return V2{acc[0][i][j][r], acc[1][i][j][r]};
+    } else {
+      const T p1 = acc[0][i][j][r], p2 = acc[1][i][j][r], p3 = acc[2][i][j][r];
+      return V2{p1 - p2, p3 - p1 - p2};
+    }
+  };
+  const bool use_beta = (bre != T(0) || bim != T(0));
+  auto put = [&](int64_t off, V2 v) {
+    T cr = are * v.x - aim * v.y, ci = are * v.y + aim * v.x;
+    V2* c = C + off;
+    if (use_beta) {
+      const V2 y = *c;
+      cr += bre * y.x - bim * y.y;
+      ci += bre * y.y + bim * y.x;
+    }
+    *c = V2{cr, ci};
+  };
+  if constexpr (KSPLIT) {
+    __shared__ V2 red[NW][TI * TJ * 256];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          red[wave][(i * 16 + cpx<T>::row(kq, r)) * (16 * TJ) + j * 16 + r16] = value(i, j, r);
+    __syncthreads();
+    for (int e = tid; e < TI * TJ * 256; e += 64 * NW) {
+      V2 s = red[0][e];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) {
+        s.x += red[w][e].x;
+        s.y += red[w][e].y;
+      }
+      const int64_t m = m0 + e / (16 * TJ), n = n0 + e % (16 * TJ);
+      if (m < M && n < N) put(om.row(m) + om.col(n), s);
+    }
+  } else {
+    int64_t coff[TJ];
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      const int64_t n = n0 + j * 16 + r16;
+      coff[j] = n < N ? om.col(n) : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t m = m0 + i * 16 + cpx<T>::row(kq, r);
+        if (m >= M) continue;
+        const int64_t roff = om.row(m);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+          if (coff[j] >= 0) put(roff + coff[j], value(i, j, r));
+      }
+  }
+}
+
+template <typename T, int TI, int TJ, int NW, bool KSPLIT, int U>
+static void wgo(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim, const void* A, int64_t lda,
+                const void* B, int64_t ldb, double bre, double bim, void* C, const OutMap& om, hipStream_t st,
+                int splits, int64_t kchunk, int64_t cstride, bool conjb) {
+  using V2 = typename cpx<T>::type;
+  const int64_t nbm = (m + 16 * TI - 1) / (16 * TI), nt = nbm * ((n + 16 * TJ - 1) / (16 * TJ));
+  const int64_t nb = KSPLIT ? nt : (nt + NW - 1) / NW;
+  LRCC_REQUIRE(nb < (int64_t(1) << 31), LRCC_E_INVALID, "gemm grid too large");
+#define WGO_(TA_, TB_)                                                                                           \
+  hipLaunchKernelGGL((wgemm_kernel<T, TA_, TB_, TI, TJ, NW, KSPLIT, U>), dim3((unsigned)nb, (unsigned)splits),   \
+                     dim3(64 * NW), 0, st, m, n, k, (T)are, (T)aim, (const V2*)A, lda, (const V2*)B, ldb, (T)bre, \
+                     (T)bim, (V2*)C, om, kchunk, cstride, (T)(conjb ? -1.0 : 1.0), nbm)
+  if (!ta && !tb)
+    WGO_(false, false);
+  else if (!ta && tb)
+    WGO_(false, true);
+  else if (ta && !tb)
+    WGO_(true, false);
+  else
+    WGO_(true, true);
+#undef WGO_
+  HIP_CHECK(hipGetLastError());
+}
+
+// Variants: 0 and 1 share one 16 x 16 tile among 8 and 4 wavefronts, 2
+// shares a 32 x 32 tile (8 wavefronts in FP64, 4 deeper-stepping ones in
+// FP32: the FP64 accumulators leave registers for two-deep steps only), 3
+// and 4 give every wavefront a 16 x 16 or a 16 x 32 tile of its own.
+template <typename T>
+void launch_wave_gemm(const WavePlan& p, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim,
+                      const void* A, int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C,
+                      const OutMap& om, int64_t cstride, hipStream_t st, bool conjb) {
+  constexpr bool F64 = sizeof(T) == 8;
+#define W_(TI, TJ, NW, KSP, U)                                                                                   \
+  wgo<T, TI, TJ, NW, KSP, U>(ta, tb, m, n, k, are, aim, A, lda, B, ldb, bre, bim, C, om, st, p.splits, p.kchunk, \
+                             cstride, conjb)
+  switch (p.variant) {
+    case 0: return W_(1, 1, 8, true, 4);
+    case 1: return W_(1, 1, 4, true, 4);
+    case 2: return W_(2, 2, F64 ? 8 : 4, true, F64 ? 2 : 4);
+    case 3: return W_(1, 1, 4, false, 4);
+    case 4: return W_(1, 2, 4, false, 4);
+  }
+#undef W_
+  throw Error(LRCC_E_INTERNAL, "unknown wavefront GEMM variant");
+}
+
+// Which products run here, and how.  t16 and t32 count the 16 x 16 and
+// 32 x 32 tiles of the output; figures are tiled kernel / this kernel in us.
+//  * Addresses are 32-bit offsets from a tile's base: a leading dimension
+//    beyond 2^32 bytes over 32 rows stays on the tiled kernel.
+//  * Shallow (K <= 24): the output's traffic bounds both; the tiled kernel's
+//    wider rows win from t16 = 8192 on (FP64 150x60000x20 79 / 94,
+//    108000x10x10 (6750 tiles) 20 / 13).
+//  * K <= 512 in FP64 on 1024 tiles or more: a tile per wavefront
+//    (60000x150x150 274 / 252, 400x22500x400 581 / 542), except where the
+//    64 x 64 tiles fit without padding (1200x14400x240 638 / 654: both
+//    extents of 1000 or more).  FP32 is L2-bound there (44652x121x121
+//    62 / 73) and takes the tiled kernel from 4096 tiles on.
+//  * One 16 x 16 tile per workgroup where an extent is at most 16 or 32 x 32
+//    tiles are few (FP64 600^3 42 against 48 on 32 x 32); 8 wavefronts below
+//    512 tiles, 4 above.
+//  * 32 x 32 tiles otherwise: in FP64 until 1024 tiles of 128 x 128 fill the
+//    chip at the tiled kernel's higher intensity (18000x3000x3000 runs at 66
+//    TFLOP/s there), in FP32 below 4e9 complex MACs or at most 96 wide
+//    (1728x576x57600 2862 / 3511, 72x240x518400 999 / 810).
+//  * Splits over K fill the chip's workgroup slots: at least 384 depths each
+//    for the 16 x 16 tile, 256 for 32 x 32 (partials of at most 64 MB).
+template <typename T>
+WavePlan wave_plan(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bool can_split) {
+  constexpr bool F64 = sizeof(T) == 8;
+  WavePlan p;
+  if (m <= 0 || n <= 0 || k <= 0) return p;
+  if (std::max(lda, ldb) * 32 * (int64_t)(2 * sizeof(T)) >= (int64_t(1) << 32)) return p;
+  auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  const int64_t t16 = cdiv(m, 16) * cdiv(n, 16), t32 = cdiv(m, 32) * cdiv(n, 32);
+  const bool narrow = std::min(m, n) <= 16;
+  int64_t slots = 0, mink = 0, tiles = 0;
+  if (k <= 24) {
+    if (t16 >= 8192) return p;
+    p.variant = t16 >= 1024 ? 3 : 1;
+  } else if (k <= 512 && t16 >= 1024) {
+    if (F64 ? std::min(m, n) >= 1000 : t16 >= 4096) return p;
+    p.variant = narrow ? 3 : 4;
+  } else if (narrow || (k < 2048 && t32 < (F64 ? 900 : 256))) {
+    p.variant = t16 < 512 ? 0 : 1;
+    slots = 512, mink = 384, tiles = t16;
+  } else {
+    if (F64 ? cdiv(m, 128) * cdiv(n, 128) >= 1024 : ((double)m * n * k >= 4e9 && std::min(m, n) > 96)) return p;
+    p.variant = 2;
+    slots = F64 ? 256 : 512, mink = 256, tiles = t32;
+  }
+  p.kchunk = k;
+  if (!can_split || tiles == 0 || tiles >= 2 * slots) return p;
+  const int64_t part = m * n * (int64_t)(2 * sizeof(T));
+  const int64_t smax = std::min<int64_t>({64, k / mink, (int64_t(64) << 20) / part});
+  auto eff = [&](int64_t s) {
+    const int64_t w = tiles * s, rounds = cdiv(w, slots);
+    return (double)w / (double)(rounds * slots);
+  };
+  double best = 0;
+  for (int64_t s = 1; s <= smax; ++s) best = std::max(best, eff(s));
+  for (int64_t s = 1; s <= smax; ++s)
+    if (eff(s) >= 0.9 * best) {
+      if (s > 1 && eff(s) >= 1.15 * eff(1)) {
+        p.kchunk = cdiv(cdiv(k, s), 16) * 16;
+        p.splits = (int)cdiv(k, p.kchunk);
+      }
+      break;
+    }
+  return p;
+}
+
+#define INST_(T)                                                                                                    \
+  template void launch_wave_gemm<T>(const WavePlan&, bool, bool, int64_t, int64_t, int64_t, double, double,         \
+                                    const void*, int64_t, const void*, int64_t, double, double, void*,              \
+                                    const OutMap&, int64_t, hipStream_t, bool);                                     \
+  template WavePlan wave_plan<T>(int64_t, int64_t, int64_t, int64_t, int64_t, bool);
+INST_(double)
+INST_(float)
+#undef INST_
+
+}  // namespace lrcc

@@ -122,9 +122,23 @@ void launch_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, 
                  hipStream_t st, int kind = 0, void* ws = nullptr, size_t ws_bytes = 0,
                  const OutMap* om = nullptr, bool conj_b = false,  // conj_b: use conj(B)
                  bool allow_tune = true);  // false: never time candidate tiles (no device allocation)
-int gemm_splits(int64_t m, int64_t n, int64_t k, bool fp64);
+int gemm_splits(int64_t m, int64_t n, int64_t k, bool fp64);  // of the tiled kernel
 template <typename T>
-size_t gemm_workspace_bytes(int64_t m, int64_t n, int64_t k);
+size_t gemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb);
+
+// Products with few or narrow tiles (gemm_wave.hip): the variant that runs
+// one (-1: the tiled kernel does), its splits over K and their depth.
+struct WavePlan {
+  int variant = -1, splits = 1;
+  int64_t kchunk = 0;
+};
+template <typename T>
+WavePlan wave_plan(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bool can_split);
+// Partials go to C + split * cstride when the plan splits.
+template <typename T>
+void launch_wave_gemm(const WavePlan& p, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim,
+                      const void* A, int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C,
+                      const OutMap& om, int64_t cstride, hipStream_t st, bool conjb);
 
 // Per-shape tile autotuning of launch_gemm (process-wide).
 void set_gemm_autotune(bool on);

@@ -7,7 +7,7 @@
 // a second kernel reduces in fixed order.  Here those partials live in a
 // static device array of kStaticScratchBytes per GPU, which every GPU that
 // runs this entry point holds until the process ends.  The library never
-// splits a product into more than 256 MiB of partials (gemm_splits caps the
+// splits a product into more than 256 MiB of partials (gemm_splits and wave_plan cap the
 // split at that size), so the array holds the split the library picks for
 // every shape; a product that would need more is rejected with
 // LRCC_E_INVALID.  The partials are written in full before they are read,
@@ -63,8 +63,8 @@ extern "C" int lrcc_gemm_noalloc(int precision, int transa, int transb, int64_t 
     LRCC_REQUIRE(precision == LRCC_FP64 || precision == LRCC_MIXED, LRCC_E_INVALID, "bad precision");
     LRCC_REQUIRE(m >= 0 && n >= 0 && k >= 0, LRCC_E_INVALID, "negative size");
     LRCC_REQUIRE(lda >= (transa ? m : k) && ldb >= (transb ? k : n) && ldc >= n, LRCC_E_INVALID, "leading dimension");
-    const size_t wsb = precision == LRCC_FP64 ? gemm_workspace_bytes<double>(m, n, k)
-                                              : gemm_workspace_bytes<float>(m, n, k);
+    const size_t wsb = precision == LRCC_FP64 ? gemm_workspace_bytes<double>(m, n, k, lda, ldb)
+                                              : gemm_workspace_bytes<float>(m, n, k, lda, ldb);
     LRCC_REQUIRE(wsb <= kStaticScratchBytes, LRCC_E_INVALID,
                  "product needs " + std::to_string(wsb) + " bytes of split-K partials, above the " +
                      std::to_string(kStaticScratchBytes) + "-byte static scratch of lrcc_gemm_noalloc");

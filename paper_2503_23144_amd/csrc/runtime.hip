@@ -319,7 +319,7 @@ void Executor<T>::gemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double
                      (om || ldc >= N),
                  LRCC_E_INTERNAL, "gemm operands exceed their buffers");
   }
-  const size_t wsb = gemm_workspace_bytes<T>(M, N, K);
+  const size_t wsb = gemm_workspace_bytes<T>(M, N, K, lda, ldb);
   void* ws = wsb ? scratch(4, wsb) : nullptr;
   GemmArgs g{ta, tb, M, N, K, are, aim, A, lda, B, ldb, bre, C, ldc, ladder, ws, wsb, OutMap(), om != nullptr, conjb};
   if (om) g.om = *om;
