@@ -18,7 +18,7 @@ SRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "liblrcc.so")
 
-SOURCES = ["program.cpp", "devmem.hip", "kernels.hip", "gemm.hip", "gemm_wave.hip", "runtime.hip", "integrals.hip", "solver.hip", "fnspp.hip",
+SOURCES = ["program.cpp", "devmem.hip", "kernels.hip", "gemm.hip", "gemm_wave.hip", "gemm_split.hip", "runtime.hip", "integrals.hip", "solver.hip", "fnspp.hip",
            "abi.hip", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

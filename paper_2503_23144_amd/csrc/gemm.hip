@@ -57,13 +57,6 @@ template <typename T>
 constexpr int padk() { return sizeof(T) == 4 ? 2 : 1; }
 constexpr int PADR = 16;
 
-// Map a linear workgroup id to (tile_m, tile_n).  Hardware dispatches
-// consecutive ids round-robin over the 8 XCDs; regroup so that each XCD sees
-// a contiguous run of ids (XCDs 0..r-1 take one tile more when the grid does
-// not divide by 8).  Runs are then walked in groups of GM tile rows, M
-// fastest: 32 consecutive tiles on one XCD cover 8 x 4 tiles, so A and B
-// panels are both shared in that XCD's L2.
-constexpr int64_t GM = 8;
 // Products at most this wide (n) use the 128 x 32 tile.
 constexpr int64_t kNarrow = 32;
 
@@ -76,21 +69,6 @@ static bool split_narrow(int64_t m, int64_t n) {
   const double p32 = (double)((m + 127) / 128 * 128) * (double)((n + 31) / 32 * 32);
   return p32 < 0.9 * p64;
 }
-__device__ inline void tile_of(int64_t bid, int64_t nbm, int64_t nbn, int64_t& tm, int64_t& tn) {
-  const int64_t total = nbm * nbn;
-  int64_t id = bid;
-  if (total >= 64) {
-    const int64_t q = total / 8, r = total % 8, x = bid % 8, j = bid / 8;
-    id = (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
-  }
-  const int64_t width = GM * nbn;
-  const int64_t first_m = (id / width) * GM;
-  const int64_t gm = nbm - first_m < GM ? nbm - first_m : GM;
-  const int64_t rem = id % width;
-  tm = first_m + rem % gm;
-  tn = rem / gm;
-}
-
 // Register staging of one operand tile: IN elements along the dimension
 // that is contiguous in global memory, PER elements per thread, STEP rows of
 // the other dimension per pass of the NT threads.
@@ -347,7 +325,8 @@ __global__ void __launch_bounds__(64 * NW) zgemm_kernel(int64_t M, int64_t N, in
 // C = alpha * sum_s P[s] + beta * C over an m x n tile set (split-K reduction)
 template <typename T>
 __global__ void splitk_reduce_kernel(int64_t m, int64_t n, int splits, const typename cpx<T>::type* __restrict__ P,
-                                     T are, T aim, T bre, T bim, typename cpx<T>::type* __restrict__ C, OutMap om) {
+                                     T are, T aim, T bre, T bim, typename cpx<T>::type* __restrict__ C, OutMap om,
+                                     int64_t m0, int64_t n0) {
   const int64_t total = m * n;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     T sr = 0, si = 0;
@@ -357,7 +336,7 @@ __global__ void splitk_reduce_kernel(int64_t m, int64_t n, int splits, const typ
       si += p.y;
     }
     T cr = are * sr - aim * si, ci = are * si + aim * sr;
-    typename cpx<T>::type* c = C + om.row(e / n) + om.col(e % n);
+    typename cpx<T>::type* c = C + om.row(m0 + e / n) + om.col(n0 + e % n);
     if (bre != T(0) || bim != T(0)) {
       const typename cpx<T>::type y = *c;
       cr += bre * y.x - bim * y.y;
@@ -369,12 +348,18 @@ __global__ void splitk_reduce_kernel(int64_t m, int64_t n, int splits, const typ
 
 template <typename T>
 static void launch_splitk_reduce(int64_t m, int64_t n, int splits, const void* ws, double are, double aim, double bre,
-                                 double bim, void* C, const OutMap& om, hipStream_t st) {
+                                 double bim, void* C, const OutMap& om, hipStream_t st, int64_t m0 = 0,
+                                 int64_t n0 = 0) {
   using V2 = typename cpx<T>::type;
   const unsigned blocks = (unsigned)std::min<int64_t>((m * n + 255) / 256, 4096);
   hipLaunchKernelGGL(splitk_reduce_kernel<T>, dim3(blocks), dim3(256), 0, st, m, n, splits, (const V2*)ws, (T)are,
-                     (T)aim, (T)bre, (T)bim, (V2*)C, om);
+                     (T)aim, (T)bre, (T)bim, (V2*)C, om, m0, n0);
   HIP_CHECK(hipGetLastError());
+}
+
+void launch_splitk_reduce_f32(int64_t m, int64_t n, int splits, const void* P, double are, double aim, double bre,
+                              double bim, void* C, const OutMap& om, int64_t m0, int64_t n0, hipStream_t st) {
+  launch_splitk_reduce<float>(m, n, splits, P, are, aim, bre, bim, C, om, st, m0, n0);
 }
 
 template <typename T, int KIND, int BM, int BN, int WGM, int NW = 4>
@@ -608,9 +593,17 @@ template <typename T>
 void launch_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim, const void* A,
                  int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C, int64_t ldc,
                  hipStream_t st, int kind, void* ws, size_t ws_bytes, const OutMap* omap, bool conj_b,
-                 bool allow_tune) {
+                 bool allow_tune, const SplitPlan* sp, void* pack_ws) {
   if (m <= 0 || n <= 0) return;
   const OutMap om = omap ? *omap : OutMap::plain(ldc);
+  if constexpr (sizeof(T) == 4) {
+    if (sp && sp->use && pack_ws && forced_tile() < 0) {
+      if (trace_on())
+        fprintf(stderr, "[lrcc gemm] c64 ta=%d tb=%d kind=%d m=%lld n=%lld k=%lld tile=b%d splits=%d\n", (int)ta,
+                (int)tb, kind, (long long)m, (long long)n, (long long)k, sp->small ? 1 : 0, sp->splits);
+      return launch_split_gemm(*sp, ta, tb, m, n, k, are, aim, A, lda, B, ldb, bre, bim, C, om, pack_ws, st, conj_b);
+    }
+  }
   if (forced_tile() < 0) {
     WavePlan p = wave_plan<T>(m, n, k, lda, ldb, true);
     if (p.splits > 1 && !(ws && ws_bytes >= (size_t)p.splits * m * n * 2 * sizeof(T)))
@@ -731,10 +724,10 @@ void launch_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, 
 
 template void launch_gemm<double>(bool, bool, int64_t, int64_t, int64_t, double, double, const void*, int64_t,
                                   const void*, int64_t, double, double, void*, int64_t, hipStream_t, int, void*,
-                                  size_t, const OutMap*, bool, bool);
+                                  size_t, const OutMap*, bool, bool, const SplitPlan*, void*);
 template void launch_gemm<float>(bool, bool, int64_t, int64_t, int64_t, double, double, const void*, int64_t,
                                  const void*, int64_t, double, double, void*, int64_t, hipStream_t, int, void*,
-                                 size_t, const OutMap*, bool, bool);
+                                 size_t, const OutMap*, bool, bool, const SplitPlan*, void*);
 template size_t gemm_workspace_bytes<double>(int64_t, int64_t, int64_t, int64_t, int64_t);
 template size_t gemm_workspace_bytes<float>(int64_t, int64_t, int64_t, int64_t, int64_t);
 

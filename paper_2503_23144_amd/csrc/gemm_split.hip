@@ -1,0 +1,374 @@
+// Complex FP32 GEMM on the BF16 matrix cores, for large products.
+//
+// The FP32 MFMA rate bounds the tiled kernel (119 TFLOP/s of 157 in the 3M
+// count); BF16 runs at 16 times that rate.  An FP32 number is exactly the
+// sum of three BF16 numbers, x = h + m + l (8 significant bits each,
+// round to nearest), so a real FP32 product is six BF16 products,
+//   x y = h h + h m + m h + m m + h l + l h   (+ terms below 2^-25 |x y|),
+// each exact in FP32 and added up in FP32 by the MFMA: 18 BF16 products for
+// one complex 3M product, 2.7 times fewer matrix-core cycles than the FP32
+// instruction needs.
+//
+// split_pack_kernel writes both operands as the LDS image the product reads:
+// blocks of 128 rows x 16 depths, for each of re, im and re + im (the 3M
+// sums, rounded to FP32 as in the tiled kernel) and each of h, m, l, eight
+// consecutive depths of a row in 16 bytes.  Transposes, conjugation and
+// padding end there (zeros beyond the operand), so one product kernel serves
+// all layouts and its loads go straight from global memory to LDS.
+//
+// split_gemm_kernel: a 256 x 128 tile on 8 wavefronts of 64 x 64 (or 128 x
+// 128 on 4), two LDS stages, the next one in flight during the products.
+// P1 = Ar Br, P2 = Ai Bi and P3 = (Ar+Ai)(Br+Bi) are accumulated one after
+// the other over the whole depth, P3 on top of -P1 - P2, so 128 accumulator
+// registers hold a 64 x 64 complex tile and leave room for the fragments at
+// two wavefronts per SIMD; a 3M tile with all three at once would not fit.
+//
+// What bounds it: power.  A register-only BF16 MFMA loop on normal data
+// sustains 1.3-1.5 PFLOP/s of the nominal 2.5 on this card; the kernel runs
+// at 1.1-1.2.  Measured, TFLOP/s in the 6 MNK count, tiled -> this (packing
+// apart): 18000x3000x3000 121 -> 196, 4560x11175x11175 118 -> 190,
+// 2280x11175x3000 111 -> 185.
+//
+// Accuracy: the MFMA adds 16 products before it rounds into the accumulator,
+// where the FP32 instruction adds 4, so the error against 64 bits is smaller
+// at equal depth (18000x3000x3000 1.19e-6 against 1.39e-6 in the 2-norm).
+// kChain bounds the depth of one accumulation chain, so that it stays below
+// that of the tiled kernel where that one splits K, too.
+//
+// Range: an input above BF16's largest finite value is truncated, not
+// rounded, into h, so finite inputs stay finite.  An infinite or NaN input
+// makes its row or column NaN (in the 3M scheme at least the imaginary part
+// is NaN already).  Inputs below 2^-109 lose low bits of l to BF16's
+// smallest subnormal, 2^-133.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "common.h"
+#include "kernels.h"
+#include "mfma.h"
+
+namespace lrcc {
+
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+
+namespace {
+constexpr int kRB = 128;                       // rows of a packed block
+constexpr int kSlab = 16;                      // depths of a packed slab
+constexpr int kChunk = kRB * kSlab * 3 * 2;    // bytes of one block x slab x component (three BF16 terms)
+
+__device__ inline uint16_t bits(__bf16 x) { return __builtin_bit_cast(uint16_t, x); }
+
+// x = h + m + l exactly
+__device__ inline void split3(float x, uint16_t& h, uint16_t& m, uint16_t& l) {
+  __bf16 bh = (__bf16)x;
+  float fh = (float)bh;
+  if (!(__builtin_fabsf(fh) < __builtin_inff())) {
+    if (__builtin_fabsf(x) < __builtin_inff()) {
+      fh = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & 0xffff0000u);
+      bh = (__bf16)fh;
+    } else {
+      h = bits(bh), m = 0, l = 0;
+      return;
+    }
+  }
+  const float r = x - fh;
+  const __bf16 bm = (__bf16)r;
+  h = bits(bh);
+  m = bits(bm);
+  l = bits((__bf16)(r - (float)bm));
+}
+}  // namespace
+
+// One workgroup: 128 rows x 16 depths at a time, read along the operand's
+// contiguous dimension and turned in LDS, so that every thread splits eight
+// consecutive depths of one row and writes 16 bytes per component and term.
+template <bool KMAJ>
+__global__ void __launch_bounds__(256)
+    split_pack_kernel(int64_t rows, int64_t K, const float2* __restrict__ X, int64_t ld, float sgn, int64_t nslab,
+                      uint4* __restrict__ P) {
+  __shared__ float2 t[kRB][kSlab + 1];
+  const int tid = threadIdx.x;
+  const int64_t r0 = (int64_t)blockIdx.x * kRB;
+  for (int64_t s = blockIdx.y; s < nslab; s += gridDim.y) {
+    const int64_t k0 = s * kSlab;
+#pragma unroll
+    for (int q = 0; q < kRB * kSlab / 256; ++q) {
+      const int e = q * 256 + tid;
+      const int row = KMAJ ? e % kRB : e / kSlab, kk = KMAJ ? e / kRB : e % kSlab;
+      const int64_t r = r0 + row, k = k0 + kk;
+      const bool in = r < rows && k < K;
+      const float2 v = X[in ? (KMAJ ? k * ld + r : r * ld + k) : 0];
+      t[row][kk] = in ? float2{v.x, v.y * sgn} : float2{0.0f, 0.0f};
+    }
+    __syncthreads();
+    const int row = tid & (kRB - 1), kg = tid >> 7;
+    float2 x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = t[row][kg * 8 + e];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      uint32_t w[3][4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        uint16_t u[2][3];
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+          const float2 v = x[2 * q + z];
+          split3(c == 0 ? v.x : c == 1 ? v.y : v.x + v.y, u[z][0], u[z][1], u[z][2]);
+        }
+#pragma unroll
+        for (int p = 0; p < 3; ++p) w[p][q] = (uint32_t)u[0][p] | ((uint32_t)u[1][p] << 16);
+      }
+      uint4* d = P + (((int64_t)blockIdx.x * 3 + c) * nslab + s) * (kChunk / 16);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) d[(p * 2 + kg) * kRB + row] = uint4{w[p][0], w[p][1], w[p][2], w[p][3]};
+    }
+    __syncthreads();
+  }
+}
+
+template <int WGM, int WGN, int NS>  // NS slabs per stage
+__global__ void __launch_bounds__(64 * WGM * WGN, 2)
+    split_gemm_kernel(int64_t M, int64_t N, int64_t nslab, const char* __restrict__ Ap, const char* __restrict__ Bp,
+                      float are, float aim, float bre, float bim, float2* __restrict__ C, OutMap om, int64_t om0,
+                      int64_t on0, int64_t schunk, int64_t cstride) {
+  constexpr int NW = WGM * WGN, BM = 64 * WGM, BN = 64 * WGN;
+  constexpr int RA = BM / kRB, RB = BN / kRB;
+  constexpr int STAGE = (RA + RB) * NS * kChunk;
+  __shared__ __align__(16) char lds[2][STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, kg = lane >> 5;
+  const int wm = (wave / WGN) * 64, wn = (wave % WGN) * 64;
+  const int64_t nbm = (M + BM - 1) / BM, nbn = (N + BN - 1) / BN;
+  int64_t tm, tn;
+  tile_of(blockIdx.x, nbm, nbn, tm, tn);
+  const int64_t s0 = (int64_t)blockIdx.y * schunk;
+  const int64_t ns = (nslab < s0 + schunk ? nslab : s0 + schunk) - s0;
+  C += (int64_t)blockIdx.y * cstride;
+  const int64_t nrbA = (M + kRB - 1) / kRB, nrbB = (N + kRB - 1) / kRB;
+
+  // Stage t of component c: NS consecutive slabs of every row block, copied
+  // as they lie (1 KB per wavefront load).  Blocks beyond the operand feed
+  // outputs that are never stored; they read its last block.
+  constexpr int PER = NS * kChunk / 1024, TOT = (RA + RB) * PER, NQ = TOT / NW;
+  static_assert(TOT % NW == 0, "stage does not split over the wavefronts");
+  const char* src[NQ];
+  int dst[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int x = q * NW + wave, b = x / PER, o = x % PER;
+    const bool isa = b < RA;
+    const int64_t blk = isa ? tm * RA + b : tn * RB + (b - RA), last = (isa ? nrbA : nrbB) - 1;
+    const uintptr_t base = isa ? (uintptr_t)Ap : (uintptr_t)Bp;
+    src[q] = (const char*)(base + ((blk < last ? blk : last) * 3 * nslab + s0) * kChunk + o * 1024);
+    dst[q] = b * NS * kChunk + o * 1024;
+  }
+  auto issue = [&](int buf, int c, int64_t t) __attribute__((always_inline)) {
+    const int64_t at = (c * nslab + t * NS) * kChunk;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)(src[q] + at + lane * 16),
+          (__attribute__((address_space(3))) void*)(lds[buf] + dst[q]), 16, 0, 0);
+  };
+  f16v acc[2][2][2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[p][i][j] = f16v{0};
+  const int ra = (wm / kRB) * NS * kChunk + (kg * kRB + wm % kRB + l32) * 16;
+  const int rb = (RA + wn / kRB) * NS * kChunk + (kg * kRB + wn % kRB + l32) * 16;
+  auto compute = [&](int buf, f16v(&a)[2][2]) __attribute__((always_inline)) {
+    const char* L = lds[buf];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      bf8 fa[3][2], fb[3][2];
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          fa[p][i] = *(const bf8*)(L + ra + s * kChunk + p * (kChunk / 3) + i * 512);
+          fb[p][i] = *(const bf8*)(L + rb + s * kChunk + p * (kChunk / 3) + i * 512);
+        }
+      // small terms first; m l, l m and l l lie below FP32's rounding
+      constexpr int PA[6] = {0, 2, 1, 0, 1, 0}, PB[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+      for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            a[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[PA[t]][i], fb[PB[t]][j], a[i][j], 0, 0, 0);
+    }
+  };
+  const int64_t nt = (ns + NS - 1) / NS;
+  int buf = 0;
+  issue(0, 0, 0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  auto pass = [&](int c, f16v(&a)[2][2]) __attribute__((always_inline)) {
+    for (int64_t t = 0; t < nt; ++t) {
+      if (t + 1 < nt)
+        issue(buf ^ 1, c, t + 1);
+      else if (c < 2)
+        issue(buf ^ 1, c + 1, 0);
+      compute(buf, a);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      buf ^= 1;
+    }
+  };
+  pass(0, acc[0]);
+  pass(1, acc[1]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const f16v p1 = acc[0][i][j], p2 = acc[1][i][j];
+      acc[0][i][j] = p1 - p2;
+      acc[1][i][j] = -p1 - p2;
+    }
+  pass(2, acc[1]);
+
+  const bool use_beta = (bre != 0.0f || bim != 0.0f);
+  int64_t coff[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int64_t n = tn * BN + wn + j * 32 + l32;
+    coff[j] = n < N ? om.col(on0 + n) : -1;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t m = tm * BM + wm + i * 32 + (r / 4) * 8 + kg * 4 + r % 4;
+      if (m >= M) continue;
+      const int64_t roff = om.row(om0 + m);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (coff[j] < 0) continue;
+        const float re = acc[0][i][j][r], im = acc[1][i][j][r];
+        float cr = are * re - aim * im, ci = are * im + aim * re;
+        float2* c = C + roff + coff[j];
+        if (use_beta) {
+          const float2 y = *c;
+          cr += bre * y.x - bim * y.y;
+          ci += bre * y.y + bim * y.x;
+        }
+        *c = float2{cr, ci};
+      }
+    }
+}
+
+namespace {
+constexpr int64_t kChain = 3072;                    // deepest accumulation chain
+int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+int64_t slabs(int64_t k) { return cdiv(k, 2 * kSlab) * 2; }  // padded to whole stages
+size_t pack_bytes(int64_t rows, int64_t k) { return (size_t)(cdiv(rows, kRB) * 3 * slabs(k)) * kChunk; }
+
+void pack(bool kmaj, int64_t rows, int64_t k, const void* X, int64_t ld, bool conj, void* P, hipStream_t st) {
+  const int64_t ns = slabs(k);
+  const dim3 grid((unsigned)cdiv(rows, kRB), (unsigned)std::min<int64_t>(ns, 4096));
+  if (kmaj)
+    hipLaunchKernelGGL(split_pack_kernel<true>, grid, dim3(256), 0, st, rows, k, (const float2*)X, ld,
+                       conj ? -1.0f : 1.0f, ns, (uint4*)P);
+  else
+    hipLaunchKernelGGL(split_pack_kernel<false>, grid, dim3(256), 0, st, rows, k, (const float2*)X, ld,
+                       conj ? -1.0f : 1.0f, ns, (uint4*)P);
+  HIP_CHECK(hipGetLastError());
+}
+}  // namespace
+
+// Packing moves 26 bytes per operand element (4 TB/s), the product saves
+// 1.8e-14 s per complex MAC: it pays from m n / (m + n) = 600 on (8052x671x671:
+// 224 us tiled, 150 + 67 us here; 9600x400x22500 would lose).  Below 3e9 MACs
+// the wavefront kernel or the launches decide.  The 128 x 128 tile, 7 %
+// slower per padded element, serves extents that pad the 256-row tile more.
+// Where the tiles leave the chip's 256 slots (512 for the smaller tile)
+// badly filled, several chains of K run side by side into partials.
+// Operands larger than the budget are packed in row blocks of the larger one.
+SplitPlan split_plan(int64_t m, int64_t n, int64_t k, size_t budget) {
+  SplitPlan p;
+  if (m <= 0 || n <= 0 || k < 256 || (double)m * n * k < 3e9 || (double)m * n < 600.0 * (double)(m + n)) return p;
+  p.use = true;
+  p.small = (double)cdiv(m, 256) * 256 > 1.07 * (double)cdiv(m, 128) * 128;
+  p.mc = m, p.nc = n;
+  int64_t chains = cdiv(k, kChain);
+  const int64_t tiles = cdiv(m, p.small ? 128 : 256) * cdiv(n, 128), slots = p.small ? 512 : 256;
+  auto eff = [&](int64_t s) {
+    const int64_t w = tiles * s;
+    return (double)w / (double)(cdiv(w, slots) * slots);
+  };
+  if (tiles < 4 * slots) {
+    const int64_t smax = std::min<int64_t>({8, k / 512, (int64_t)(budget / 4) / (m * n * 8)});
+    double best = 0;
+    for (int64_t s = 1; s <= smax; ++s) best = std::max(best, eff(s));
+    for (int64_t s = 1; s <= smax; ++s)
+      if (eff(s) >= 0.95 * best) {
+        if (eff(s) >= 1.1 * eff(1)) p.splits = (int)s;
+        break;
+      }
+  }
+  chains = cdiv(chains, p.splits) * p.splits;
+  const int64_t chain = cdiv(cdiv(k, chains), 2 * kSlab) * 2 * kSlab;
+  p.kl = std::min(k, chain * p.splits);
+  // row blocks of the larger operand until both fit beside the partials
+  const size_t packs = budget - (p.splits > 1 ? (size_t)p.splits * m * n * 8 : 0);
+  int64_t& big = m >= n ? p.mc : p.nc;
+  for (int64_t parts = 2; big > 2048 && pack_bytes(p.mc, p.kl) + pack_bytes(p.nc, p.kl) > packs; ++parts)
+    big = cdiv(cdiv(m >= n ? m : n, parts), 256) * 256;
+  p.a_bytes = pack_bytes(p.mc, p.kl);
+  p.b_bytes = pack_bytes(p.nc, p.kl);
+  p.bytes = p.a_bytes + p.b_bytes + (p.splits > 1 ? (size_t)p.splits * p.mc * p.nc * 8 : 0);
+  if (p.a_bytes + p.b_bytes > budget || (p.splits > 1 && p.bytes > budget)) p.use = false;
+  return p;
+}
+
+void launch_split_gemm(const SplitPlan& p, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim,
+                       const void* A, int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C,
+                       const OutMap& om, void* ws, hipStream_t st, bool conjb) {
+  char* Pa = (char*)ws;
+  char* Pb = Pa + p.a_bytes;
+  char* part = Pb + p.b_bytes;
+  const int64_t bm = p.small ? 128 : 256;
+  for (int64_t k0 = 0; k0 < k; k0 += p.kl) {
+    const int64_t kl = std::min(p.kl, k - k0), ns = slabs(kl);
+    const int64_t sc = cdiv(cdiv(ns, p.splits), 2) * 2;
+    const int splits = (int)cdiv(ns, sc);
+    const double br = k0 == 0 ? bre : 1.0, bi = k0 == 0 ? bim : 0.0;
+    bool a_packed = false;
+    for (int64_t n0 = 0; n0 < n; n0 += p.nc) {
+      const int64_t nc = std::min(p.nc, n - n0);
+      pack(!tb, nc, kl, (const char*)B + (tb ? n0 * ldb + k0 : k0 * ldb + n0) * 8, ldb, conjb, Pb, st);
+      for (int64_t m0 = 0; m0 < m; m0 += p.mc) {
+        const int64_t mc = std::min(p.mc, m - m0);
+        if (!a_packed || p.mc < m)
+          pack(ta, mc, kl, (const char*)A + (ta ? k0 * lda + m0 : m0 * lda + k0) * 8, lda, false, Pa, st);
+        a_packed = true;
+        const int64_t nb = cdiv(mc, bm) * cdiv(nc, 128);
+        LRCC_REQUIRE(nb < (int64_t(1) << 31), LRCC_E_INVALID, "gemm grid too large");
+        const dim3 grid((unsigned)nb, (unsigned)splits);
+        const bool parts = splits > 1;
+        const OutMap mo = parts ? OutMap::plain(nc) : om;
+        const float al[2] = {parts ? 1.0f : (float)are, parts ? 0.0f : (float)aim};
+        const float be[2] = {parts ? 0.0f : (float)br, parts ? 0.0f : (float)bi};
+        float2* out = (float2*)(parts ? part : (char*)C);
+        const int64_t om0 = parts ? 0 : m0, on0 = parts ? 0 : n0;
+        if (p.small)
+          hipLaunchKernelGGL((split_gemm_kernel<2, 2, 1>), grid, dim3(256), 0, st, mc, nc, ns, Pa, Pb, al[0], al[1],
+                             be[0], be[1], out, mo, om0, on0, sc, mc * nc);
+        else
+          hipLaunchKernelGGL((split_gemm_kernel<4, 2, 2>), grid, dim3(512), 0, st, mc, nc, ns, Pa, Pb, al[0], al[1],
+                             be[0], be[1], out, mo, om0, on0, sc, mc * nc);
+        HIP_CHECK(hipGetLastError());
+        if (parts) launch_splitk_reduce_f32(mc, nc, splits, part, are, aim, br, bi, C, om, m0, n0, st);
+      }
+    }
+  }
+}
+
+}  // namespace lrcc

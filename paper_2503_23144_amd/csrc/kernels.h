@@ -121,7 +121,8 @@ void launch_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, 
                  int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C, int64_t ldc,
                  hipStream_t st, int kind = 0, void* ws = nullptr, size_t ws_bytes = 0,
                  const OutMap* om = nullptr, bool conj_b = false,  // conj_b: use conj(B)
-                 bool allow_tune = true);  // false: never time candidate tiles (no device allocation)
+                 bool allow_tune = true,   // false: never time candidate tiles (no device allocation)
+                 const struct SplitPlan* sp = nullptr, void* pack_ws = nullptr);  // FP32: split_plan and its memory
 int gemm_splits(int64_t m, int64_t n, int64_t k, bool fp64);  // of the tiled kernel
 template <typename T>
 size_t gemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb);
@@ -139,6 +140,24 @@ template <typename T>
 void launch_wave_gemm(const WavePlan& p, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim,
                       const void* A, int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C,
                       const OutMap& om, int64_t cstride, hipStream_t st, bool conjb);
+
+// Large FP32 products on the BF16 matrix cores (gemm_split.hip): both
+// operands are packed into `bytes` of device memory, mc x nc of the output and
+// kl of the depth at a time.
+struct SplitPlan {
+  bool use = false, small = false;
+  int splits = 1;
+  int64_t mc = 0, nc = 0, kl = 0;
+  size_t a_bytes = 0, b_bytes = 0, bytes = 0;
+};
+constexpr size_t kPackBudget = size_t(1280) << 20;  // most memory a plan asks for, unless told otherwise
+SplitPlan split_plan(int64_t m, int64_t n, int64_t k, size_t budget = kPackBudget);
+void launch_split_gemm(const SplitPlan& p, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim,
+                       const void* A, int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C,
+                       const OutMap& om, void* ws, hipStream_t st, bool conjb);
+// C[m0.., n0..] = alpha sum_s P[s] + beta C over an m x n block of FP32 partials
+void launch_splitk_reduce_f32(int64_t m, int64_t n, int splits, const void* P, double are, double aim, double bre,
+                              double bim, void* C, const OutMap& om, int64_t m0, int64_t n0, hipStream_t st);
 
 // Per-shape tile autotuning of launch_gemm (process-wide).
 void set_gemm_autotune(bool on);

@@ -9,7 +9,8 @@
 // runs this entry point holds until the process ends.  The library never
 // splits a product into more than 256 MiB of partials (gemm_splits and wave_plan cap the
 // split at that size), so the array holds the split the library picks for
-// every shape; a product that would need more is rejected with
+// every shape, and large FP32 products pack their operands into it
+// (split_plan with this size as its budget); one that would need more is rejected with
 // LRCC_E_INVALID.  The partials are written in full before they are read,
 // so nothing has to be cleared between calls.  All calls on one GPU share
 // its array: calls that overlap in time on one GPU (on different streams)
@@ -68,14 +69,16 @@ extern "C" int lrcc_gemm_noalloc(int precision, int transa, int transb, int64_t 
     LRCC_REQUIRE(wsb <= kStaticScratchBytes, LRCC_E_INVALID,
                  "product needs " + std::to_string(wsb) + " bytes of split-K partials, above the " +
                      std::to_string(kStaticScratchBytes) + "-byte static scratch of lrcc_gemm_noalloc");
-    void* ws = wsb ? scratch_on_current_device() : nullptr;
+    SplitPlan sp;  // large FP32 products: packed operands in the same array
+    if (precision == LRCC_MIXED) sp = split_plan(m, n, k, kStaticScratchBytes);
+    void* ws = wsb || sp.use ? scratch_on_current_device() : nullptr;
     const hipStream_t st = (hipStream_t)stream;
     if (precision == LRCC_FP64)
       launch_gemm<double>(transa != 0, transb != 0, m, n, k, alpha[0], alpha[1], A, lda, B, ldb, beta[0], beta[1], C,
                           ldc, st, 0, ws, wsb, nullptr, false, false);
     else
       launch_gemm<float>(transa != 0, transb != 0, m, n, k, alpha[0], alpha[1], A, lda, B, ldb, beta[0], beta[1], C,
-                         ldc, st, 0, ws, wsb, nullptr, false, false);
+                         ldc, st, 0, ws, wsb, nullptr, false, false, &sp, ws);
     HIP_CHECK(hipGetLastError());
     return LRCC_OK;
   } catch (const Error& e) {

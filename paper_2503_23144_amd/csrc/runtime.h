@@ -177,6 +177,8 @@ class Executor {
     OutMap om;  // output layout when mapped
     bool mapped;
     bool conjb;  // use conj(B)
+    void* pack;  // packed operands (scratch slot kPackSlot)
+    SplitPlan sp;
   };
   struct RunKey {
     const OpList* ops;
@@ -242,7 +244,8 @@ class Executor {
             int64_t capC, bool ladder, const OutMap* om = nullptr, bool conjb = false);
   bool output_map(const std::string& Mc, const std::string& Nc, const std::string& cl, OutMap& om) const;
   int cached_permute(int id, const std::string& src, const std::string& dst, const void* p, int64_t cap);
-  static constexpr int kPermSlot = 5;
+  void* pack_scratch(int64_t M, int64_t N, int64_t K, SplitPlan& s);
+  static constexpr int kPermSlot = 5, kPackSlot = 9;
   struct PermEntry {
     int tensor = -1;
     std::vector<int> perm;

@@ -40,9 +40,9 @@ Executor<T>::Executor(const Module& m, Dims d, hipStream_t st) : m_(m), d_(d), s
   bound_.assign(n, 0);
   pooled_.assign(n, 0);
   // 0-2 permutations, 3 virtual constants, 4 split-K partials, 5-6 cached permutations,
-  // 7-8 DF-direct ladder: (ae|bf) block and rebuilt rows of W
-  scr_.assign(9, nullptr);
-  scr_cap_.assign(9, 0);
+  // 7-8 DF-direct ladder: (ae|bf) block and rebuilt rows of W, 9 packed GEMM operands
+  scr_.assign(10, nullptr);
+  scr_cap_.assign(10, 0);
   dot_out_ = dev_alloc(64);
   dot_work_ = dev_alloc(1024 * 16);
 }
@@ -208,6 +208,30 @@ void* Executor<T>::scratch(int slot, size_t bytes) {
   return scr_[slot];
 }
 
+// Scratch for the packed operands of a large FP32 product (split_plan):
+// taken only while it stays below an eighth of the free memory, so that the
+// buffers a run cannot do without keep their room, and not while a graph is
+// captured (a run before the capture has taken it, or the product runs
+// without).  Null when there is none.
+template <typename T>
+void* Executor<T>::pack_scratch(int64_t M, int64_t N, int64_t K, SplitPlan& s) {
+  if (sizeof(T) == 8) return nullptr;
+  s = split_plan(M, N, K);
+  if (!s.use) return nullptr;
+  if (scr_cap_[kPackSlot] < s.bytes) {
+    if (capturing_ || outer_ || 8 * s.bytes > (size_t)dev_available()) return nullptr;
+    try {
+      scratch(kPackSlot, s.bytes);
+    } catch (const Error& e) {
+      if (e.code != LRCC_E_NOMEM) throw;
+      scr_[kPackSlot] = nullptr;  // freed before the failed request
+      scr_cap_[kPackSlot] = 0;
+      return nullptr;
+    }
+  }
+  return scr_[kPackSlot];
+}
+
 // current batch of the op being executed (dims of '#')
 static thread_local int64_t g_nb = 1;
 
@@ -319,9 +343,12 @@ void Executor<T>::gemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double
                      (om || ldc >= N),
                  LRCC_E_INTERNAL, "gemm operands exceed their buffers");
   }
-  const size_t wsb = gemm_workspace_bytes<T>(M, N, K, lda, ldb);
+  SplitPlan sp;
+  void* pack = pack_scratch(M, N, K, sp);
+  const size_t wsb = pack ? 0 : gemm_workspace_bytes<T>(M, N, K, lda, ldb);
   void* ws = wsb ? scratch(4, wsb) : nullptr;
-  GemmArgs g{ta, tb, M, N, K, are, aim, A, lda, B, ldb, bre, C, ldc, ladder, ws, wsb, OutMap(), om != nullptr, conjb};
+  GemmArgs g{ta, tb, M,  N,   K,        are,           aim,   A,    lda,  B,
+             ldb, bre, C, ldc, ladder, ws, wsb, OutMap(), om != nullptr, conjb, pack, sp};
   if (om) g.om = *om;
   if (capturing_) {
     if (timing_ && ladder) {  // leave the graph: the ladder is timed between segments
@@ -331,7 +358,7 @@ void Executor<T>::gemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double
       HIP_CHECK(hipStreamBeginCapture(st_, hipStreamCaptureModeThreadLocal));
     } else {
       launch_gemm<T>(ta, tb, M, N, K, are, aim, A, lda, B, ldb, bre, 0.0, C, ldc, st_, ladder ? 1 : 0, ws, wsb, om,
-                     conjb);
+                     conjb, true, &sp, pack);
     }
     return;
   }
@@ -346,7 +373,7 @@ void Executor<T>::launch_timed(const GemmArgs& g) {
     HIP_CHECK(hipEventRecord(e0, st_));
   }
   launch_gemm<T>(g.ta, g.tb, g.M, g.N, g.K, g.are, g.aim, g.A, g.lda, g.B, g.ldb, g.bre, 0.0, g.C, g.ldc, st_,
-                 g.ladder ? 1 : 0, g.ws, g.wsb, g.mapped ? &g.om : nullptr, g.conjb);
+                 g.ladder ? 1 : 0, g.ws, g.wsb, g.mapped ? &g.om : nullptr, g.conjb, true, &g.sp, g.pack);
   if (timing_) {
     e1 = get_event();
     HIP_CHECK(hipEventRecord(e1, st_));

@@ -46,3 +46,56 @@ def _check(dtype, ta, tb, m, n, k, noalloc):
                                    (257, 130, 300), (33, 65, 2049), (31, 32, 9001)])
 def test_gemm_few_tiles_matches_host(dtype, ta, tb, m, n, k):
     _check(dtype, ta, tb, m, n, k, noalloc=True)
+
+
+# large FP32 products (operands split into three BF16 terms): both tiles, chains
+# of K run side by side and one after the other, an operand packed in row blocks,
+# remainders of every tile, slab and chain.  The bound is that of the other GEMM
+# tests; inputs of mixed magnitude check that small rows keep their own accuracy.
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("m,n,k", [(1300, 1310, 2001), (2900, 1025, 1100), (6005, 1400, 3100), (1201, 5000, 6200)])
+def test_gemm_split_operands_matches_64_bits(ta, tb, m, n, k):
+    from paper_2503_23144_amd import lrcc
+    g = torch.Generator(device="cuda:0").manual_seed(m + n + k)
+    rand = lambda *s: torch.randn(*s, dtype=torch.complex64, device="cuda:0", generator=g)  # noqa: E731
+    A, B, C0 = rand(*((k, m) if ta else (m, k))), rand(*((n, k) if tb else (k, n))), rand(m, n)
+    rows = (10.0 ** -(torch.arange(m, device="cuda:0") % 7)).to(torch.complex64)
+    A = A * (rows[None, :] if ta else rows[:, None])
+    C0 = C0 * rows[:, None]
+    al, be = 0.6 - 0.2j, -0.3 + 0.7j
+    C = C0.clone()
+    lrcc.gemm(A, B, C, transa=bool(ta), transb=bool(tb), alpha=al, beta=be, noalloc=True)
+    D = torch.complex128
+    ref = al * ((A.T if ta else A).to(D) @ (B.T if tb else B).to(D)) + be * C0.to(D)
+    err = (C.to(D) - ref).abs().amax(1) / rows.real.double()
+    scale = np.sqrt(k) * 5.0 * 5.0 + 5.0
+    assert float(err.max()) <= 20 * 2e-7 * scale * np.sqrt(k)
+    # no further from 64 bits than the FP32 matrix cores
+    lrcc.gemm_set_tile(0)
+    try:
+        C2 = C0.clone()
+        lrcc.gemm(A, B, C2, transa=bool(ta), transb=bool(tb), alpha=al, beta=be, noalloc=True)
+    finally:
+        lrcc.gemm_set_tile(-1)
+    rel = [float(((x.to(D) - ref).abs() ** 2).sum(1).div((ref.abs() ** 2).sum(1)).sqrt().max()) for x in (C, C2)]
+    assert rel[0] <= 1.1 * rel[1], rel
+
+
+def test_gemm_split_operands_extreme_inputs():
+    """Values near the ends of the FP32 range, zeros and infinities."""
+    from paper_2503_23144_amd import lrcc
+    m = n = 1536
+    k = 1536
+    z = lambda *s: torch.zeros(*s, dtype=torch.complex64, device="cuda:0")  # noqa: E731
+    A, B, C = z(m, k), z(k, n), z(m, n)
+    A[0, 0], B[0, 0] = 3.4e38, 0.5         # rounds up to infinity in BF16
+    A[1, 1], B[1, 1] = 1.17549435e-38, 1e30  # smallest normal number
+    A[2, 2], B[2, 2] = float("inf"), 2.0
+    A[3, 3], B[3, 3] = float("nan"), 1.0
+    lrcc.gemm(A, B, C, noalloc=True)
+    torch.cuda.synchronize()
+    c = C.cpu().numpy()
+    assert abs(c[0, 0].real - 1.7e38) <= 1e-6 * 1.7e38 and np.isfinite(c[0]).all()
+    assert abs(c[1, 1].real - 1.17549435e-8) <= 1e-6 * 1.2e-8
+    assert not np.isfinite(c[2, 2]) and not np.isfinite(c[3, 3])
+    assert not c[4:].any()
