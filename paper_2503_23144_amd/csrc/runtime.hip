@@ -334,6 +334,18 @@ template <typename T>
 void Executor<T>::gemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double are, double aim, const void* A,
                        int64_t lda, int64_t capA, const void* B, int64_t ldb, int64_t capB, double bre, void* C,
                        int64_t ldc, int64_t capC, bool ladder, const OutMap* om, bool conjb) {
+  // Lanes of the epilogue run along the columns.  A mapped output whose
+  // fastest index is a row index would be written 8 or 16 bytes at a time;
+  // as C^T = B^T A^T that index runs along the lanes.
+  if (om && !conjb && N >= 64 && om->mstr[om->nm - 1] == 1 && om->nstr[om->nn - 1] != 1) {
+    OutMap t;
+    t.nm = om->nn, t.nn = om->nm;
+    for (int k = 0; k < kMapRank; ++k) {
+      t.mdim[k] = om->ndim[k], t.mstr[k] = om->nstr[k];
+      t.ndim[k] = om->mdim[k], t.nstr[k] = om->mstr[k];
+    }
+    return gemm(!tb, !ta, N, M, K, are, aim, B, ldb, capB, A, lda, capA, bre, C, ldc, capC, ladder, &t, false);
+  }
   if (M > 0 && N > 0 && K > 0) {
     int64_t spanA = ta ? (K - 1) * lda + M : (M - 1) * lda + K;
     int64_t spanB = tb ? (N - 1) * ldb + K : (K - 1) * ldb + N;
@@ -384,7 +396,8 @@ void Executor<T>::launch_timed(const GemmArgs& g) {
 
 // Digits of the product's M and N index strings in the layout of the output
 // string cl (row-major): each letter's stride in cl, letters that are also
-// adjacent in cl merged.  False if either side needs more than kMapRank.
+// adjacent in cl merged.  False if either side needs more than kMapRank or
+// is too long for the kernels' 32-bit decode.
 template <typename T>
 bool Executor<T>::output_map(const std::string& Mc, const std::string& Nc, const std::string& cl, OutMap& om) const {
   auto dimof = [&](char l) { return l == '#' ? g_nb : dim(l); };
@@ -415,7 +428,7 @@ bool Executor<T>::output_map(const std::string& Mc, const std::string& Nc, const
     }
     return true;
   };
-  return side(Mc, om.nm, om.mdim, om.mstr) && side(Nc, om.nn, om.ndim, om.nstr);
+  return side(Mc, om.nm, om.mdim, om.mstr) && side(Nc, om.nn, om.ndim, om.nstr) && DevMap::fits(om);
 }
 
 // Permuted copies of batched operands live in two scratch slots for the
