@@ -103,7 +103,7 @@ template <typename T, bool TA, bool TB, int KIND, int BM, int BN, int WGM, int B
 __global__ void __launch_bounds__(64 * NW) zgemm_kernel(int64_t M, int64_t N, int64_t K, T are, T aim,
                                                   const typename cpx<T>::type* __restrict__ A, int64_t lda,
                                                   const typename cpx<T>::type* __restrict__ B, int64_t ldb, T bre,
-                                                  T bim, typename cpx<T>::type* __restrict__ C, OutMap om,
+                                                  T bim, typename cpx<T>::type* __restrict__ C, DevMap om,
                                                   int64_t kchunk, int64_t cstride, T bsgn) {
   using V2 = typename cpx<T>::type;
   constexpr int NT = 64 * NW;
@@ -325,7 +325,7 @@ __global__ void __launch_bounds__(64 * NW) zgemm_kernel(int64_t M, int64_t N, in
 // C = alpha * sum_s P[s] + beta * C over an m x n tile set (split-K reduction)
 template <typename T>
 __global__ void splitk_reduce_kernel(int64_t m, int64_t n, int splits, const typename cpx<T>::type* __restrict__ P,
-                                     T are, T aim, T bre, T bim, typename cpx<T>::type* __restrict__ C, OutMap om,
+                                     T are, T aim, T bre, T bim, typename cpx<T>::type* __restrict__ C, DevMap om,
                                      int64_t m0, int64_t n0) {
   const int64_t total = m * n;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
@@ -353,7 +353,7 @@ static void launch_splitk_reduce(int64_t m, int64_t n, int splits, const void* w
   using V2 = typename cpx<T>::type;
   const unsigned blocks = (unsigned)std::min<int64_t>((m * n + 255) / 256, 4096);
   hipLaunchKernelGGL(splitk_reduce_kernel<T>, dim3(blocks), dim3(256), 0, st, m, n, splits, (const V2*)ws, (T)are,
-                     (T)aim, (T)bre, (T)bim, (V2*)C, om, m0, n0);
+                     (T)aim, (T)bre, (T)bim, (V2*)C, DevMap(om), m0, n0);
   HIP_CHECK(hipGetLastError());
 }
 
@@ -386,7 +386,8 @@ static void go(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, do
   }
 #define GO_(TA_, TB_)                                                                                        \
   hipLaunchKernelGGL((zgemm_kernel<T, TA_, TB_, KIND, BM, BN, WGM, BK, NW>), dim3((unsigned)nb, (unsigned)splits), dim3(NT), \
-                     0, st, m, n, k, (T)ar, (T)ai, (const V2*)A, lda, (const V2*)B, ldb, (T)br, (T)bi, (V2*)out, mo,  \
+                     0, st, m, n, k, (T)ar, (T)ai, (const V2*)A, lda, (const V2*)B, ldb, (T)br, (T)bi, (V2*)out, \
+                     DevMap(mo), \
                      kchunk, cstride, (T)(conjb ? -1.0 : 1.0))
   if (!ta && !tb)
     GO_(false, false);
@@ -596,6 +597,7 @@ void launch_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, 
                  bool allow_tune, const SplitPlan* sp, void* pack_ws) {
   if (m <= 0 || n <= 0) return;
   const OutMap om = omap ? *omap : OutMap::plain(ldc);
+  LRCC_REQUIRE(DevMap::fits(om), LRCC_E_INTERNAL, "output map: more than 2^31 rows or columns");
   if constexpr (sizeof(T) == 4) {
     if (sp && sp->use && pack_ws && forced_tile() < 0) {
       if (trace_on())

@@ -132,7 +132,7 @@ __global__ void __launch_bounds__(256)
 template <int WGM, int WGN, int NS>  // NS slabs per stage
 __global__ void __launch_bounds__(64 * WGM * WGN, 2)
     split_gemm_kernel(int64_t M, int64_t N, int64_t nslab, const char* __restrict__ Ap, const char* __restrict__ Bp,
-                      float are, float aim, float bre, float bim, float2* __restrict__ C, OutMap om, int64_t om0,
+                      float are, float aim, float bre, float bim, float2* __restrict__ C, DevMap om, int64_t om0,
                       int64_t on0, int64_t schunk, int64_t cstride) {
   constexpr int NW = WGM * WGN, BM = 64 * WGM, BN = 64 * WGN;
   constexpr int RA = BM / kRB, RB = BN / kRB;
@@ -283,19 +283,31 @@ void pack(bool kmaj, int64_t rows, int64_t k, const void* X, int64_t ld, bool co
 }
 }  // namespace
 
-// Packing moves 26 bytes per operand element (4 TB/s), the product saves
-// 1.8e-14 s per complex MAC: it pays from m n / (m + n) = 600 on (8052x671x671:
-// 224 us tiled, 150 + 67 us here; 9600x400x22500 would lose).  Below 3e9 MACs
-// the wavefront kernel or the launches decide.  The 128 x 128 tile, 7 %
-// slower per padded element, serves extents that pad the 256-row tile more.
+// Both kernels' times are estimated and this one runs where it saves 8 %:
+// 6 MNK over 190 TFLOP/s here (177 with the 128 x 128 tile, which serves
+// extents that pad the 256-row tile more) and 118 on the tiled kernel, on
+// extents padded to each one's tiles, both 1 + 60 / k times that for the
+// fill and drain of a shallow tile (k = 150: 85 TFLOP/s tiled), and the
+// packing's 26 bytes per operand element at 4.9 TB/s.  Measured, tiled ->
+// here, us: 540000x400x400 5330 -> 4610, 8052x671x671 224 -> 205;
+// 9600x400x22500 (28 % padding) would stay at 4950.  Below a depth of 256 the
+// output's traffic is no longer hidden, one workgroup per CU (480x450000x150
+// 2460 -> 2670); below 2e9 MACs the wavefront kernel or the launches decide.
 // Where the tiles leave the chip's 256 slots (512 for the smaller tile)
 // badly filled, several chains of K run side by side into partials.
 // Operands larger than the budget are packed in row blocks of the larger one.
 SplitPlan split_plan(int64_t m, int64_t n, int64_t k, size_t budget) {
   SplitPlan p;
-  if (m <= 0 || n <= 0 || k < 256 || (double)m * n * k < 3e9 || (double)m * n < 600.0 * (double)(m + n)) return p;
+  if (m <= 0 || n <= 0 || k < 256 || (double)m * n * k < 2e9) return p;
+  auto padded = [](int64_t x, int64_t to) { return (double)(cdiv(x, to) * to); };
+  const double fill = 1.0 + 60.0 / (double)k;
+  const double big_s = padded(m, 256) / 190e12, small_s = padded(m, 128) / 177e12;
+  p.small = small_s < big_s;
+  const double here = 6.0 * std::min(big_s, small_s) * padded(n, 128) * (double)k * fill +
+                      26.0 / 4.9e12 * (double)(m + n) * (double)k + 10e-6;
+  const double tiled = 6.0 * padded(m, 64) * padded(n, 64) * (double)k / 118e12 * fill;
+  if (here > 0.92 * tiled) return p;
   p.use = true;
-  p.small = (double)cdiv(m, 256) * 256 > 1.07 * (double)cdiv(m, 128) * 128;
   p.mc = m, p.nc = n;
   int64_t chains = cdiv(k, kChain);
   const int64_t tiles = cdiv(m, p.small ? 128 : 256) * cdiv(n, 128), slots = p.small ? 512 : 256;
@@ -360,10 +372,10 @@ void launch_split_gemm(const SplitPlan& p, bool ta, bool tb, int64_t m, int64_t 
         const int64_t om0 = parts ? 0 : m0, on0 = parts ? 0 : n0;
         if (p.small)
           hipLaunchKernelGGL((split_gemm_kernel<2, 2, 1>), grid, dim3(256), 0, st, mc, nc, ns, Pa, Pb, al[0], al[1],
-                             be[0], be[1], out, mo, om0, on0, sc, mc * nc);
+                             be[0], be[1], out, DevMap(mo), om0, on0, sc, mc * nc);
         else
           hipLaunchKernelGGL((split_gemm_kernel<4, 2, 2>), grid, dim3(512), 0, st, mc, nc, ns, Pa, Pb, al[0], al[1],
-                             be[0], be[1], out, mo, om0, on0, sc, mc * nc);
+                             be[0], be[1], out, DevMap(mo), om0, on0, sc, mc * nc);
         HIP_CHECK(hipGetLastError());
         if (parts) launch_splitk_reduce_f32(mc, nc, splits, part, are, aim, br, bi, C, om, m0, n0, st);
       }

@@ -33,7 +33,7 @@ template <typename T, bool TA, bool TB, int TI, int TJ, int NW, bool KSPLIT, int
 __global__ void __launch_bounds__(64 * NW)
     wgemm_kernel(int64_t M, int64_t N, int64_t K, T are, T aim, const typename cpx<T>::type* __restrict__ A,
                  int64_t lda, const typename cpx<T>::type* __restrict__ B, int64_t ldb, T bre, T bim,
-                 typename cpx<T>::type* __restrict__ C, OutMap om, int64_t kchunk, int64_t cstride, T bsgn,
+                 typename cpx<T>::type* __restrict__ C, DevMap om, int64_t kchunk, int64_t cstride, T bsgn,
                  int64_t nbm) {
   using V2 = typename cpx<T>::type;
   using ACC = typename cpx<T>::acc;
@@ -217,7 +217,7 @@ static void wgo(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, d
 #define WGO_(TA_, TB_)                                                                                           \
   hipLaunchKernelGGL((wgemm_kernel<T, TA_, TB_, TI, TJ, NW, KSPLIT, U>), dim3((unsigned)nb, (unsigned)splits),   \
                      dim3(64 * NW), 0, st, m, n, k, (T)are, (T)aim, (const V2*)A, lda, (const V2*)B, ldb, (T)bre, \
-                     (T)bim, (V2*)C, om, kchunk, cstride, (T)(conjb ? -1.0 : 1.0), nbm)
+                     (T)bim, (V2*)C, DevMap(om), kchunk, cstride, (T)(conjb ? -1.0 : 1.0), nbm)
   if (!ta && !tb)
     WGO_(false, false);
   else if (!ta && tb)

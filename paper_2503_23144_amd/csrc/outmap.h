@@ -47,4 +47,60 @@ struct OutMap {
   __host__ __device__ int64_t col(int64_t n) const { return off(n, nn, ndim, nstr); }
 };
 
+// The map as the kernels take it.  An epilogue decodes some ten indices per
+// lane; a 32-bit division by a run-time radix costs about 40 instructions, so
+// each radix comes with its reciprocal: q = (mulhi(y, mul) + y) >> sh for y <
+// 2^31.  (FP32 into interleaved tensors, us with divisions -> so: 10800000 x
+// 20 x 20 1380 -> 1212, 3600 x 60000 x 20 1283 -> 1107, 480 x 450000 x 20 1326
+// -> 1152.)
+struct DevMap {
+  struct Side {
+    int nd;
+    uint32_t dim[kMapRank], mul[kMapRank], sh[kMapRank];
+    int64_t str[kMapRank];
+    __device__ int64_t off(int64_t x) const {
+      if (nd == 1) return x * str[0];
+      int64_t o = 0;
+      uint32_t y = (uint32_t)x;
+#pragma unroll
+      for (int k = kMapRank - 1; k >= 0; --k) {
+        if (k >= nd) continue;
+        const uint32_t q = (__umulhi(y, mul[k]) + y) >> sh[k];
+        o += (int64_t)(y - q * dim[k]) * str[k];
+        y = q;
+      }
+      return o;
+    }
+  };
+  Side m, n;
+  __device__ int64_t row(int64_t x) const { return m.off(x); }
+  __device__ int64_t col(int64_t x) const { return n.off(x); }
+
+  static Side side(int nd, const int64_t* dim, const int64_t* str) {
+    Side s{};
+    s.nd = nd;
+    for (int k = 0; k < nd; ++k) {
+      s.str[k] = str[k];
+      const uint64_t d = dim[k] < INT32_MAX ? (uint64_t)dim[k] : (uint64_t)INT32_MAX;
+      uint32_t l = 0;
+      while ((uint64_t(1) << l) < d) ++l;
+      s.dim[k] = (uint32_t)d;
+      s.mul[k] = (uint32_t)(((uint64_t(1) << 32) * ((uint64_t(1) << l) - d)) / d + 1);
+      s.sh[k] = l;
+    }
+    return s;
+  }
+  // Indices stay below 2^31: the product of several radices is checked here
+  // (a single radix is not decoded).
+  static bool fits(const OutMap& o) {
+    auto prod = [](int nd, const int64_t* dim) {
+      double p = 1;
+      for (int k = 0; k < nd; ++k) p *= (double)dim[k];
+      return nd == 1 || p < 2147483648.0;
+    };
+    return prod(o.nm, o.mdim) && prod(o.nn, o.ndim);
+  }
+  explicit DevMap(const OutMap& o) : m(side(o.nm, o.mdim, o.mstr)), n(side(o.nn, o.ndim, o.nstr)) {}
+};
+
 }  // namespace lrcc
