@@ -472,8 +472,7 @@ void Context::mp2_response(int nw, const double* om, cplx& emp2, std::vector<cpl
   invalidate();
   residual64(t.p, R.p, nullptr);
   x64->run(P.eta0, 1);
-  launch_copy_rows<double, double>(1, n1, x64->ptr(P.e_gt1), n1, e0.p, n, st);
-  launch_copy_rows<double, double>(1, n2, x64->ptr(P.e_gt2p), n2, (char*)e0.p + n1 * 16, n, st);
+  launch_join_vectors<double, double>(1, n1, n2, x64->ptr(P.e_gt1), x64->ptr(P.e_gt2p), e0.p, st);
   // t(1), lambda(1) and E_MP2 = E(t(1))
   launch_jacobi(1, n, D.as<double>(), nullptr, nullptr, R.p, t.p, nullptr, st);
   lam.ensure(vb);

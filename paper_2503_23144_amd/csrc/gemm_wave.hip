@@ -230,6 +230,127 @@ static void wgo(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, d
   HIP_CHECK(hipGetLastError());
 }
 
+// The product of two operands in any index order: element (m, k) of A lies at
+// A + ma.row(m) + ma.col(k), (n, k) of B at B + mb.row(n) + mb.col(k), so a
+// small operand needs no permuted copy before its product.  One 16 x 16
+// tile per workgroup, K shared by its NW wavefronts as above; the offsets
+// along K are decoded once per workgroup into LDS.  What bounds it is the
+// latency of one pass (3-5 us), what it saves is the copy's own launch: the
+// right product at o=4, v=16 has 30 of them in 89 launches.
+template <typename T, int NW>
+__global__ void __launch_bounds__(64 * NW)
+    mgemm_kernel(int M, int N, int K, T are, T aim, const typename cpx<T>::type* __restrict__ A, DevMap ma,
+                 const typename cpx<T>::type* __restrict__ B, DevMap mb, T bre, T bim,
+                 typename cpx<T>::type* __restrict__ C, DevMap om, int nbm) {
+  using V2 = typename cpx<T>::type;
+  using ACC = typename cpx<T>::acc;
+  constexpr bool G3 = cpx<T>::gauss;
+  constexpr int U = 4, KS = 4 * U, STEP = KS * NW;
+  __shared__ uint32_t ka[kMapDepth], kb[kMapDepth];
+  __shared__ V2 red[NW][256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int m0 = (int)(blockIdx.x % nbm) * 16, n0 = (int)(blockIdx.x / nbm) * 16;
+  for (int k = tid; k < K; k += 64 * NW) {
+    ka[k] = (uint32_t)ma.col(k);
+    kb[k] = (uint32_t)mb.col(k);
+  }
+  // rows beyond M and columns beyond N feed outputs that are never stored
+  const V2* pa = A + ma.row(m0 + r16 < M ? m0 + r16 : M - 1);
+  const V2* pb = B + mb.row(n0 + r16 < N ? n0 + r16 : N - 1);
+  __syncthreads();
+  struct Frag {
+    V2 a[U], b[U];
+  };
+  auto load = [&](Frag& f, int k0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + kq * U + u;
+      const bool in = k < K;
+      const V2 x = pa[ka[in ? k : 0]], y = pb[kb[in ? k : 0]];
+      f.a[u] = in ? x : V2{0, 0};
+      f.b[u] = in ? y : V2{0, 0};
+    }
+  };
+  ACC acc[3] = {ACC{0, 0, 0, 0}, ACC{0, 0, 0, 0}, ACC{0, 0, 0, 0}};
+  auto products = [&](const Frag& f) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const V2 a = f.a[u], b = f.b[u];
+      if constexpr (!G3) {
+        acc[0] = mfma(a.x, b.x, acc[0]);
+        acc[1] = mfma(a.x, b.y, acc[1]);
+        acc[0] = mfma(-a.y, b.y, acc[0]);
+        acc[1] = mfma(a.y, b.x, acc[1]);
+      } else {
+        acc[0] = mfma(a.x, b.x, acc[0]);
+        acc[1] = mfma(a.y, b.y, acc[1]);
+        acc[2] = mfma(a.x + a.y, b.x + b.y, acc[2]);
+      }
+    }
+  };
+  int k = wave * KS;
+  Frag f0, f1;
+  if (k < K) load(f0, k);
+  while (k < K) {
+    if (k + STEP < K) load(f1, k + STEP);
+    products(f0);
+    k += STEP;
+    if (k >= K) break;
+    if (k + STEP < K) load(f0, k + STEP);
+    products(f1);
+    k += STEP;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    V2 v;
+    if constexpr (!G3)
+      v = V2{acc[0][r], acc[1][r]};
+    else
+      v = V2{acc[0][r] - acc[1][r], acc[2][r] - acc[0][r] - acc[1][r]};
+    red[wave][cpx<T>::row(kq, r) * 16 + r16] = v;
+  }
+  __syncthreads();
+  for (int e = tid; e < 256; e += 64 * NW) {
+    V2 s = red[0][e];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      s.x += red[w][e].x;
+      s.y += red[w][e].y;
+    }
+    const int m = m0 + e / 16, n = n0 + e % 16;
+    if (m >= M || n >= N) continue;
+    T cr = are * s.x - aim * s.y, ci = are * s.y + aim * s.x;
+    V2* c = C + om.row(m) + om.col(n);
+    if (bre != T(0) || bim != T(0)) {
+      const V2 y = *c;
+      cr += bre * y.x - bim * y.y;
+      ci += bre * y.y + bim * y.x;
+    }
+    *c = V2{cr, ci};
+  }
+}
+
+template <typename T>
+void launch_mapped_gemm(int64_t m, int64_t n, int64_t k, double are, double aim, const void* A, const OutMap& ma,
+                        const void* B, const OutMap& mb, double bre, double bim, void* C, const OutMap& om,
+                        hipStream_t st) {
+  using V2 = typename cpx<T>::type;
+  const int64_t nbm = (m + 15) / 16, nb = nbm * ((n + 15) / 16);
+  LRCC_REQUIRE(k <= kMapDepth && nb < (int64_t(1) << 31) && DevMap::fits(ma) && DevMap::fits(mb) && DevMap::fits(om),
+               LRCC_E_INTERNAL, "mapped product too large");
+#define MGO_(NW)                                                                                                   \
+  hipLaunchKernelGGL((mgemm_kernel<T, NW>), dim3((unsigned)nb), dim3(64 * NW), 0, st, (int)m, (int)n, (int)k, (T)are, \
+                     (T)aim, (const V2*)A, DevMap(ma), (const V2*)B, DevMap(mb), (T)bre, (T)bim, (V2*)C,           \
+                     DevMap(om), (int)nbm)
+  if (k > 64 && nb < 512)
+    MGO_(8);
+  else
+    MGO_(4);
+#undef MGO_
+  HIP_CHECK(hipGetLastError());
+}
+
 // Variants: 0 and 1 share one 16 x 16 tile among 8 and 4 wavefronts, 2
 // shares a 32 x 32 tile (8 wavefronts in FP64, 4 deeper-stepping ones in
 // FP32: the FP64 accumulators leave registers for two-deep steps only), 3
@@ -323,7 +444,9 @@ WavePlan wave_plan(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bo
   template void launch_wave_gemm<T>(const WavePlan&, bool, bool, int64_t, int64_t, int64_t, double, double,         \
                                     const void*, int64_t, const void*, int64_t, double, double, void*,              \
                                     const OutMap&, int64_t, hipStream_t, bool);                                     \
-  template WavePlan wave_plan<T>(int64_t, int64_t, int64_t, int64_t, int64_t, bool);
+  template WavePlan wave_plan<T>(int64_t, int64_t, int64_t, int64_t, int64_t, bool);                                \
+  template void launch_mapped_gemm<T>(int64_t, int64_t, int64_t, double, double, const void*, const OutMap&,        \
+                                      const void*, const OutMap&, double, double, void*, const OutMap&, hipStream_t);
 INST_(double)
 INST_(float)
 #undef INST_

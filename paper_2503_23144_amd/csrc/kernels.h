@@ -141,6 +141,14 @@ void launch_wave_gemm(const WavePlan& p, bool ta, bool tb, int64_t m, int64_t n,
                       const void* A, int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C,
                       const OutMap& om, int64_t cstride, hipStream_t st, bool conjb);
 
+// A small product whose operands lie in any index order: ma maps (m, k) and mb
+// (n, k) to element offsets as om does (m, n).  Depth at most kMapDepth.
+constexpr int kMapDepth = 2048;
+template <typename T>
+void launch_mapped_gemm(int64_t m, int64_t n, int64_t k, double are, double aim, const void* A, const OutMap& ma,
+                        const void* B, const OutMap& mb, double bre, double bim, void* C, const OutMap& om,
+                        hipStream_t st);
+
 // Large FP32 products on the BF16 matrix cores (gemm_split.hip): both
 // operands are packed into `bytes` of device memory, mc x nc of the output and
 // kl of the depth at a time.
@@ -212,6 +220,12 @@ void launch_diis_check(int64_t nvec, const void* dots, double tol, int stall, in
 // A singular system restarts the slot's subspace from its newest entry.
 void launch_diis_coef(int64_t nvec, int m, const void* gram, DiisSlot* st_dev, const int* active, void* G,
                       void* coef, hipStream_t st);
+// (x1[r], x2[r]) = x[r] and back, r < rows: vectors [rows][n1 + n2], parts [rows][n1], [rows][n2]
+template <typename Ti, typename To>
+void launch_split_vectors(int64_t rows, int64_t n1, int64_t n2, const void* x, void* x1, void* x2, hipStream_t st);
+template <typename Ti, typename To>
+void launch_join_vectors(int64_t rows, int64_t n1, int64_t n2, const void* x1, const void* x2, void* x,
+                         hipStream_t st);
 // dst[r*dld + i] = (To) src[r*sld + i], i < w, r < rows (complex; strided row copy)
 template <typename Ti, typename To>
 void launch_copy_rows(int64_t rows, int64_t w, const void* src, int64_t sld, void* dst, int64_t dld,

@@ -1126,6 +1126,47 @@ template void launch_copy_rows<double, float>(int64_t, int64_t, const void*, int
 template void launch_copy_rows<float, float>(int64_t, int64_t, const void*, int64_t, void*, int64_t, hipStream_t);
 template void launch_copy_rows<float, double>(int64_t, int64_t, const void*, int64_t, void*, int64_t, hipStream_t);
 
+// Amplitude vectors x[r] = (x1 [n1], x2 [n2]) against their two parts as
+// program tensors, one launch for both (each part of a small vector is a
+// launch-bound copy of its own otherwise).
+template <typename Ti, typename To, bool JOIN>
+__global__ void vector_parts_kernel(int64_t n1, int64_t n2, const typename cplx2<Ti>::type* __restrict__ s,
+                                    const typename cplx2<Ti>::type* __restrict__ s2,
+                                    typename cplx2<To>::type* __restrict__ d,
+                                    typename cplx2<To>::type* __restrict__ d2) {
+  const int64_t r = blockIdx.y, n = n1 + n2;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    const auto x = !JOIN ? s[r * n + i] : i < n1 ? s[r * n1 + i] : s2[r * n2 + i - n1];
+    (JOIN ? d[r * n + i] : i < n1 ? d[r * n1 + i] : d2[r * n2 + i - n1]) = {(To)x.x, (To)x.y};
+  }
+}
+
+template <typename Ti, typename To>
+void launch_split_vectors(int64_t rows, int64_t n1, int64_t n2, const void* x, void* x1, void* x2, hipStream_t st) {
+  if (rows <= 0) return;
+  LRCC_REQUIRE(rows < 65536, LRCC_E_INVALID, "too many rows");
+  hipLaunchKernelGGL((vector_parts_kernel<Ti, To, false>), dim3(nblocks(n1 + n2, 256, 8192), (unsigned)rows), dim3(256),
+                     0, st, n1, n2, (const typename cplx2<Ti>::type*)x, nullptr, (typename cplx2<To>::type*)x1,
+                     (typename cplx2<To>::type*)x2);
+  LAUNCH_CHECK();
+}
+template <typename Ti, typename To>
+void launch_join_vectors(int64_t rows, int64_t n1, int64_t n2, const void* x1, const void* x2, void* x,
+                         hipStream_t st) {
+  if (rows <= 0) return;
+  LRCC_REQUIRE(rows < 65536, LRCC_E_INVALID, "too many rows");
+  hipLaunchKernelGGL((vector_parts_kernel<Ti, To, true>), dim3(nblocks(n1 + n2, 256, 8192), (unsigned)rows), dim3(256),
+                     0, st, n1, n2, (const typename cplx2<Ti>::type*)x1, (const typename cplx2<Ti>::type*)x2,
+                     (typename cplx2<To>::type*)x, nullptr);
+  LAUNCH_CHECK();
+}
+template void launch_split_vectors<double, double>(int64_t, int64_t, int64_t, const void*, void*, void*, hipStream_t);
+template void launch_split_vectors<double, float>(int64_t, int64_t, int64_t, const void*, void*, void*, hipStream_t);
+template void launch_join_vectors<double, double>(int64_t, int64_t, int64_t, const void*, const void*, void*,
+                                                  hipStream_t);
+template void launch_join_vectors<float, float>(int64_t, int64_t, int64_t, const void*, const void*, void*,
+                                                hipStream_t);
+
 __global__ void denominators_kernel(int64_t o, int64_t v, const double* __restrict__ eps, double* __restrict__ D) {
   int64_t n1 = o * v, V = v * (v - 1) / 2, O = o * (o - 1) / 2;
   int64_t n = n1 + O * V;

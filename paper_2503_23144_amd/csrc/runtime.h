@@ -243,6 +243,10 @@ class Executor {
             int64_t lda, int64_t capA, const void* B, int64_t ldb, int64_t capB, double bre, void* C, int64_t ldc,
             int64_t capC, bool ladder, const OutMap* om = nullptr, bool conjb = false);
   bool output_map(const std::string& Mc, const std::string& Nc, const std::string& cl, OutMap& om) const;
+  static constexpr int64_t kMapElems = 1 << 20;
+  bool mapped_product(const Op& op, const std::string& a, const std::string& b, const std::string& c,
+                      const std::string& Mc, const std::string& Nc, const std::string& Kx, const void* pa, int64_t ca,
+                      const void* pb, int64_t cb, void* pc, int64_t cc);
   int cached_permute(int id, const std::string& src, const std::string& dst, const void* p, int64_t cap);
   void* pack_scratch(int64_t M, int64_t N, int64_t K, SplitPlan& s);
   static constexpr int kPermSlot = 5, kPackSlot = 9;

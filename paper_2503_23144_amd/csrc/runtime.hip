@@ -431,6 +431,41 @@ bool Executor<T>::output_map(const std::string& Mc, const std::string& Nc, const
   return side(Mc, om.nm, om.mdim, om.mstr) && side(Nc, om.nn, om.ndim, om.nstr) && DevMap::fits(om);
 }
 
+// A product of small operands that would need permuted copies reads them in
+// place (launch_mapped_gemm).  Up to kMapElems elements per operand the copy's
+// launch costs more than the scattered reads; the depth is bounded by the
+// kernel's table.  False, launching nothing, where it does not apply.
+template <typename T>
+bool Executor<T>::mapped_product(const Op& op, const std::string& a, const std::string& b, const std::string& c,
+                                 const std::string& Mc, const std::string& Nc, const std::string& Kx, const void* pa,
+                                 int64_t ca, const void* pb, int64_t cb, void* pc, int64_t cc) {
+  auto size = [&](const std::string& s) {
+    int64_t p = 1;
+    for (char ch : s) p *= ch == '#' ? g_nb : dim(ch);
+    return p;
+  };
+  const int64_t M = size(Mc), N = size(Nc), K = size(Kx);
+  if (size(a) > kMapElems || size(b) > kMapElems || M * N > 4 * kMapElems || K > kMapDepth) return false;
+  OutMap ma, mb, om;
+  if (!output_map(Mc, Kx, a, ma) || !output_map(Nc, Kx, b, mb) || !output_map(Mc, Nc, c, om)) return false;
+  LRCC_REQUIRE(ma.row(M - 1) + ma.col(K - 1) < ca && mb.row(N - 1) + mb.col(K - 1) < cb &&
+                   om.row(M - 1) + om.col(N - 1) < cc,
+               LRCC_E_INTERNAL, "mapped product exceeds its buffers");
+  hipEvent_t e0 = nullptr;
+  const bool timed = timing_ && !capturing_;
+  if (timed) {
+    e0 = get_event();
+    HIP_CHECK(hipEventRecord(e0, st_));
+  }
+  launch_mapped_gemm<T>(M, N, K, op.are, op.aim, pa, ma, pb, mb, op.acc ? 1.0 : 0.0, 0.0, pc, om, st_);
+  if (timed) {
+    hipEvent_t e1 = get_event();
+    HIP_CHECK(hipEventRecord(e1, st_));
+    pending_.push_back({e0, e1, -1, (sizeof(T) == 8 ? 8.0 : 6.0) * (double)M * (double)N * (double)K});
+  }
+  return true;
+}
+
 // Permuted copies of batched operands live in two scratch slots for the
 // rest of a run, keyed by (tensor, permutation of its index positions).  A
 // tensor is final once it is first read in a program, so a copy made from it
@@ -539,6 +574,8 @@ void Executor<T>::contract(const Op& op, int nb) {
     return (a_ok(Kx) ? 0 : size(a)) + (b_ok(Kx) ? 0 : size(b));
   };
   std::string Kx = cost(Ka) <= cost(Kb) ? Ka : Kb;
+
+  if ((!a_ok(Kx) || !b_ok(Kx)) && !ladder && mapped_product(op, a, b, c, Mc, Nc, Kx, pa, ca, pb, cb, pc, cc)) return;
 
   bool ta, tb;
   int64_t lda, ldb;
@@ -1416,6 +1453,7 @@ void Executor<T>::prepare(const OpList& ops, int nb, const std::vector<int>& kee
 template <typename T>
 void Executor<T>::run_ops(const OpList& ops, int nb) {
   pcache_[0] = pcache_[1] = PermEntry();
+  pnext_ = 0;  // the same copies land in the same slots on every run, captured or not
   for (size_t i = 0; i < ops.size(); ++i) {
     const Op& op = ops[i];
     switch (op.kind) {
@@ -1444,6 +1482,11 @@ void Executor<T>::run(const OpList& ops, int nb, const std::vector<int>& keep) {
   g_nb = nb;
   keep_ = keep;
   prepare(ops, nb, keep);
+  // batched tensors of their own storage grow with max_nb_: before a graph of
+  // this run is looked up or captured, not inside the capture
+  for (const Op& op : ops)
+    for (int u : {op.out, op.a, op.b})
+      if (u >= 0 && m_[u].batched) ptr(u);
   if (!graphs_on_ || outer_) {
     run_ops(ops, nb);
     return;

@@ -442,11 +442,9 @@ void Context::sigma64(Side side, int nb, const void* in, void* out) {
             std::vector<int>{P.l_gt1, P.l_gt2p}, x32.get());
   int a1 = r ? P.r_dt1 : P.l_gO1, a2 = r ? P.r_dt2p : P.l_gO2p;
   int o1 = r ? P.r_dO1 : P.l_gt1, o2 = r ? P.r_dO2p : P.l_gt2p;
-  launch_copy_rows<double, double>(nb, n1, in, n, x64->ptr(a1), n1, st);
-  launch_copy_rows<double, double>(nb, n2, (const char*)in + n1 * 16, n, x64->ptr(a2), n2, st);
+  launch_split_vectors<double, double>(nb, n1, n2, in, x64->ptr(a1), x64->ptr(a2), st);
   x64->run(r ? right_prog(64) : left_prog(64), nb, {o1, o2});
-  launch_copy_rows<double, double>(nb, n1, x64->ptr(o1), n1, out, n, st);
-  launch_copy_rows<double, double>(nb, n2, x64->ptr(o2), n2, (char*)out + n1 * 16, n, st);
+  launch_join_vectors<double, double>(nb, n1, n2, x64->ptr(o1), x64->ptr(o2), out, st);
   sigma_count += nb;
 }
 
@@ -458,11 +456,9 @@ void Context::sigma32(Side side, int nb, const void* in64, void* out32) {
             std::vector<int>{P.l_gt1, P.l_gt2p}, x64.get());
   int a1 = r ? P.r_dt1 : P.l_gO1, a2 = r ? P.r_dt2p : P.l_gO2p;
   int o1 = r ? P.r_dO1 : P.l_gt1, o2 = r ? P.r_dO2p : P.l_gt2p;
-  launch_copy_rows<double, float>(nb, n1, in64, n, x32->ptr(a1), n1, st);
-  launch_copy_rows<double, float>(nb, n2, (const char*)in64 + n1 * 16, n, x32->ptr(a2), n2, st);
+  launch_split_vectors<double, float>(nb, n1, n2, in64, x32->ptr(a1), x32->ptr(a2), st);
   x32->run(r ? right_prog(32) : left_prog(32), nb, {o1, o2});
-  launch_copy_rows<float, float>(nb, n1, x32->ptr(o1), n1, out32, n, st);
-  launch_copy_rows<float, float>(nb, n2, x32->ptr(o2), n2, (char*)out32 + n1 * 8, n, st);
+  launch_join_vectors<float, float>(nb, n1, n2, x32->ptr(o1), x32->ptr(o2), out32, st);
   sigma_count += nb;
 }
 
@@ -485,8 +481,7 @@ void Context::xi_vectors(void* out) {
     gather_mu_blocks(*this, 1, &c, P.x_df);
     x64->run(P.xi, 1, {P.x_dO1, P.x_dO2p});
     char* o = (char*)out + (size_t)c * n * 16;
-    launch_copy_rows<double, double>(1, n1, x64->ptr(P.x_dO1), n1, o, n, st);
-    launch_copy_rows<double, double>(1, n2, x64->ptr(P.x_dO2p), n2, o + n1 * 16, n, st);
+    launch_join_vectors<double, double>(1, n1, n2, x64->ptr(P.x_dO1), x64->ptr(P.x_dO2p), o, st);
   }
 }
 
@@ -502,16 +497,14 @@ void Context::hvp(int nb, const int* comp, const void* Xdt, void* out) {
   x64->set_max_batch(nb);
   make_room(x64.get(), P.hvp, nb, {P.h_out1, P.h_out2p}, x32.get());
   if (Xdt) {
-    launch_copy_rows<double, double>(nb, n1, Xdt, n, x64->ptr(P.h_dt1), n1, st);
-    launch_copy_rows<double, double>(nb, n2, (const char*)Xdt + n1 * 16, n, x64->ptr(P.h_dt2p), n2, st);
+    launch_split_vectors<double, double>(nb, n1, n2, Xdt, x64->ptr(P.h_dt1), x64->ptr(P.h_dt2p), st);
   } else {
     launch_fill_zero<double>(x64->ptr(P.h_dt1), nb * n1, st);
     launch_fill_zero<double>(x64->ptr(P.h_dt2p), nb * n2, st);
   }
   gather_mu_blocks(*this, nb, comp, P.h_df);
   x64->run(P.hvp, nb, {P.h_out1, P.h_out2p});
-  launch_copy_rows<double, double>(nb, n1, x64->ptr(P.h_out1), n1, out, n, st);
-  launch_copy_rows<double, double>(nb, n2, x64->ptr(P.h_out2p), n2, (char*)out + n1 * 16, n, st);
+  launch_join_vectors<double, double>(nb, n1, n2, x64->ptr(P.h_out1), x64->ptr(P.h_out2p), out, st);
 }
 
 static void vec_norms(Context& c, int nb, const void* v, std::vector<double>& out) {
@@ -558,11 +551,9 @@ void Context::fx32(int nb, const void* X64, void* out32) {
   }
   x32->set_max_batch(nb);
   make_room(x32.get(), P.hvpt, nb, {P.f_out1, P.f_out2p}, x64.get());
-  launch_copy_rows<double, float>(nb, n1, X64, n, x32->ptr(P.f_dt1), n1, st);
-  launch_copy_rows<double, float>(nb, n2, (const char*)X64 + n1 * 16, n, x32->ptr(P.f_dt2p), n2, st);
+  launch_split_vectors<double, float>(nb, n1, n2, X64, x32->ptr(P.f_dt1), x32->ptr(P.f_dt2p), st);
   x32->run(P.hvpt, nb, {P.f_out1, P.f_out2p});
-  launch_copy_rows<float, float>(nb, n1, x32->ptr(P.f_out1), n1, out32, n, st);
-  launch_copy_rows<float, float>(nb, n2, x32->ptr(P.f_out2p), n2, (char*)out32 + n1 * 8, n, st);
+  launch_join_vectors<float, float>(nb, n1, n2, x32->ptr(P.f_out1), x32->ptr(P.f_out2p), out32, st);
 }
 
 // ---------------------------------------------------------------- DIIS
@@ -946,8 +937,7 @@ void Context::solve_lambda(SolveStats& so) {
   DevBuf e0;
   e0.ensure(vb);
   x64->run(P.eta0, 1);
-  launch_copy_rows<double, double>(1, n1, x64->ptr(P.e_gt1), n1, e0.p, n, st);
-  launch_copy_rows<double, double>(1, n2, x64->ptr(P.e_gt2p), n2, (char*)e0.p + n1 * 16, n, st);
+  launch_join_vectors<double, double>(1, n1, n2, x64->ptr(P.e_gt1), x64->ptr(P.e_gt2p), e0.p, st);
   lam.ensure(vb);
   launch_jacobi(1, n, D.as<double>(), nullptr, nullptr, e0.p, lam.p, nullptr, st);
   std::vector<SolveStats> ss;

@@ -99,3 +99,34 @@ def test_gemm_split_operands_extreme_inputs():
     assert abs(c[1, 1].real - 1.17549435e-8) <= 1e-6 * 1.2e-8
     assert not np.isfinite(c[2, 2]) and not np.isfinite(c[3, 3])
     assert not c[4:].any()
+
+
+@pytest.mark.parametrize("o,v", [(3, 10), (5, 21), (8, 44)])
+def test_small_workflow_repeats_with_graphs(o, v):
+    """Small systems read permuted operands in place and share one executor
+    between batches of one and three: the truncation workflow and products on
+    a side stream give the same results every time, as without graphs."""
+    from paper_2503_23144_amd import lrcc
+    from paper_2503_23144_amd.synth import make_inputs
+    inp = make_inputs(o, v, 2 * v, seed=5)
+    om = [0.05]
+
+    def workflow(graphs):
+        st = torch.cuda.Stream()
+        c = lrcc.Context(stream=st.cuda_stream, graphs=graphs)
+        out = []
+        for _ in range(4):
+            c.load_df(o, v, inp.B)
+            c.load_fock(inp.fock)
+            c.load_dipoles(inp.mu)
+            for _ in range(3):
+                e0, a0 = c.mp2_response(om)
+            _, occ = c.fnspp_truncate(om, keep=v // 2)
+            e1, a1 = c.mp2_response(om)
+            out.append(np.concatenate([[e0, e1], occ, a0.ravel(), a1.ravel()]))
+        c.close()
+        return out
+
+    ref, got = workflow(False), workflow(True)
+    for x in got:
+        assert np.abs(x - ref[0]).max() <= 1e-12 * np.abs(ref[0]).max()
