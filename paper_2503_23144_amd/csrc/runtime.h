@@ -132,7 +132,8 @@ class Executor {
   // HIP graph replay.  With graphs on, a run whose program, batch and every
   // buffer address match an earlier (eager) run is captured into HIP graphs
   // on the second occurrence and replayed from the third on.  On the null
-  // stream, graph runs execute on a private stream joined to it by events.
+  // stream the capturing run executes on a private stream joined to it by
+  // events; eager runs and replays stay on the null stream itself.
   // With timing on, the ladder GEMMs stay outside the graphs (launched
   // between graph segments) so HIP events can time them; the other GEMMs
   // inside graphs are then not timed.
@@ -209,7 +210,7 @@ class Executor {
   hipStream_t saved_st_ = nullptr;
   int64_t epoch_ = 0;
   Recorded* rec_ = nullptr;
-  hipStream_t gst_ = nullptr;  // private stream of graph runs
+  hipStream_t gst_ = nullptr;  // private stream of capturing runs
   hipEvent_t fork_ = nullptr, join_ = nullptr;
   int64_t replays_ = 0, captures_ = 0;
 

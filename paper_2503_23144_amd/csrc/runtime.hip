@@ -1491,7 +1491,17 @@ void Executor<T>::run(const OpList& ops, int nb, const std::vector<int>& keep) {
     run_ops(ops, nb);
     return;
   }
-  // capture is not possible on the null stream: fork onto the private one
+  auto it = graphs_.find(make_key(ops, nb, keep));
+  if (it == graphs_.end()) {
+    run_ops(ops, nb);  // eager: lazy allocations and GEMM tile tuning happen here
+    if (graphs_.size() >= 64) clear_graphs();
+    graphs_.emplace(make_key(ops, nb, keep), Recorded());
+    return;
+  }
+  if (it->second.state == 1) return replay(it->second);
+  // Capture is not possible on the null stream: this one run goes to the
+  // private stream, joined to it by events.  Eager runs and replays stay on the
+  // caller's stream; the two joins took 77 us of a 295 us product at o=4, v=16.
   const hipStream_t caller = st_;
   const bool fork = caller == nullptr;
   if (fork) {
@@ -1500,16 +1510,7 @@ void Executor<T>::run(const OpList& ops, int nb, const std::vector<int>& keep) {
     st_ = gst_;
   }
   try {
-    auto it = graphs_.find(make_key(ops, nb, keep));
-    if (it == graphs_.end()) {
-      run_ops(ops, nb);  // eager: lazy allocations and GEMM tile tuning happen here
-      if (graphs_.size() >= 64) clear_graphs();
-      graphs_.emplace(make_key(ops, nb, keep), Recorded());
-    } else if (it->second.state == 0) {
-      capture(it->second, ops, nb);
-    } else {
-      replay(it->second);
-    }
+    capture(it->second, ops, nb);
   } catch (...) {
     st_ = caller;
     throw;
@@ -1596,7 +1597,7 @@ template <typename T>
 void Executor<T>::clear_graphs() {
   if (graphs_.empty()) return;
   if (gst_) HIP_CHECK(hipStreamSynchronize(gst_));
-  if (st_) HIP_CHECK(hipStreamSynchronize(st_));
+  HIP_CHECK(hipStreamSynchronize(st_));  // replays run on the caller's stream, the null stream included
   for (auto& kv : graphs_)
     for (hipGraphExec_t e : kv.second.seg)
       if (e) (void)hipGraphExecDestroy(e);
