@@ -55,7 +55,16 @@ __global__ void __launch_bounds__(64 * NW)
     tile = tile * NW + wave;
     if (tile >= nbm * ((N + 16 * TJ - 1) / (16 * TJ))) return;
   }
-  const int64_t m0 = (tile % nbm) * (16 * TI), n0 = (tile / nbm) * (16 * TJ);
+  // Below 8192 tiles each XCD takes a run of neighbouring ones (FP64
+  // 135x1770x1770 94 -> 88 us, 190x11175x11175 3590 -> 3480); longer grids
+  // walk all rows of one column block together, so that the wide operand is
+  // read once (1140x11175x11175 19400 us in runs, 18900 so).
+  int64_t tm = tile % nbm, tn = tile / nbm;
+  if (KSPLIT) {
+    const int64_t nbn = (N + 16 * TJ - 1) / (16 * TJ);
+    if (nbm * nbn < 8192) tile_of(tile, nbm, nbn, tm, tn);
+  }
+  const int64_t m0 = tm * (16 * TI), n0 = tn * (16 * TJ);
 
   // An operand address is a base common to the wavefront (advanced along k)
   // plus a 32-bit byte offset per lane.  Rows beyond M and columns beyond N
@@ -390,7 +399,7 @@ void launch_wave_gemm(const WavePlan& p, bool ta, bool tb, int64_t m, int64_t n,
 //    tiles are few (FP64 600^3 42 against 48 on 32 x 32); 8 wavefronts below
 //    512 tiles, 4 above.
 //  * 32 x 32 tiles otherwise: in FP64 until 1024 tiles of 128 x 128 fill the
-//    chip at the tiled kernel's higher intensity (18000x3000x3000 runs at 66
+//    chip at the tiled kernel's higher intensity (18000x3000x3000 runs at 62-66
 //    TFLOP/s there), in FP32 below 4e9 complex MACs or at most 96 wide
 //    (1728x576x57600 2862 / 3511, 72x240x518400 999 / 810).
 //  * Splits over K fill the chip's workgroup slots: at least 384 depths each
