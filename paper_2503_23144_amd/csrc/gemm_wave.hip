@@ -239,34 +239,75 @@ static void wgo(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, d
   HIP_CHECK(hipGetLastError());
 }
 
-// The product of two operands in any index order: element (m, k) of A lies at
-// A + ma.row(m) + ma.col(k), (n, k) of B at B + mb.row(n) + mb.col(k), so a
-// small operand needs no permuted copy before its product.  One 16 x 16
-// tile per workgroup, K shared by its NW wavefronts as above; the offsets
-// along K are decoded once per workgroup into LDS.  What bounds it is the
-// latency of one pass (3-5 us), what it saves is the copy's own launch: the
-// right product at o=4, v=16 has 30 of them in 89 launches.
+// Small products whose operands lie in any index order: element (m, k) of A
+// lies at A + am(m) + ak(k), (n, k) of B at B + bn(n) + bk(k), so a small operand
+// needs no permuted copy before its product.  One 16 x 16 tile per workgroup,
+// K shared by its NW wavefronts as above; the offsets along K are decoded
+// once per workgroup into LDS.  What bounds such a product is the latency of
+// one pass (3-10 us by its depth, one or a few workgroups of 256 CUs busy), so
+// up to kMapTerms products independent of each other share a launch.  Right
+// product at o = 4, v = 16, FP64: 57 launches in 218 us alone, 33 in 162 in
+// groups; a term of depth 1024 takes 17 us, the matrix cores of one CU.
+template <typename T>
+struct MapTerm {
+  using V2 = typename cpx<T>::type;
+  struct Side {  // DevMap::Side with 32-bit strides: kernel arguments are limited to 4 KB
+    uint32_t dim[kMapRank], mul[kMapRank];
+    int32_t str[kMapRank];
+    uint8_t sh[kMapRank];
+    int nd;
+    __device__ int off(int x) const {
+      if (nd == 1) return x * str[0];
+      int o = 0;
+      uint32_t y = (uint32_t)x;
+#pragma unroll
+      for (int k = kMapRank - 1; k >= 0; --k) {
+        if (k >= nd) continue;
+        const uint32_t q = (__umulhi(y, mul[k]) + y) >> sh[k];
+        o += (int)(y - q * dim[k]) * str[k];
+        y = q;
+      }
+      return o;
+    }
+  };
+  const V2 *A, *B;
+  V2* C;
+  T are, aim, beta;
+  int M, N, K, nbm;
+  Side am, ak, bn, bk, cm, cn;
+};
+constexpr int kMapTerms = 8;
+template <typename T>
+struct MapGroup {
+  int n, first[kMapTerms];  // first workgroup of each term
+  MapTerm<T> t[kMapTerms];
+};
+static_assert(sizeof(MapGroup<double>) <= 3584, "kernel arguments: 4 KB with the implicit ones");
+
 template <typename T, int NW>
-__global__ void __launch_bounds__(64 * NW)
-    mgemm_kernel(int M, int N, int K, T are, T aim, const typename cpx<T>::type* __restrict__ A, DevMap ma,
-                 const typename cpx<T>::type* __restrict__ B, DevMap mb, T bre, T bim,
-                 typename cpx<T>::type* __restrict__ C, DevMap om, int nbm) {
+__global__ void __launch_bounds__(64 * NW) mgemm_kernel(MapGroup<T> g) {
   using V2 = typename cpx<T>::type;
   using ACC = typename cpx<T>::acc;
   constexpr bool G3 = cpx<T>::gauss;
   constexpr int U = 4, KS = 4 * U, STEP = KS * NW;
   __shared__ uint32_t ka[kMapDepth], kb[kMapDepth];
   __shared__ V2 red[NW][256];
+  int ti = 0;
+#pragma unroll
+  for (int i = 1; i < kMapTerms; ++i)
+    if (i < g.n && (int)blockIdx.x >= g.first[i]) ti = i;
+  const MapTerm<T>& p = g.t[ti];
+  const int M = p.M, N = p.N, K = p.K, bid = (int)blockIdx.x - g.first[ti];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kq = lane >> 4;
-  const int m0 = (int)(blockIdx.x % nbm) * 16, n0 = (int)(blockIdx.x / nbm) * 16;
+  const int m0 = (bid % p.nbm) * 16, n0 = (bid / p.nbm) * 16;
   for (int k = tid; k < K; k += 64 * NW) {
-    ka[k] = (uint32_t)ma.col(k);
-    kb[k] = (uint32_t)mb.col(k);
+    ka[k] = (uint32_t)p.ak.off(k);
+    kb[k] = (uint32_t)p.bk.off(k);
   }
   // rows beyond M and columns beyond N feed outputs that are never stored
-  const V2* pa = A + ma.row(m0 + r16 < M ? m0 + r16 : M - 1);
-  const V2* pb = B + mb.row(n0 + r16 < N ? n0 + r16 : N - 1);
+  const V2* pa = p.A + p.am.off(m0 + r16 < M ? m0 + r16 : M - 1);
+  const V2* pb = p.B + p.bn.off(n0 + r16 < N ? n0 + r16 : N - 1);
   __syncthreads();
   struct Frag {
     V2 a[U], b[U];
@@ -274,7 +315,7 @@ __global__ void __launch_bounds__(64 * NW)
   auto load = [&](Frag& f, int k0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int k = k0 + kq * U + u;
+      const int k = k0 + u * 4 + kq;  // neighbouring lane groups read neighbouring depths
       const bool in = k < K;
       const V2 x = pa[ka[in ? k : 0]], y = pb[kb[in ? k : 0]];
       f.a[u] = in ? x : V2{0, 0};
@@ -329,35 +370,69 @@ __global__ void __launch_bounds__(64 * NW)
     }
     const int m = m0 + e / 16, n = n0 + e % 16;
     if (m >= M || n >= N) continue;
-    T cr = are * s.x - aim * s.y, ci = are * s.y + aim * s.x;
-    V2* c = C + om.row(m) + om.col(n);
-    if (bre != T(0) || bim != T(0)) {
+    T cr = p.are * s.x - p.aim * s.y, ci = p.are * s.y + p.aim * s.x;
+    V2* c = p.C + p.cm.off(m) + p.cn.off(n);
+    if (p.beta != T(0)) {
       const V2 y = *c;
-      cr += bre * y.x - bim * y.y;
-      ci += bre * y.y + bim * y.x;
+      cr += p.beta * y.x;
+      ci += p.beta * y.y;
     }
     *c = V2{cr, ci};
   }
 }
 
 template <typename T>
-void launch_mapped_gemm(int64_t m, int64_t n, int64_t k, double are, double aim, const void* A, const OutMap& ma,
-                        const void* B, const OutMap& mb, double bre, double bim, void* C, const OutMap& om,
-                        hipStream_t st) {
+void launch_mapped_gemm(const MappedProduct* p, int n, hipStream_t st) {
   using V2 = typename cpx<T>::type;
-  const int64_t nbm = (m + 15) / 16, nb = nbm * ((n + 15) / 16);
-  LRCC_REQUIRE(k <= kMapDepth && nb < (int64_t(1) << 31) && DevMap::fits(ma) && DevMap::fits(mb) && DevMap::fits(om),
-               LRCC_E_INTERNAL, "mapped product too large");
-#define MGO_(NW)                                                                                                   \
-  hipLaunchKernelGGL((mgemm_kernel<T, NW>), dim3((unsigned)nb), dim3(64 * NW), 0, st, (int)m, (int)n, (int)k, (T)are, \
-                     (T)aim, (const V2*)A, DevMap(ma), (const V2*)B, DevMap(mb), (T)bre, (T)bim, (V2*)C,           \
-                     DevMap(om), (int)nbm)
-  if (k > 64 && nb < 512)
-    MGO_(8);
-  else
-    MGO_(4);
-#undef MGO_
-  HIP_CHECK(hipGetLastError());
+  auto side = [](int nd, const int64_t* dim, const int64_t* str) {
+    const DevMap::Side d = DevMap::side(nd, dim, str);
+    typename MapTerm<T>::Side s{};
+    s.nd = nd;
+    for (int k = 0; k < nd; ++k) {
+      LRCC_REQUIRE(d.str[k] >= 0 && d.str[k] < INT32_MAX, LRCC_E_INTERNAL, "mapped product too large");
+      s.dim[k] = d.dim[k], s.mul[k] = d.mul[k], s.sh[k] = (uint8_t)d.sh[k], s.str[k] = (int32_t)d.str[k];
+    }
+    return s;
+  };
+  for (int i0 = 0; i0 < n; i0 += kMapTerms) {
+    MapGroup<T> g{};
+    g.n = std::min(kMapTerms, n - i0);
+    int64_t nb = 0, depth = 0;
+    for (int i = 0; i < g.n; ++i) {
+      const MappedProduct& q = p[i0 + i];
+      LRCC_REQUIRE(q.m > 0 && q.n > 0 && q.k > 0 && q.k <= kMapDepth && DevMap::fits(q.ma) && DevMap::fits(q.mb) &&
+                       DevMap::fits(q.om) && q.ma.row(q.m - 1) + q.ma.col(q.k - 1) < INT32_MAX &&
+                       q.mb.row(q.n - 1) + q.mb.col(q.k - 1) < INT32_MAX &&
+                       q.om.row(q.m - 1) + q.om.col(q.n - 1) < INT32_MAX,
+                   LRCC_E_INTERNAL, "mapped product too large");
+      const int64_t nbm = (q.m + 15) / 16;
+      g.first[i] = (int)nb;
+      nb += nbm * ((q.n + 15) / 16);
+      LRCC_REQUIRE(nb < INT32_MAX / 1024, LRCC_E_INTERNAL, "mapped product too large");
+      depth = std::max(depth, q.k);
+      g.t[i] = MapTerm<T>{(const V2*)q.A,
+                          (const V2*)q.B,
+                          (V2*)q.C,
+                          (T)q.are,
+                          (T)q.aim,
+                          (T)q.beta,
+                          (int)q.m,
+                          (int)q.n,
+                          (int)q.k,
+                          (int)nbm,
+                          side(q.ma.nm, q.ma.mdim, q.ma.mstr),
+                          side(q.ma.nn, q.ma.ndim, q.ma.nstr),
+                          side(q.mb.nm, q.mb.mdim, q.mb.mstr),
+                          side(q.mb.nn, q.mb.ndim, q.mb.nstr),
+                          side(q.om.nm, q.om.mdim, q.om.mstr),
+                          side(q.om.nn, q.om.ndim, q.om.nstr)};
+    }
+    if (depth > 64 && nb < 512)
+      hipLaunchKernelGGL((mgemm_kernel<T, 8>), dim3((unsigned)nb), dim3(64 * 8), 0, st, g);
+    else
+      hipLaunchKernelGGL((mgemm_kernel<T, 4>), dim3((unsigned)nb), dim3(64 * 4), 0, st, g);
+    HIP_CHECK(hipGetLastError());
+  }
 }
 
 // Variants: 0 and 1 share one 16 x 16 tile among 8 and 4 wavefronts, 2
@@ -454,8 +529,7 @@ WavePlan wave_plan(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bo
                                     const void*, int64_t, const void*, int64_t, double, double, void*,              \
                                     const OutMap&, int64_t, hipStream_t, bool);                                     \
   template WavePlan wave_plan<T>(int64_t, int64_t, int64_t, int64_t, int64_t, bool);                                \
-  template void launch_mapped_gemm<T>(int64_t, int64_t, int64_t, double, double, const void*, const OutMap&,        \
-                                      const void*, const OutMap&, double, double, void*, const OutMap&, hipStream_t);
+  template void launch_mapped_gemm<T>(const MappedProduct*, int, hipStream_t);
 INST_(double)
 INST_(float)
 #undef INST_

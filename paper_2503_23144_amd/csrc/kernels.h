@@ -141,13 +141,20 @@ void launch_wave_gemm(const WavePlan& p, bool ta, bool tb, int64_t m, int64_t n,
                       const void* A, int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C,
                       const OutMap& om, int64_t cstride, hipStream_t st, bool conjb);
 
-// A small product whose operands lie in any index order: ma maps (m, k) and mb
-// (n, k) to element offsets as om does (m, n).  Depth at most kMapDepth.
+// A small product C = alpha A B + beta C whose operands lie in any index order:
+// ma maps (m, k) and mb (n, k) to element offsets as om does (m, n).  Depth at
+// most kMapDepth, offsets below 2^31.
 constexpr int kMapDepth = 2048;
+struct MappedProduct {
+  int64_t m, n, k;
+  double are, aim, beta;
+  const void *A, *B;
+  void* C;
+  OutMap ma, mb, om;
+};
+// n products, none of which reads or writes what another one writes.
 template <typename T>
-void launch_mapped_gemm(int64_t m, int64_t n, int64_t k, double are, double aim, const void* A, const OutMap& ma,
-                        const void* B, const OutMap& mb, double bre, double bim, void* C, const OutMap& om,
-                        hipStream_t st);
+void launch_mapped_gemm(const MappedProduct* p, int n, hipStream_t st);
 
 // Large FP32 products on the BF16 matrix cores (gemm_split.hip): both
 // operands are packed into `bytes` of device memory, mc x nc of the output and

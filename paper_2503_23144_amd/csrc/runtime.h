@@ -13,6 +13,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <functional>
 #include <map>
 #include <string>
 #include <vector>
@@ -214,6 +215,33 @@ class Executor {
   hipEvent_t fork_ = nullptr, join_ = nullptr;
   int64_t replays_ = 0, captures_ = 0;
 
+  // Deferred launches.  Small ops of a run are not launched one by one: each is
+  // queued with the address ranges that it reads and writes, on the level
+  // after the last queued op whose ranges conflict with its own.  flush()
+  // launches level by level, the products of a level together; every launch
+  // that does not go through the queue flushes it first.  Ranges are actual
+  // addresses, so buffers that share a pool slot keep their order.
+  struct Range {
+    const char *lo, *hi;
+    bool meets(const Range& o) const { return lo < o.hi && o.lo < hi; }
+  };
+  Range range(const void* p, int64_t elems) const {
+    return {(const char*)p, (const char*)p + elems * (int64_t)(2 * sizeof(T))};
+  }
+  struct Deferred {
+    int level;
+    std::vector<Range> in;
+    Range out;
+    std::function<void()> launch;  // empty: the product
+    MappedProduct product;
+  };
+  std::vector<Deferred> queue_;
+  void defer(Deferred d);
+  // f launches an op writing `out`; queued when everything it touches is small
+  template <typename F>
+  void issue(std::vector<Range> in, Range out, F f);
+  void flush();
+
   void contract(const Op& op, int nb);
   void contract_virtual(const Op& op);
   // Writes V (letters vlet, as in an op) into dst in the order of `tgt`,
@@ -245,9 +273,10 @@ class Executor {
             int64_t capC, bool ladder, const OutMap* om = nullptr, bool conjb = false);
   bool output_map(const std::string& Mc, const std::string& Nc, const std::string& cl, OutMap& om) const;
   static constexpr int64_t kMapElems = 1 << 20;
+  static constexpr int64_t kGroupTiles = 256, kGroupDepth = 1024;
   bool mapped_product(const Op& op, const std::string& a, const std::string& b, const std::string& c,
                       const std::string& Mc, const std::string& Nc, const std::string& Kx, const void* pa, int64_t ca,
-                      const void* pb, int64_t cb, void* pc, int64_t cc);
+                      const void* pb, int64_t cb, void* pc, int64_t cc, bool copies);
   int cached_permute(int id, const std::string& src, const std::string& dst, const void* p, int64_t cap);
   void* pack_scratch(int64_t M, int64_t N, int64_t K, SplitPlan& s);
   static constexpr int kPermSlot = 5, kPackSlot = 9;

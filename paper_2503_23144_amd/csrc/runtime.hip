@@ -431,34 +431,97 @@ bool Executor<T>::output_map(const std::string& Mc, const std::string& Nc, const
   return side(Mc, om.nm, om.mdim, om.mstr) && side(Nc, om.nn, om.ndim, om.nstr) && DevMap::fits(om);
 }
 
-// A product of small operands that would need permuted copies reads them in
-// place (launch_mapped_gemm).  Up to kMapElems elements per operand the copy's
-// launch costs more than the scattered reads; the depth is bounded by the
-// kernel's table.  False, launching nothing, where it does not apply.
+// Queues an op behind those that it conflicts with.
+template <typename T>
+void Executor<T>::defer(Deferred d) {
+  d.level = 0;
+  for (const Deferred& e : queue_) {
+    bool conflict = e.out.meets(d.out);
+    for (const Range& r : d.in) conflict = conflict || r.meets(e.out);
+    for (const Range& r : e.in) conflict = conflict || r.meets(d.out);
+    if (conflict) d.level = std::max(d.level, e.level + 1);
+  }
+  queue_.push_back(std::move(d));
+}
+
+template <typename T>
+template <typename F>
+void Executor<T>::issue(std::vector<Range> in, Range out, F f) {
+  int64_t most = out.hi - out.lo;
+  for (const Range& r : in) most = std::max<int64_t>(most, r.hi - r.lo);
+  if (timing_ || most > kMapElems * (int64_t)(2 * sizeof(T))) {
+    flush();
+    f();
+    return;
+  }
+  Deferred d{};
+  d.in = std::move(in);
+  d.out = out;
+  d.launch = f;
+  defer(std::move(d));
+}
+
+template <typename T>
+void Executor<T>::flush() {
+  if (queue_.empty()) return;
+  std::vector<Deferred> q;
+  q.swap(queue_);
+  int last = 0;
+  for (const Deferred& d : q) last = std::max(last, d.level);
+  std::vector<MappedProduct> group;
+  for (int l = 0; l <= last; ++l) {
+    group.clear();
+    for (const Deferred& d : q)
+      if (d.level == l) {
+        if (d.launch)
+          d.launch();
+        else
+          group.push_back(d.product);
+      }
+    if (!group.empty()) launch_mapped_gemm<T>(group.data(), (int)group.size(), st_);
+  }
+}
+
+// Products read in place and launched together (launch_mapped_gemm).  One
+// that would need permuted copies (`copies`) runs so up to kMapElems elements
+// per operand, where the copy's launch costs more than the scattered reads;
+// the depth is bounded by the kernel's table.  One that needs none runs so
+// where it leaves most of the chip idle: kGroupTiles tiles of 16 x 16 are one
+// per CU, and beyond kGroupDepth the split of K in the GEMM's own plan is
+// worth its second launch.  False, doing nothing, where it does not apply.
 template <typename T>
 bool Executor<T>::mapped_product(const Op& op, const std::string& a, const std::string& b, const std::string& c,
                                  const std::string& Mc, const std::string& Nc, const std::string& Kx, const void* pa,
-                                 int64_t ca, const void* pb, int64_t cb, void* pc, int64_t cc) {
+                                 int64_t ca, const void* pb, int64_t cb, void* pc, int64_t cc, bool copies) {
   auto size = [&](const std::string& s) {
     int64_t p = 1;
     for (char ch : s) p *= ch == '#' ? g_nb : dim(ch);
     return p;
   };
   const int64_t M = size(Mc), N = size(Nc), K = size(Kx);
+  if (M == 0 || N == 0 || K == 0) return false;
   if (size(a) > kMapElems || size(b) > kMapElems || M * N > 4 * kMapElems || K > kMapDepth) return false;
-  OutMap ma, mb, om;
-  if (!output_map(Mc, Kx, a, ma) || !output_map(Nc, Kx, b, mb) || !output_map(Mc, Nc, c, om)) return false;
-  LRCC_REQUIRE(ma.row(M - 1) + ma.col(K - 1) < ca && mb.row(N - 1) + mb.col(K - 1) < cb &&
-                   om.row(M - 1) + om.col(N - 1) < cc,
+  if (!copies && (timing_ || K > kGroupDepth || ((M + 15) / 16) * ((N + 15) / 16) > kGroupTiles)) return false;
+  MappedProduct p{M, N, K, op.are, op.aim, op.acc ? 1.0 : 0.0, pa, pb, pc, {}, {}, {}};
+  if (!output_map(Mc, Kx, a, p.ma) || !output_map(Nc, Kx, b, p.mb) || !output_map(Mc, Nc, c, p.om)) return false;
+  LRCC_REQUIRE(p.ma.row(M - 1) + p.ma.col(K - 1) < ca && p.mb.row(N - 1) + p.mb.col(K - 1) < cb &&
+                   p.om.row(M - 1) + p.om.col(N - 1) < cc,
                LRCC_E_INTERNAL, "mapped product exceeds its buffers");
+  if (!timing_) {
+    Deferred d{};
+    d.in = {range(pa, size(a)), range(pb, size(b))};
+    d.out = range(pc, size(c));
+    d.product = p;
+    defer(std::move(d));
+    return true;
+  }
   hipEvent_t e0 = nullptr;
-  const bool timed = timing_ && !capturing_;
-  if (timed) {
+  if (!capturing_) {
     e0 = get_event();
     HIP_CHECK(hipEventRecord(e0, st_));
   }
-  launch_mapped_gemm<T>(M, N, K, op.are, op.aim, pa, ma, pb, mb, op.acc ? 1.0 : 0.0, 0.0, pc, om, st_);
-  if (timed) {
+  launch_mapped_gemm<T>(&p, 1, st_);
+  if (!capturing_) {
     hipEvent_t e1 = get_event();
     HIP_CHECK(hipEventRecord(e1, st_));
     pending_.push_back({e0, e1, -1, (sizeof(T) == 8 ? 8.0 : 6.0) * (double)M * (double)N * (double)K});
@@ -490,9 +553,13 @@ int Executor<T>::cached_permute(int id, const std::string& src, const std::strin
 template <typename T>
 void Executor<T>::contract(const Op& op, int nb) {
   (void)nb;
-  if (dl_L_ && (op.a == ladder_const || op.b == ladder_const)) return ladder_direct(op);
-  if (!tri_.empty() && (op.a == ladder_const || op.b == ladder_const)) return ladder_triangle(op);
-  if (is_virtual(op.a) || is_virtual(op.b)) return contract_virtual(op);
+  const bool wop = op.a == ladder_const || op.b == ladder_const;
+  if ((wop && (dl_L_ || !tri_.empty())) || is_virtual(op.a) || is_virtual(op.b)) {
+    flush();
+    if (wop && dl_L_) return ladder_direct(op);
+    if (wop && !tri_.empty()) return ladder_triangle(op);
+    return contract_virtual(op);
+  }
   std::string a = letters(op.a, op.ai), b = letters(op.b, op.bi), c = letters(op.out, op.oi);
   const void* pa = ptr(op.a);
   const void* pb = ptr(op.b);
@@ -538,6 +605,7 @@ void Executor<T>::contract(const Op& op, int nb) {
   const bool acc = op.acc;
 
   if (Mc.empty() && Nc.empty()) {  // full contraction to a scalar
+    flush();
     LRCC_REQUIRE(!m_[op.out].batched, LRCC_E_INTERNAL, "batched scalar output");
     const void* pb2 = pb;
     if (b != a) {
@@ -575,7 +643,9 @@ void Executor<T>::contract(const Op& op, int nb) {
   };
   std::string Kx = cost(Ka) <= cost(Kb) ? Ka : Kb;
 
-  if ((!a_ok(Kx) || !b_ok(Kx)) && !ladder && mapped_product(op, a, b, c, Mc, Nc, Kx, pa, ca, pb, cb, pc, cc)) return;
+  const bool copies = !a_ok(Kx) || !b_ok(Kx);
+  if (!(ladder && copies) && mapped_product(op, a, b, c, Mc, Nc, Kx, pa, ca, pb, cb, pc, cc, copies)) return;
+  flush();
 
   bool ta, tb;
   int64_t lda, ldb;
@@ -996,12 +1066,19 @@ void Executor<T>::add(const Op& op, int nb) {
   (void)nb;
   if (is_virtual(op.a)) {  // a permuted copy of a virtual constant: written straight into the output
     LRCC_REQUIRE(!m_[op.out].batched, LRCC_E_INTERNAL, "add: batch mismatch");
+    flush();
     materialize(op.a, op.ai, op.oi, 0, 0, 0, ptr(op.out), capacity(op.out), op.are, op.aim, op.acc);
     return;
   }
   std::string a = letters(op.a, op.ai), c = letters(op.out, op.oi);
   LRCC_REQUIRE(m_[op.a].batched == m_[op.out].batched, LRCC_E_INTERNAL, "add: batch mismatch");
-  permute_into(ptr(op.a), capacity(op.a), a, ptr(op.out), capacity(op.out), c, op.are, op.aim, op.acc ? 1 : 0, 0);
+  const void* src = ptr(op.a);
+  void* dst = ptr(op.out);
+  const int64_t ca = capacity(op.a), cc = capacity(op.out);
+  issue({range(src, elems(op.a, (int)g_nb))}, range(dst, elems(op.out, (int)g_nb)),
+        [this, src, ca, a, dst, cc, c, re = op.are, im = op.aim, acc = op.acc] {
+          permute_into(src, ca, a, dst, cc, c, re, im, acc ? 1 : 0, 0);
+        });
 }
 
 // Permute-accumulates into one tensor whose sources are in its index order
@@ -1052,6 +1129,7 @@ bool Executor<T>::fuse_adds(const OpList& ops, const std::vector<size_t>& idx, b
   for (size_t g0 = 0; g0 < idx.size(); g0 += 4) {  // at most four sources per launch
     SumSources s = virt_;
     s.n = 0;
+    std::vector<Range> in;
     for (size_t g = g0; g < idx.size() && g < g0 + 4; ++g) {
       const Op& o = ops[idx[g]];
       const bool v = o.a == virt_id_;
@@ -1061,8 +1139,17 @@ bool Executor<T>::fuse_adds(const OpList& ops, const std::vector<size_t>& idx, b
       s.re[s.n] = o.are;
       s.im[s.n] = o.aim;
       ++s.n;
+      if (!v) in.push_back(range(ptr(o.a), total));
+      for (int k = 0; v && k < s.nouter; ++k) {
+        in.push_back(range(s.U[k], (s.ustride[k] ? g_nb : 1) * s.ni * np));
+        in.push_back(range(s.V[k], (s.vstride[k] ? g_nb : 1) * s.nj * nq));
+      }
     }
-    launch_sum_swap<T>(s, ptr(o0.out), g0 == 0 ? o0.acc : true, total / (np * nq), np, nq, st_);
+    void* out = ptr(o0.out);
+    const bool acc = g0 == 0 ? o0.acc : true;
+    issue(std::move(in), range(out, total), [this, s, out, acc, rows = total / (np * nq), np, nq] {
+      launch_sum_swap<T>(s, out, acc, rows, np, nq, st_);
+    });
   }
   return true;
 }
@@ -1262,7 +1349,11 @@ void Executor<T>::pack(const Op& op, int nb) {
   }
   LRCC_REQUIRE(ptot <= capacity(op.out) && fmax < capacity(op.a) && s <= capacity(op.a), LRCC_E_INTERNAL,
                "pack exceeds its buffers");
-  launch_pack<T>(ptr(op.a), ptr(op.out), d, op.are, op.aim, op.acc, st_);
+  const void* full = ptr(op.a);
+  void* packed = ptr(op.out);
+  issue({range(full, s)}, range(packed, ptot), [this, full, packed, d, re = op.are, im = op.aim, acc = op.acc] {
+    launch_pack<T>(full, packed, d, re, im, acc, st_);
+  });
 }
 
 template <typename T>
@@ -1308,7 +1399,12 @@ void Executor<T>::unpack(const Op& op, int nb) {
   }
   LRCC_REQUIRE(d.full_elems <= capacity(op.out) && s <= capacity(op.a), LRCC_E_INTERNAL,
                "unpack exceeds its buffers");
-  launch_unpack<T>(ptr(op.a), ptr(op.out), d, op.are, op.aim, op.acc, st_);
+  const void* packed = ptr(op.a);
+  void* full = ptr(op.out);
+  issue({range(packed, s)}, range(full, d.full_elems),
+        [this, packed, full, d, re = op.are, im = op.aim, acc = op.acc] {
+          launch_unpack<T>(packed, full, d, re, im, acc, st_);
+        });
 }
 
 int64_t tensor_elems(const Module& m, const Dims& d, int id, int nb) {
@@ -1454,6 +1550,7 @@ template <typename T>
 void Executor<T>::run_ops(const OpList& ops, int nb) {
   pcache_[0] = pcache_[1] = PermEntry();
   pnext_ = 0;  // the same copies land in the same slots on every run, captured or not
+  queue_.clear();  // of a run that threw
   for (size_t i = 0; i < ops.size(); ++i) {
     const Op& op = ops[i];
     switch (op.kind) {
@@ -1470,10 +1567,12 @@ void Executor<T>::run_ops(const OpList& ops, int nb) {
       case OpKind::Unpack: unpack(op, nb); break;
       case OpKind::Zero:
         LRCC_REQUIRE(elems(op.out, nb) <= capacity(op.out), LRCC_E_INTERNAL, "zero-fill exceeds its buffer");
-        launch_fill_zero<T>(ptr(op.out), elems(op.out, nb), st_);
+        issue({}, range(ptr(op.out), elems(op.out, nb)),
+              [this, p = ptr(op.out), n = elems(op.out, nb)] { launch_fill_zero<T>(p, n, st_); });
         break;
     }
   }
+  flush();
 }
 
 template <typename T>
