@@ -45,6 +45,25 @@ struct PackDesc {
   int64_t pstride[kMaxRank];  // packed stride of each packed dim
 };
 
+// Ops of one run on packed pairs: packs into one tensor, summed in order
+// (the first plain or accumulating, the others accumulating), and unpacks
+// into different ones.  One launch each where pack_fits / unpack_fits hold
+// for every term and no more than kPackTerms are given.
+constexpr int kPackTerms = 6;
+struct PackTerm {
+  const void* src;
+  void* dst;
+  PackDesc d;
+  double are, aim;
+  bool acc;
+};
+bool pack_fits(const PackDesc& d);
+bool unpack_fits(const PackDesc& d);
+template <typename T>
+void launch_packs(const PackTerm* t, int n, hipStream_t st);
+template <typename T>
+void launch_unpacks(const PackTerm* t, int n, hipStream_t st);
+
 template <typename T>
 void launch_pack(const void* full, void* packed, const PackDesc& d, double are, double aim, bool acc,
                  hipStream_t st);

@@ -285,31 +285,47 @@ __global__ void __launch_bounds__(256) unpack_kernel(const typename cplx2<T>::ty
 
 // Unpack of the common layout: the packed tensor's last dim is a pair
 // (a < b) whose two full dims are the full tensor's last two, an n x n
-// row-major block per outer row.  A workgroup (32 x 8 threads) writes up to
-// TPB consecutive 32 x 32 tiles of one outer row's block.  The packed entries
+// row-major block per outer row.  A workgroup (32 x 8 threads) writes tpb
+// consecutive 32 x 32 tiles of one outer row's block.  The packed entries
 // P(a,b) = b(b-1)/2 + a run along a, so a tile's a < b entries are staged in
 // LDS as [b][a]: the packed reads (along a) and the full writes (along b) are
 // both coalesced.  The a > b entries, -P(b,a) when the pair is antisymmetric
 // (mode 1), run along b and are read directly; the diagonal and, for mode 0,
-// the a > b part are 0.
-constexpr int UT = 32, TPB = 4, PTPB = 1;  // tile edge; tiles per workgroup (unpack, pack)
+// the a > b part are 0.  Bound by memory on large tensors, where four tiles
+// share the row's decode; on small ones by one workgroup's chain of tiles, so
+// there each tile has its own, and the unpacks of a run share a launch
+// (blockIdx.y): the left program's first four at o = 10, v = 60, three
+// vectors, FP64, 55 us -> 22 us.
+constexpr int UT = 32;                     // tile edge
+constexpr int64_t kTailBlocks = 1 << 24;   // workgroups of a launch
+
+struct UnpackArgs {
+  struct Term {
+    const void* packed;
+    void* full;
+    double are, aim;
+    int acc, frank, tailmode;
+    int64_t rows;
+    int64_t fdims[kMaxRank], pstride[kMaxRank];  // both per full dim
+    signed char fsec[kMaxRank], mode[kMaxRank];
+  };
+  Term t[kPackTerms];
+};
 
 template <typename T, typename I>
-__global__ void __launch_bounds__(256) unpack_tail_pair_kernel(const typename cplx2<T>::type* __restrict__ packed,
-                                                               typename cplx2<T>::type* __restrict__ full,
-                                                               PackDesc d, I rows, int n, int nt, T are, T aim,
-                                                               int acc) {
+__global__ void __launch_bounds__(256) unpack_tail_pair_kernel(UnpackArgs args, int n, int nt, int tpb) {
   using C = typename cplx2<T>::type;
   constexpr int NY = 256 / UT;
   __shared__ C tile[UT][UT + 1];
-  const int in = d.rank - 1;
-  const int mode = d.mode[in];
+  const UnpackArgs::Term& d = args.t[blockIdx.y];
+  const int mode = d.tailmode, acc = d.acc;
+  const T are = (T)d.are, aim = (T)d.aim;
   const int tx = threadIdx.x % UT, ty = threadIdx.x / UT;
-  const int tiles = nt * nt, chunks = (tiles + TPB - 1) / TPB;
-  const int64_t nblk = (int64_t)rows * chunks;
+  const int tiles = nt * nt, chunks = (tiles + tpb - 1) / tpb;
+  const int64_t nblk = d.rows * chunks;
   for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-    const I r = (I)(blk / chunks);
-    const int c = (int)(blk % chunks);
+    const I r = (I)((I)blk / (I)chunks);
+    const int c = (int)((I)blk - r * (I)chunks);
     // packed offset and sign of outer row r, in one pass over the outer full
     // dims (the second index of a pair is the dim right after its first)
     I rem = r;
@@ -321,26 +337,25 @@ __global__ void __launch_bounds__(256) unpack_tail_pair_kernel(const typename cp
       const I q = rem / dk;
       const int64_t i = (int64_t)(rem - q * dk);
       rem = q;
-      const int j = d.fmap[k];
       if (d.fsec[k] < 0) {
-        off += i * d.pstride[j];
+        off += i * d.pstride[k];
       } else if (d.fsec[k] == 1) {
         qsec = i;
       } else if (i == qsec) {
         zero = true;
       } else if (i < qsec) {
-        off += (qsec * (qsec - 1) / 2 + i) * d.pstride[j];
-      } else if (d.mode[j]) {
-        off += (i * (i - 1) / 2 + qsec) * d.pstride[j];
+        off += (qsec * (qsec - 1) / 2 + i) * d.pstride[k];
+      } else if (d.mode[k]) {
+        off += (i * (i - 1) / 2 + qsec) * d.pstride[k];
         s = -s;
       } else {
         zero = true;
       }
     }
-    const C* prow = packed + off;
-    C* frow = full + (int64_t)r * n * n;
-    const int t1 = min(tiles, (c + 1) * TPB);
-    for (int t = c * TPB; t < t1; ++t) {
+    const C* prow = (const C*)d.packed + off;
+    C* frow = (C*)d.full + (int64_t)r * n * n;
+    const int t1 = min(tiles, (c + 1) * tpb);
+    for (int t = c * tpb; t < t1; ++t) {
       const int ta = t / nt, tb = t % nt;
       const int a0 = ta * UT, b0 = tb * UT;
       if (!zero && ta <= tb) {
@@ -381,80 +396,106 @@ __global__ void __launch_bounds__(256) unpack_tail_pair_kernel(const typename cp
 }
 
 // Pack of the same layout (the last packed dim a pair (a < b) over the full
-// tensor's last two dims, fp = n, fq = 1; at most two outer pairs).  A
-// workgroup forms the packed entries of up to PTPB tiles ta <= tb of the n x n
-// block of one outer packed row.  For each order of the outer pairs (summed
-// in the order of pack_kernel), full[a][b] is staged in LDS as [a][b] (read
-// along b) and read back along a, and -full[b][a] (mode 1) is read along a
-// directly, so the packed writes P(a,b) = b(b-1)/2 + a (along a) and every
-// read are coalesced.
+// tensor's last two dims, fp = n, fq = 1; at most two outer pairs), summed over
+// up to kPackTerms sources.  A workgroup forms the packed entries of one tile
+// ta <= tb of the n x n block of one outer packed row.  For each order of the
+// outer pairs (summed in the order of pack_kernel), full[a][b] is staged in
+// LDS as [a][b] (read along b) and read back along a, and -full[b][a] (mode 1)
+// is read along a directly, so the packed writes P(a,b) = b(b-1)/2 + a (along
+// a) and every read are coalesced.  Bound by memory; one launch for the five
+// packs that end the right program reads and writes the packed tensor once,
+// not five times (FP32 o = 20, v = 150, 24 vectors: 2.27 ms -> 1.64 ms in
+// all; o = 4, v = 16, FP64: 30 us -> 13 us).
+struct PackArgs {
+  struct Term {
+    const void* full;
+    double are, aim;
+    int mode;  // of the tail pair
+    int64_t fstride[kMaxRank], fp[kMaxRank], fq[kMaxRank];
+    signed char pair[kMaxRank], pmode[kMaxRank];
+  };
+  int n, in, acc;  // sources; outer packed dims
+  int64_t dims[kMaxRank];
+  Term t[kPackTerms];
+};
+
 template <typename T, typename I>
-__global__ void __launch_bounds__(256) pack_tail_pair_kernel(const typename cplx2<T>::type* __restrict__ full,
-                                                             typename cplx2<T>::type* __restrict__ packed,
-                                                             PackDesc d, I rows, int n, int nt, T are, T aim,
-                                                             int acc) {
+__global__ void __launch_bounds__(256)
+    pack_tail_pair_kernel(PackArgs args, typename cplx2<T>::type* __restrict__ packed, I rows, int n, int nt) {
   using C = typename cplx2<T>::type;
   constexpr int NY = 256 / UT, EPT = UT / NY;  // thread rows, outputs per thread
   __shared__ C tile[UT][UT + 1];
-  const int in = d.rank - 1;
-  const int mode = d.mode[in];
+  // per source and order of its outer pairs: offset, sign (0: order unused)
+  __shared__ int64_t co[kPackTerms][4];
+  __shared__ int cs[kPackTerms][4];
   const int tx = threadIdx.x % UT, ty = threadIdx.x / UT;
-  const int tiles = nt * (nt + 1) / 2, chunks = (tiles + PTPB - 1) / PTPB;
-  const int64_t npk = (int64_t)n * (n - 1) / 2, nblk = (int64_t)rows * chunks;
+  const int tiles = nt * (nt + 1) / 2;
+  const int64_t npk = (int64_t)n * (n - 1) / 2, nblk = (int64_t)rows * tiles;
   for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-    const I r = (I)(blk / chunks);
-    const int c = (int)(blk % chunks);
-    // outer packed row r: plain offset and both orders of each outer pair
-    I rem = r;
-    int64_t off = 0, o1a = 0, o2a = 0, o1b = 0, o2b = 0;
-    int np = 0, mda = 0, mdb = 0;
-    for (int k = in - 1; k >= 0; --k) {
-      const I dk = (I)d.dims[k];
-      const I q = rem / dk;
-      const int64_t i = (int64_t)(rem - q * dk);
-      rem = q;
-      if (d.pair[k]) {
-        int64_t pa, pb;
-        decode_pair(i, pa, pb);
-        const int64_t x1 = pa * d.fp[k] + pb * d.fq[k], x2 = pb * d.fp[k] + pa * d.fq[k];
-        if (np == 0) {
-          o1a = x1, o2a = x2, mda = d.mode[k];
+    const I r = (I)(blk / tiles);
+    const int t = (int)(blk % tiles);
+    if ((int)threadIdx.x < args.n) {
+      // outer packed row r: plain offset and both orders of each outer pair
+      const PackArgs::Term& d = args.t[threadIdx.x];
+      I rem = r;
+      int64_t off = 0, o1a = 0, o2a = 0, o1b = 0, o2b = 0;
+      int np = 0, mda = 0, mdb = 0;
+      for (int k = args.in - 1; k >= 0; --k) {
+        const I dk = (I)args.dims[k];
+        const I q = rem / dk;
+        const int64_t i = (int64_t)(rem - q * dk);
+        rem = q;
+        if (d.pair[k]) {
+          int64_t pa, pb;
+          decode_pair(i, pa, pb);
+          const int64_t x1 = pa * d.fp[k] + pb * d.fq[k], x2 = pb * d.fp[k] + pa * d.fq[k];
+          if (np == 0) {
+            o1a = x1, o2a = x2, mda = d.pmode[k];
+          } else {
+            o1b = x1, o2b = x2, mdb = d.pmode[k];
+          }
+          ++np;
         } else {
-          o1b = x1, o2b = x2, mdb = d.mode[k];
+          off += i * d.fstride[k];
         }
-        ++np;
-      } else {
-        off += i * d.fstride[k];
+      }
+      // order mo: bit 0 swaps the first outer pair found (innermost), bit 1 the second
+      for (int mo = 0; mo < 4; ++mo) {
+        const bool ba = (mo & 1) != 0, bb = (mo & 2) != 0;
+        const bool ok = mo < (1 << np) && (!ba || mda) && (!bb || mdb);
+        co[threadIdx.x][mo] = off + (np > 0 ? (ba ? o2a : o1a) : 0) + (np > 1 ? (bb ? o2b : o1b) : 0);
+        cs[threadIdx.x][mo] = !ok ? 0 : ba != bb ? -1 : 1;
       }
     }
-    // order mo: bit 0 swaps the first outer pair found (innermost), bit 1 the second
-    int64_t co[4];
-    T cs[4];
-    bool cok[4];
-#pragma unroll
-    for (int mo = 0; mo < 4; ++mo) {
-      const bool ba = (mo & 1) != 0, bb = (mo & 2) != 0;
-      cok[mo] = mo < (1 << np) && (!ba || mda) && (!bb || mdb);
-      co[mo] = off + (np > 0 ? (ba ? o2a : o1a) : 0) + (np > 1 ? (bb ? o2b : o1b) : 0);
-      cs[mo] = (ba != bb) ? T(-1) : T(1);
-    }
+    __syncthreads();
     C* prow = packed + (int64_t)r * npk;
-    const int t1 = min(tiles, (c + 1) * PTPB);
-    for (int t = c * PTPB; t < t1; ++t) {
-      // tile t -> (ta <= tb), t = tb (tb + 1) / 2 + ta
-      int tb = (int)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
-      while (tb * (tb + 1) / 2 > t) --tb;
-      while ((tb + 1) * (tb + 2) / 2 <= t) ++tb;
-      const int ta = t - tb * (tb + 1) / 2;
-      const int a0 = ta * UT, b0 = tb * UT;
-      T re[EPT], im[EPT];
+    // tile t -> (ta <= tb), t = tb (tb + 1) / 2 + ta
+    int tb = (int)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
+    while (tb * (tb + 1) / 2 > t) --tb;
+    while ((tb + 1) * (tb + 2) / 2 <= t) ++tb;
+    const int ta = t - tb * (tb + 1) / 2;
+    const int a0 = ta * UT, b0 = tb * UT;
+    T re[EPT], im[EPT];
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) re[e] = im[e] = 0;
+    for (int e = 0; e < EPT; ++e) {
+      const int a = a0 + tx, b = b0 + ty + NY * e;
+      re[e] = im[e] = 0;
+      if (args.acc && a < b && b < n) {
+        const C yv = prow[(int64_t)b * (b - 1) / 2 + a];
+        re[e] = yv.x;
+        im[e] = yv.y;
+      }
+    }
+    for (int q = 0; q < args.n; ++q) {
+      const PackArgs::Term& d = args.t[q];
+      T sr[EPT], si[EPT];
 #pragma unroll
+      for (int e = 0; e < EPT; ++e) sr[e] = si[e] = 0;
       for (int mo = 0; mo < 4; ++mo) {
-        if (!cok[mo]) continue;  // uniform over the workgroup
-        const C* fb = full + co[mo];
-        const T sm = cs[mo];
+        const int sgn = cs[q][mo];
+        if (sgn == 0) continue;  // uniform over the workgroup
+        const C* fb = (const C*)d.full + co[q][mo];
+        const T sm = (T)sgn;
         for (int y = ty; y < UT; y += NY) {  // full[a][b] for a = a0 + y, along b
           const int a = a0 + y, b = b0 + tx;
           if (a < n && b < n) tile[y][tx] = fb[(int64_t)a * n + b];
@@ -465,60 +506,102 @@ __global__ void __launch_bounds__(256) pack_tail_pair_kernel(const typename cplx
           const int a = a0 + tx, b = b0 + ty + NY * e;
           if (a < b && b < n) {
             const C x = tile[tx][b - b0];
-            re[e] += sm * x.x;
-            im[e] += sm * x.y;
-            if (mode) {
+            sr[e] += sm * x.x;
+            si[e] += sm * x.y;
+            if (d.mode) {
               const C z = fb[(int64_t)b * n + a];
-              re[e] += -sm * z.x;
-              im[e] += -sm * z.y;
+              sr[e] += -sm * z.x;
+              si[e] += -sm * z.y;
             }
           }
         }
         __syncthreads();  // the tile is rewritten for the next order
       }
+      const T are = (T)d.are, aim = (T)d.aim;
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
-        const int a = a0 + tx, b = b0 + ty + NY * e;
-        if (a < b && b < n) {
-          T rr = are * re[e] - aim * im[e], ii = are * im[e] + aim * re[e];
-          C* pp = prow + (int64_t)b * (b - 1) / 2 + a;
-          if (acc) {
-            const C yv = *pp;
-            rr += yv.x;
-            ii += yv.y;
-          }
-          *pp = C{rr, ii};
-        }
+        re[e] += are * sr[e] - aim * si[e];
+        im[e] += are * si[e] + aim * sr[e];
       }
     }
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const int a = a0 + tx, b = b0 + ty + NY * e;
+      if (a < b && b < n) prow[(int64_t)b * (b - 1) / 2 + a] = C{re[e], im[e]};
+    }
+    __syncthreads();  // co and cs are rewritten for the next row
   }
+}
+
+bool pack_fits(const PackDesc& d) {
+  const int in = d.rank - 1;
+  int outer_pairs = 0;
+  for (int k = 0; k < in; ++k) outer_pairs += d.pair[k] ? 1 : 0;
+  return in >= 0 && d.pair[in] && d.npair[in] >= 2 && d.npair[in] < 46341 && d.fp[in] == d.npair[in] &&
+         d.fq[in] == 1 && outer_pairs <= 2;
+}
+
+bool unpack_fits(const PackDesc& d) {
+  const int in = d.rank - 1;
+  // every pair's second full dim must follow its first (one-pass row decode)
+  bool adjacent = true;
+  for (int k = 0; k < d.frank; ++k)
+    if (d.fsec[k] == 0) adjacent = adjacent && k + 1 < d.frank && d.fsec[k + 1] == 1 && d.fmap[k + 1] == d.fmap[k];
+  if (!(in >= 0 && d.frank >= 2 && adjacent && d.pair[in] && d.fmap[d.frank - 2] == in &&
+        d.fsec[d.frank - 2] == 0 && d.fmap[d.frank - 1] == in && d.fsec[d.frank - 1] == 1 && d.pstride[in] == 1))
+    return false;
+  const int64_t n = d.npair[in];
+  return n >= 2 && n < 46341 && d.fdims[d.frank - 2] == n && d.fdims[d.frank - 1] == n;
+}
+
+template <typename T>
+void launch_packs(const PackTerm* t, int n, hipStream_t st) {
+  using C = typename cplx2<T>::type;
+  LRCC_REQUIRE(n >= 1 && n <= kPackTerms, LRCC_E_INTERNAL, "packs: too many sources");
+  const PackDesc& d0 = t[0].d;
+  PackArgs a{};
+  a.n = n;
+  a.in = d0.rank - 1;
+  a.acc = t[0].acc ? 1 : 0;
+  int64_t total = 1;
+  for (int k = 0; k < d0.rank; ++k) a.dims[k] = d0.dims[k], total *= d0.dims[k];
+  if (total == 0) return;
+  for (int q = 0; q < n; ++q) {
+    const PackDesc& d = t[q].d;
+    bool same = d.rank == d0.rank && t[q].dst == t[0].dst && (q == 0 || t[q].acc) && pack_fits(d);
+    for (int k = 0; k < d0.rank; ++k) same = same && d.dims[k] == d0.dims[k];
+    LRCC_REQUIRE(same, LRCC_E_INTERNAL, "packs: sources do not fit");
+    PackArgs::Term& p = a.t[q];
+    p.full = t[q].src;
+    p.are = t[q].are, p.aim = t[q].aim;
+    p.mode = d.mode[a.in];
+    for (int k = 0; k < a.in; ++k) {
+      p.pair[k] = d.pair[k] ? 1 : 0, p.pmode[k] = d.mode[k] ? 1 : 0;
+      p.fstride[k] = d.fstride[k], p.fp[k] = d.fp[k], p.fq[k] = d.fq[k];
+    }
+  }
+  const int64_t np = d0.npair[a.in], rows = total / d0.dims[a.in], nt = (np + UT - 1) / UT;
+  const int64_t blocks = std::min<int64_t>(rows * (nt * (nt + 1) / 2), kTailBlocks);
+  if (total < (int64_t(1) << 31))
+    hipLaunchKernelGGL((pack_tail_pair_kernel<T, uint32_t>), dim3((unsigned)blocks), dim3(256), 0, st, a,
+                       (C*)t[0].dst, (uint32_t)rows, (int)np, (int)nt);
+  else
+    hipLaunchKernelGGL((pack_tail_pair_kernel<T, int64_t>), dim3((unsigned)blocks), dim3(256), 0, st, a,
+                       (C*)t[0].dst, rows, (int)np, (int)nt);
+  LAUNCH_CHECK();
 }
 
 template <typename T>
 void launch_pack(const void* full, void* packed, const PackDesc& d, double are, double aim, bool acc,
                  hipStream_t st) {
+  if (pack_fits(d)) {
+    const PackTerm t{full, packed, d, are, aim, acc};
+    return launch_packs<T>(&t, 1, st);
+  }
   int64_t total = 1;
   for (int k = 0; k < d.rank; ++k) total *= d.dims[k];
   if (total == 0) return;
   using C = typename cplx2<T>::type;
-  const int in = d.rank - 1;
-  int outer_pairs = 0;
-  for (int k = 0; k < in; ++k) outer_pairs += d.pair[k] ? 1 : 0;
-  if (in >= 0 && d.pair[in] && d.npair[in] >= 2 && d.npair[in] < 46341 && d.fp[in] == d.npair[in] &&
-      d.fq[in] == 1 && outer_pairs <= 2) {
-    const int64_t n = d.npair[in], rows = total / d.dims[in], nt = (n + UT - 1) / UT;
-    const int64_t chunks = (nt * (nt + 1) / 2 + PTPB - 1) / PTPB;
-    const int64_t blocks = std::min<int64_t>(rows * chunks, int64_t(1) << 24);
-    if (total < (int64_t(1) << 31))
-      hipLaunchKernelGGL((pack_tail_pair_kernel<T, uint32_t>), dim3((unsigned)blocks), dim3(256), 0, st,
-                         (const C*)full, (C*)packed, d, (uint32_t)rows, (int)n, (int)nt, (T)are, (T)aim,
-                         acc ? 1 : 0);
-    else
-      hipLaunchKernelGGL((pack_tail_pair_kernel<T, int64_t>), dim3((unsigned)blocks), dim3(256), 0, st,
-                         (const C*)full, (C*)packed, d, rows, (int)n, (int)nt, (T)are, (T)aim, acc ? 1 : 0);
-    LAUNCH_CHECK();
-    return;
-  }
   if (total < (int64_t(1) << 31))
     hipLaunchKernelGGL((pack_kernel<T, uint32_t>), dim3(nblocks(total)), dim3(256), 0, st, (const C*)full,
                        (C*)packed, d, (uint32_t)total, (T)are, (T)aim, acc ? 1 : 0);
@@ -529,33 +612,52 @@ void launch_pack(const void* full, void* packed, const PackDesc& d, double are, 
 }
 
 template <typename T>
+void launch_unpacks(const PackTerm* t, int n, hipStream_t st) {
+  LRCC_REQUIRE(n >= 1 && n <= kPackTerms, LRCC_E_INTERNAL, "unpacks: too many outputs");
+  const int64_t np = t[0].d.npair[t[0].d.rank - 1], nt = (np + UT - 1) / UT;
+  UnpackArgs a{};
+  int64_t rows = 0, most = 0;
+  for (int q = 0; q < n; ++q) {
+    const PackDesc& d = t[q].d;
+    LRCC_REQUIRE(unpack_fits(d) && d.npair[d.rank - 1] == np, LRCC_E_INTERNAL, "unpacks: outputs do not fit");
+    UnpackArgs::Term& p = a.t[q];
+    p.packed = t[q].src, p.full = t[q].dst;
+    p.are = t[q].are, p.aim = t[q].aim;
+    p.acc = t[q].acc ? 1 : 0;
+    p.frank = d.frank;
+    p.tailmode = d.mode[d.rank - 1];
+    p.rows = d.full_elems / (np * np);
+    for (int k = 0; k < d.frank; ++k) {
+      p.fdims[k] = d.fdims[k];
+      p.pstride[k] = d.pstride[d.fmap[k]];
+      p.fsec[k] = (signed char)d.fsec[k];
+      p.mode[k] = d.mode[d.fmap[k]] ? 1 : 0;
+    }
+    rows = std::max(rows, p.rows);
+    most = std::max(most, d.full_elems);
+  }
+  if (rows == 0) return;
+  const int tpb = rows * n * nt * nt >= 16384 ? 4 : 1;  // four tiles in a row once they fill the chip
+  const int64_t blocks = std::min<int64_t>(rows * ((nt * nt + tpb - 1) / tpb), kTailBlocks);
+  if (most < (int64_t(1) << 31))
+    hipLaunchKernelGGL((unpack_tail_pair_kernel<T, uint32_t>), dim3((unsigned)blocks, (unsigned)n), dim3(256), 0, st,
+                       a, (int)np, (int)nt, tpb);
+  else
+    hipLaunchKernelGGL((unpack_tail_pair_kernel<T, int64_t>), dim3((unsigned)blocks, (unsigned)n), dim3(256), 0, st, a,
+                       (int)np, (int)nt, tpb);
+  LAUNCH_CHECK();
+}
+
+template <typename T>
 void launch_unpack(const void* packed, void* full, const PackDesc& d, double are, double aim, bool acc,
                    hipStream_t st) {
+  if (unpack_fits(d)) {
+    const PackTerm t{packed, full, d, are, aim, acc};
+    return launch_unpacks<T>(&t, 1, st);
+  }
   int64_t total = d.full_elems;
   if (total == 0) return;
   using C = typename cplx2<T>::type;
-  const int in = d.rank - 1;
-  // every pair's second full dim must follow its first (one-pass row decode)
-  bool adjacent = true;
-  for (int k = 0; k < d.frank; ++k)
-    if (d.fsec[k] == 0) adjacent = adjacent && k + 1 < d.frank && d.fsec[k + 1] == 1 && d.fmap[k + 1] == d.fmap[k];
-  if (in >= 0 && d.frank >= 2 && adjacent && d.pair[in] && d.fmap[d.frank - 2] == in && d.fsec[d.frank - 2] == 0 &&
-      d.fmap[d.frank - 1] == in && d.fsec[d.frank - 1] == 1 && d.pstride[in] == 1) {
-    const int64_t n = d.npair[in];
-    if (n >= 2 && n < 46341 && d.fdims[d.frank - 2] == n && d.fdims[d.frank - 1] == n) {
-      const int64_t rows = total / (n * n), nt = (n + UT - 1) / UT;
-      const int64_t blocks = std::min<int64_t>(rows * ((nt * nt + TPB - 1) / TPB), int64_t(1) << 24);
-      if (total < (int64_t(1) << 31))
-        hipLaunchKernelGGL((unpack_tail_pair_kernel<T, uint32_t>), dim3((unsigned)blocks), dim3(256), 0, st,
-                           (const C*)packed, (C*)full, d, (uint32_t)rows, (int)n, (int)nt, (T)are, (T)aim,
-                           acc ? 1 : 0);
-      else
-        hipLaunchKernelGGL((unpack_tail_pair_kernel<T, int64_t>), dim3((unsigned)blocks), dim3(256), 0, st,
-                           (const C*)packed, (C*)full, d, rows, (int)n, (int)nt, (T)are, (T)aim, acc ? 1 : 0);
-      LAUNCH_CHECK();
-      return;
-    }
-  }
   if (total < (int64_t(1) << 31))
     hipLaunchKernelGGL((unpack_kernel<T, uint32_t>), dim3(nblocks(total)), dim3(256), 0, st, (const C*)packed,
                        (C*)full, d, (uint32_t)total, (T)are, (T)aim, acc ? 1 : 0);
@@ -1534,6 +1636,8 @@ void launch_materialize(const void* src, void* out, const MatDesc& d0, double ar
 #define INST(T)                                                                                               \
   template void launch_permute<T>(const void*, void*, const PermDesc&, double, double, double, double,       \
                                   hipStream_t);                                                              \
+  template void launch_packs<T>(const PackTerm*, int, hipStream_t);                                            \
+  template void launch_unpacks<T>(const PackTerm*, int, hipStream_t);                                          \
   template void launch_pack<T>(const void*, void*, const PackDesc&, double, double, bool, hipStream_t);      \
   template void launch_unpack<T>(const void*, void*, const PackDesc&, double, double, bool, hipStream_t);    \
   template void launch_fill_zero<T>(void*, int64_t, hipStream_t);                                            \

@@ -230,16 +230,15 @@ class Executor {
   }
   struct Deferred {
     int level;
-    std::vector<Range> in;
-    Range out;
+    std::vector<Range> in, out;
     std::function<void()> launch;  // empty: the product
     MappedProduct product;
   };
   std::vector<Deferred> queue_;
   void defer(Deferred d);
-  // f launches an op writing `out`; queued when everything it touches is small
+  // f launches an op that writes `out`; queued when everything it touches is small
   template <typename F>
-  void issue(std::vector<Range> in, Range out, F f);
+  void issue(std::vector<Range> in, std::vector<Range> out, F f);
   void flush();
 
   void contract(const Op& op, int nb);
@@ -259,8 +258,9 @@ class Executor {
   int virt_id_ = -1;      // tensor evaluated in place by summed permutes (run_dressed)
   SumSources virt_{};     // its outer products
   std::vector<int> keep_;  // tensors the current run keeps
-  void pack(const Op& op, int nb);
-  void unpack(const Op& op, int nb);
+  PackTerm pack_term(const Op& op, int64_t& packed, int64_t& full);  // and the elements of both tensors
+  PackTerm unpack_term(const Op& op, int64_t& packed, int64_t& full);
+  size_t run_packs(const OpList& ops, size_t i);
   void permute_into(const void* src, int64_t src_cap, const std::string& sl, void* dst, int64_t dst_cap,
                     const std::string& dl, double are, double aim, double bre, double bim);
   void* scratch(int slot, size_t bytes);

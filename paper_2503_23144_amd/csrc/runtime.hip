@@ -436,9 +436,13 @@ template <typename T>
 void Executor<T>::defer(Deferred d) {
   d.level = 0;
   for (const Deferred& e : queue_) {
-    bool conflict = e.out.meets(d.out);
-    for (const Range& r : d.in) conflict = conflict || r.meets(e.out);
-    for (const Range& r : e.in) conflict = conflict || r.meets(d.out);
+    auto meet = [](const std::vector<Range>& x, const std::vector<Range>& y) {
+      for (const Range& r : x)
+        for (const Range& q : y)
+          if (r.meets(q)) return true;
+      return false;
+    };
+    const bool conflict = meet(e.out, d.out) || meet(e.out, d.in) || meet(e.in, d.out);
     if (conflict) d.level = std::max(d.level, e.level + 1);
   }
   queue_.push_back(std::move(d));
@@ -446,9 +450,10 @@ void Executor<T>::defer(Deferred d) {
 
 template <typename T>
 template <typename F>
-void Executor<T>::issue(std::vector<Range> in, Range out, F f) {
-  int64_t most = out.hi - out.lo;
-  for (const Range& r : in) most = std::max<int64_t>(most, r.hi - r.lo);
+void Executor<T>::issue(std::vector<Range> in, std::vector<Range> out, F f) {
+  int64_t most = 0;
+  for (const auto* v : {&in, &out})
+    for (const Range& r : *v) most = std::max<int64_t>(most, r.hi - r.lo);
   if (timing_ || most > kMapElems * (int64_t)(2 * sizeof(T))) {
     flush();
     f();
@@ -456,7 +461,7 @@ void Executor<T>::issue(std::vector<Range> in, Range out, F f) {
   }
   Deferred d{};
   d.in = std::move(in);
-  d.out = out;
+  d.out = std::move(out);
   d.launch = f;
   defer(std::move(d));
 }
@@ -510,7 +515,7 @@ bool Executor<T>::mapped_product(const Op& op, const std::string& a, const std::
   if (!timing_) {
     Deferred d{};
     d.in = {range(pa, size(a)), range(pb, size(b))};
-    d.out = range(pc, size(c));
+    d.out = {range(pc, size(c))};
     d.product = p;
     defer(std::move(d));
     return true;
@@ -1075,7 +1080,7 @@ void Executor<T>::add(const Op& op, int nb) {
   const void* src = ptr(op.a);
   void* dst = ptr(op.out);
   const int64_t ca = capacity(op.a), cc = capacity(op.out);
-  issue({range(src, elems(op.a, (int)g_nb))}, range(dst, elems(op.out, (int)g_nb)),
+  issue({range(src, elems(op.a, (int)g_nb))}, {range(dst, elems(op.out, (int)g_nb))},
         [this, src, ca, a, dst, cc, c, re = op.are, im = op.aim, acc = op.acc] {
           permute_into(src, ca, a, dst, cc, c, re, im, acc ? 1 : 0, 0);
         });
@@ -1147,7 +1152,7 @@ bool Executor<T>::fuse_adds(const OpList& ops, const std::vector<size_t>& idx, b
     }
     void* out = ptr(o0.out);
     const bool acc = g0 == 0 ? o0.acc : true;
-    issue(std::move(in), range(out, total), [this, s, out, acc, rows = total / (np * nq), np, nq] {
+    issue(std::move(in), {range(out, total)}, [this, s, out, acc, rows = total / (np * nq), np, nq] {
       launch_sum_swap<T>(s, out, acc, rows, np, nq, st_);
     });
   }
@@ -1307,8 +1312,7 @@ static void align(const std::string& pk, const std::string& fl, std::vector<int>
 }
 
 template <typename T>
-void Executor<T>::pack(const Op& op, int nb) {
-  (void)nb;
+PackTerm Executor<T>::pack_term(const Op& op, int64_t& packed, int64_t& full) {
   LRCC_REQUIRE(!is_virtual(op.a), LRCC_E_INTERNAL, "pack of a virtual constant");
   std::string pk = letters(op.out, op.oi), fl = letters(op.a, op.ai);
   auto dimof = [&](char l) { return l == '#' ? g_nb : dim(l); };
@@ -1349,16 +1353,12 @@ void Executor<T>::pack(const Op& op, int nb) {
   }
   LRCC_REQUIRE(ptot <= capacity(op.out) && fmax < capacity(op.a) && s <= capacity(op.a), LRCC_E_INTERNAL,
                "pack exceeds its buffers");
-  const void* full = ptr(op.a);
-  void* packed = ptr(op.out);
-  issue({range(full, s)}, range(packed, ptot), [this, full, packed, d, re = op.are, im = op.aim, acc = op.acc] {
-    launch_pack<T>(full, packed, d, re, im, acc, st_);
-  });
+  packed = ptot, full = s;
+  return PackTerm{ptr(op.a), ptr(op.out), d, op.are, op.aim, op.acc};
 }
 
 template <typename T>
-void Executor<T>::unpack(const Op& op, int nb) {
-  (void)nb;
+PackTerm Executor<T>::unpack_term(const Op& op, int64_t& packed, int64_t& full) {
   LRCC_REQUIRE(!is_virtual(op.a), LRCC_E_INTERNAL, "unpack of a virtual constant");
   std::string pk = letters(op.a, op.ai), fl = letters(op.out, op.oi);
   auto dimof = [&](char l) { return l == '#' ? g_nb : dim(l); };
@@ -1399,12 +1399,56 @@ void Executor<T>::unpack(const Op& op, int nb) {
   }
   LRCC_REQUIRE(d.full_elems <= capacity(op.out) && s <= capacity(op.a), LRCC_E_INTERNAL,
                "unpack exceeds its buffers");
-  const void* packed = ptr(op.a);
-  void* full = ptr(op.out);
-  issue({range(packed, s)}, range(full, d.full_elems),
-        [this, packed, full, d, re = op.are, im = op.aim, acc = op.acc] {
-          launch_unpack<T>(packed, full, d, re, im, acc, st_);
-        });
+  packed = s, full = d.full_elems;
+  return PackTerm{ptr(op.a), ptr(op.out), d, op.are, op.aim, op.acc};
+}
+
+// Runs the Pack (Unpack) ops from ops[i] on that fit one launch: packs summed
+// into one tensor, unpacks into tensors that no other op of the launch
+// touches (by address: the pool may have given an output the buffer of a
+// source that is not read again).  Returns the index after them.
+template <typename T>
+size_t Executor<T>::run_packs(const OpList& ops, size_t i) {
+  const bool packs = ops[i].kind == OpKind::Pack;
+  std::vector<PackTerm> t;
+  std::vector<Range> in, out;
+  size_t w = i;
+  for (; w < ops.size() && ops[w].kind == ops[i].kind && w - i < (size_t)kPackTerms; ++w) {
+    int64_t np, nf;
+    const PackTerm x = packs ? pack_term(ops[w], np, nf) : unpack_term(ops[w], np, nf);
+    const Range src = range(x.src, packs ? nf : np), dst = range(x.dst, packs ? np : nf);
+    bool fits = packs ? pack_fits(x.d) : unpack_fits(x.d);
+    if (!t.empty()) {
+      const PackTerm& f = t[0];
+      const int tail = x.d.rank - 1;
+      if (packs)
+        fits = fits && x.dst == f.dst && x.acc && x.d.rank == f.d.rank;
+      else
+        fits = fits && x.d.npair[tail] == f.d.npair[f.d.rank - 1];
+      for (int k = 0; packs && fits && k <= tail; ++k) fits = x.d.dims[k] == f.d.dims[k];
+      for (const Range& r : in) fits = fits && !r.meets(dst);
+      for (const Range& r : out) fits = fits && !r.meets(src) && (packs || !r.meets(dst));
+      if (!fits) break;
+    }
+    t.push_back(x);
+    in.push_back(src);
+    if (out.empty() || !packs) out.push_back(dst);
+    if (!fits || src.meets(dst)) {  // on its own
+      ++w;
+      break;
+    }
+  }
+  issue(std::move(in), std::move(out), [this, packs, t] {
+    if (t.size() == 1 && packs)
+      launch_pack<T>(t[0].src, t[0].dst, t[0].d, t[0].are, t[0].aim, t[0].acc, st_);
+    else if (t.size() == 1)
+      launch_unpack<T>(t[0].src, t[0].dst, t[0].d, t[0].are, t[0].aim, t[0].acc, st_);
+    else if (packs)
+      launch_packs<T>(t.data(), (int)t.size(), st_);
+    else
+      launch_unpacks<T>(t.data(), (int)t.size(), st_);
+  });
+  return w;
 }
 
 int64_t tensor_elems(const Module& m, const Dims& d, int id, int nb) {
@@ -1563,11 +1607,11 @@ void Executor<T>::run_ops(const OpList& ops, int nb) {
         break;
       }
       case OpKind::Add: i = run_adds(ops, i, nb) - 1; break;
-      case OpKind::Pack: pack(op, nb); break;
-      case OpKind::Unpack: unpack(op, nb); break;
+      case OpKind::Pack:
+      case OpKind::Unpack: i = run_packs(ops, i) - 1; break;
       case OpKind::Zero:
         LRCC_REQUIRE(elems(op.out, nb) <= capacity(op.out), LRCC_E_INTERNAL, "zero-fill exceeds its buffer");
-        issue({}, range(ptr(op.out), elems(op.out, nb)),
+        issue({}, {range(ptr(op.out), elems(op.out, nb))},
               [this, p = ptr(op.out), n = elems(op.out, nb)] { launch_fill_zero<T>(p, n, st_); });
         break;
     }

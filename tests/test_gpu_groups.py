@@ -36,3 +36,33 @@ def test_grouped_runs_match_single_launches(o, v, nb, precision, tol):
         for f, r in zip(calls, ref):
             assert np.abs(f() - r).max() <= tol * np.abs(r).max(), run
     c.close()
+
+
+@pytest.mark.parametrize("o,v", [(2, 3), (3, 31), (2, 32), (3, 33), (2, 65)])
+def test_summed_packs_match_oracle_at_tile_edges(o, v):
+    """The packs that end the right program and the unpacks that start the left
+    one share launches over 32 x 32 tiles of the virtual pair.  FP64 sums of at
+    most v^2 + o v < 5000 terms, sqrt(5000) * 2^-53 < 1e-14, times the depth of
+    the program (< 20), against the largest element."""
+    import torch
+
+    from oracle.response import Problem, left_sigma, right_sigma
+    from paper_2503_23144_amd import lrcc
+    print(f"packs o={o} v={v}", flush=True)
+    inp = make_inputs(o, v, o + v, seed=o * v)
+    P = Problem.from_arrays(inp.B, inp.fock, inp.mu, inp.o)
+    c = lrcc.Context(precision="fp64", tol=1e-11)
+    c.load_df(inp.o, inp.v, inp.B)
+    c.load_fock(inp.fock)
+    c.load_dipoles(inp.mu)
+    rng = np.random.default_rng(o + v)
+    t = 0.05 * (rng.standard_normal(c.n) + 1j * rng.standard_normal(c.n))
+    X = rng.standard_normal((2, c.n)) + 1j * rng.standard_normal((2, c.n))
+    c.sigma("residual", t)
+    c.set_amplitudes(lrcc.AMP_T, t)
+    for side, fn in (("right", right_sigma), ("left", left_sigma)):
+        got = c.sigma(side, X)
+        for r in range(2):
+            ref = fn(P, torch.as_tensor(t), torch.as_tensor(X[r])).resolve_conj().numpy()
+            assert np.abs(got[r] - ref).max() <= 1e-12 * np.abs(ref).max(), (side, r)
+    c.close()
