@@ -272,7 +272,8 @@ class Executor {
             int64_t lda, int64_t capA, const void* B, int64_t ldb, int64_t capB, double bre, void* C, int64_t ldc,
             int64_t capC, bool ladder, const OutMap* om = nullptr, bool conjb = false);
   bool output_map(const std::string& Mc, const std::string& Nc, const std::string& cl, OutMap& om) const;
-  static constexpr int64_t kMapElems = 1 << 20;
+  static constexpr int64_t kMapElems = 1 << 23;
+  static constexpr double kMapMacs = sizeof(T) == 8 ? 0x1p28 : 0x1p24;
   static constexpr int64_t kGroupTiles = 256, kGroupDepth = 1024;
   bool mapped_product(const Op& op, const std::string& a, const std::string& b, const std::string& c,
                       const std::string& Mc, const std::string& Nc, const std::string& Kx, const void* pa, int64_t ca,

@@ -488,9 +488,12 @@ void Executor<T>::flush() {
 }
 
 // Products read in place and launched together (launch_mapped_gemm).  One
-// that would need permuted copies (`copies`) runs so up to kMapElems elements
-// per operand, where the copy's launch costs more than the scattered reads;
-// the depth is bounded by the kernel's table.  One that needs none runs so
+// that would need permuted copies (`copies`) runs so up to kMapMacs complex
+// multiplications (and kMapElems elements per operand), where the copies cost
+// more than the scattered reads of 16 x 16 tiles; FP32 with its faster GEMMs
+// reaches that point earlier.  Limit 2^24 / 2^26 / 2^28, us: left o = 10, v = 60,
+// three vectors, FP64 1081 / 1052 / 1023; right o = 11, v = 61, 12 vectors, FP32
+// 1670 / 1714 / 1716.  The depth is bounded by the kernel's table.  One that needs none runs so
 // where it leaves most of the chip idle: kGroupTiles tiles of 16 x 16 are one
 // per CU, and beyond kGroupDepth the split of K in the GEMM's own plan is
 // worth its second launch.  False, doing nothing, where it does not apply.
@@ -506,6 +509,7 @@ bool Executor<T>::mapped_product(const Op& op, const std::string& a, const std::
   const int64_t M = size(Mc), N = size(Nc), K = size(Kx);
   if (M == 0 || N == 0 || K == 0) return false;
   if (size(a) > kMapElems || size(b) > kMapElems || M * N > 4 * kMapElems || K > kMapDepth) return false;
+  if (copies && (double)M * N * K > kMapMacs) return false;
   if (!copies && (timing_ || K > kGroupDepth || ((M + 15) / 16) * ((N + 15) / 16) > kGroupTiles)) return false;
   MappedProduct p{M, N, K, op.are, op.aim, op.acc ? 1.0 : 0.0, pa, pb, pc, {}, {}, {}};
   if (!output_map(Mc, Kx, a, p.ma) || !output_map(Nc, Kx, b, p.mb) || !output_map(Mc, Nc, c, p.om)) return false;
