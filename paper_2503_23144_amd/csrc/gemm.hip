@@ -572,6 +572,7 @@ static int forced_tile() {
   return t;
 }
 
+bool gemm_tile_forced() { return forced_tile() >= 0; }
 void set_gemm_tile(int tile) { g_forced_tile.store(tile >= 0 && tile <= 4 ? tile : -1); }
 
 // Split-K for deep products whose tile grid (64 x 64, or 128 x 32 where
@@ -627,7 +628,7 @@ void launch_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, 
   const OutMap om = omap ? *omap : OutMap::plain(ldc);
   LRCC_REQUIRE(DevMap::fits(om), LRCC_E_INTERNAL, "output map: more than 2^31 rows or columns");
   if constexpr (sizeof(T) == 4) {
-    if (sp && sp->use && pack_ws && forced_tile() < 0) {
+    if (sp && sp->use && pack_ws && (forced_tile() < 0 || sp->amap || sp->bmap)) {
       if (trace_on())
         fprintf(stderr, "[lrcc gemm] c64 ta=%d tb=%d kind=%d m=%lld n=%lld k=%lld tile=b%d splits=%d\n", (int)ta,
                 (int)tb, kind, (long long)m, (long long)n, (long long)k, sp->small ? 1 : 0, sp->splits);

@@ -82,24 +82,48 @@ __device__ inline void split3(float x, uint16_t& h, uint16_t& m, uint16_t& l) {
 }  // namespace
 
 // One workgroup: 128 rows x 16 depths at a time, read along the operand's
-// contiguous dimension and turned in LDS, so that every thread splits eight
-// consecutive depths of one row and writes 16 bytes per component and term.
-template <bool KMAJ>
+// contiguous dimension (rows with KMAJ, else depths) and turned in LDS, so that
+// every thread splits eight consecutive depths of one row and writes 16 bytes
+// per component and term.  With MAP the element (r, k) lies at X + map.row(r0
+// + r) + map.col(k0 + k).  Bound by memory: 8 bytes read and 18 written per
+// element.
+template <bool KMAJ, bool MAP>
 __global__ void __launch_bounds__(256)
-    split_pack_kernel(int64_t rows, int64_t K, const float2* __restrict__ X, int64_t ld, float sgn, int64_t nslab,
-                      uint4* __restrict__ P) {
+    split_pack_kernel(int64_t rows, int64_t K, const float2* __restrict__ X, int64_t ld, DevMap map, int64_t rbase,
+                      int64_t kbase, float sgn, int64_t nslab, uint4* __restrict__ P) {
   __shared__ float2 t[kRB][kSlab + 1];
+  constexpr int NQ = kRB * kSlab / 256;
   const int tid = threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.x * kRB;
+  int64_t roff[KMAJ ? 1 : NQ];
+  if constexpr (MAP) {
+#pragma unroll
+    for (int q = 0; q < (KMAJ ? 1 : NQ); ++q) {
+      const int64_t r = r0 + (KMAJ ? tid % kRB : (q * 256 + tid) / kSlab);
+      roff[q] = map.row(rbase + (r < rows ? r : 0));
+    }
+  }
   for (int64_t s = blockIdx.y; s < nslab; s += gridDim.y) {
     const int64_t k0 = s * kSlab;
+    int64_t koff = 0;
+    if constexpr (MAP && !KMAJ) {
+      const int64_t k = k0 + tid % kSlab;
+      koff = map.col(kbase + (k < K ? k : 0));
+    }
 #pragma unroll
-    for (int q = 0; q < kRB * kSlab / 256; ++q) {
+    for (int q = 0; q < NQ; ++q) {
       const int e = q * 256 + tid;
       const int row = KMAJ ? e % kRB : e / kSlab, kk = KMAJ ? e / kRB : e % kSlab;
       const int64_t r = r0 + row, k = k0 + kk;
       const bool in = r < rows && k < K;
-      const float2 v = X[in ? (KMAJ ? k * ld + r : r * ld + k) : 0];
+      int64_t at;
+      if constexpr (!MAP)
+        at = KMAJ ? k * ld + r : r * ld + k;
+      else if constexpr (KMAJ)
+        at = roff[0] + map.col(kbase + (k < K ? k : 0));
+      else
+        at = roff[q] + koff;
+      const float2 v = X[MAP || in ? at : 0];
       t[row][kk] = in ? float2{v.x, v.y * sgn} : float2{0.0f, 0.0f};
     }
     __syncthreads();
@@ -270,15 +294,24 @@ int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 int64_t slabs(int64_t k) { return cdiv(k, 2 * kSlab) * 2; }  // padded to whole stages
 size_t pack_bytes(int64_t rows, int64_t k) { return (size_t)(cdiv(rows, kRB) * 3 * slabs(k)) * kChunk; }
 
-void pack(bool kmaj, int64_t rows, int64_t k, const void* X, int64_t ld, bool conj, void* P, hipStream_t st) {
+void pack(bool kmaj, int64_t rows, int64_t k, const void* X, int64_t ld, bool conj, void* P, hipStream_t st,
+          const OutMap* map = nullptr, int64_t r0 = 0, int64_t k0 = 0) {
   const int64_t ns = slabs(k);
   const dim3 grid((unsigned)cdiv(rows, kRB), (unsigned)std::min<int64_t>(ns, 4096));
-  if (kmaj)
-    hipLaunchKernelGGL(split_pack_kernel<true>, grid, dim3(256), 0, st, rows, k, (const float2*)X, ld,
-                       conj ? -1.0f : 1.0f, ns, (uint4*)P);
+  if (map) kmaj = map->mstr[map->nm - 1] == 1;
+  const DevMap dm(map ? *map : OutMap::plain(ld));
+#define PACK_(KM, MP)                                                                                              \
+  hipLaunchKernelGGL((split_pack_kernel<KM, MP>), grid, dim3(256), 0, st, rows, k, (const float2*)X, ld, dm, r0, k0, \
+                     conj ? -1.0f : 1.0f, ns, (uint4*)P)
+  if (kmaj && map)
+    PACK_(true, true);
+  else if (kmaj)
+    PACK_(true, false);
+  else if (map)
+    PACK_(false, true);
   else
-    hipLaunchKernelGGL(split_pack_kernel<false>, grid, dim3(256), 0, st, rows, k, (const float2*)X, ld,
-                       conj ? -1.0f : 1.0f, ns, (uint4*)P);
+    PACK_(false, false);
+#undef PACK_
   HIP_CHECK(hipGetLastError());
 }
 }  // namespace
@@ -343,6 +376,8 @@ SplitPlan split_plan(int64_t m, int64_t n, int64_t k, size_t budget) {
 void launch_split_gemm(const SplitPlan& p, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim,
                        const void* A, int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C,
                        const OutMap& om, void* ws, hipStream_t st, bool conjb) {
+  LRCC_REQUIRE((!p.amap || DevMap::fits(p.ma)) && (!p.bmap || DevMap::fits(p.mb)), LRCC_E_INTERNAL,
+               "operand map: more than 2^31 rows or depths");
   char* Pa = (char*)ws;
   char* Pb = Pa + p.a_bytes;
   char* part = Pb + p.b_bytes;
@@ -355,10 +390,15 @@ void launch_split_gemm(const SplitPlan& p, bool ta, bool tb, int64_t m, int64_t 
     bool a_packed = false;
     for (int64_t n0 = 0; n0 < n; n0 += p.nc) {
       const int64_t nc = std::min(p.nc, n - n0);
-      pack(!tb, nc, kl, (const char*)B + (tb ? n0 * ldb + k0 : k0 * ldb + n0) * 8, ldb, conjb, Pb, st);
+      if (p.bmap)
+        pack(false, nc, kl, B, 0, conjb, Pb, st, &p.mb, n0, k0);
+      else
+        pack(!tb, nc, kl, (const char*)B + (tb ? n0 * ldb + k0 : k0 * ldb + n0) * 8, ldb, conjb, Pb, st);
       for (int64_t m0 = 0; m0 < m; m0 += p.mc) {
         const int64_t mc = std::min(p.mc, m - m0);
-        if (!a_packed || p.mc < m)
+        if ((!a_packed || p.mc < m) && p.amap)
+          pack(false, mc, kl, A, 0, false, Pa, st, &p.ma, m0, k0);
+        else if (!a_packed || p.mc < m)
           pack(ta, mc, kl, (const char*)A + (ta ? k0 * lda + m0 : m0 * lda + k0) * 8, lda, false, Pa, st);
         a_packed = true;
         const int64_t nb = cdiv(mc, bm) * cdiv(nc, 128);

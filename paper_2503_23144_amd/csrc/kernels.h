@@ -183,6 +183,10 @@ struct SplitPlan {
   int splits = 1;
   int64_t mc = 0, nc = 0, kl = 0;
   size_t a_bytes = 0, b_bytes = 0, bytes = 0;
+  // An operand in another index order than [row][k] or [k][row] is packed
+  // through its map ((row, k) -> offset), without a permuted copy.
+  bool amap = false, bmap = false;
+  OutMap ma, mb;
 };
 constexpr size_t kPackBudget = size_t(1280) << 20;  // most memory a plan asks for, unless told otherwise
 SplitPlan split_plan(int64_t m, int64_t n, int64_t k, size_t budget = kPackBudget);
@@ -195,6 +199,7 @@ void launch_splitk_reduce_f32(int64_t m, int64_t n, int splits, const void* P, d
 
 // Per-shape tile autotuning of launch_gemm (process-wide).
 void set_gemm_autotune(bool on);
+bool gemm_tile_forced();
 void set_gemm_tile(int tile);  // -1: automatic (autotuner or size heuristic)
 int gemm_tuned_shapes();
 // Tile the autotuner chose for a shape (kind 1: the ladder kernel), or -1.

@@ -268,9 +268,13 @@ class Executor {
   int64_t capacity(int id);  // complex elements addressable through ptr(id) (allocates if needed)
   int64_t dim(char letter) const;
   std::string letters(int id, const std::string& idx) const;
-  void gemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double are, double aim, const void* A,
+  // With am or bm that operand lies in the map's order (ta, lda or tb, ldb
+  // unused): false, launching nothing, where the product is not one that packs
+  // its operands.
+  bool gemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double are, double aim, const void* A,
             int64_t lda, int64_t capA, const void* B, int64_t ldb, int64_t capB, double bre, void* C, int64_t ldc,
-            int64_t capC, bool ladder, const OutMap* om = nullptr, bool conjb = false);
+            int64_t capC, bool ladder, const OutMap* om = nullptr, bool conjb = false, const OutMap* am = nullptr,
+            const OutMap* bm = nullptr);
   bool output_map(const std::string& Mc, const std::string& Nc, const std::string& cl, OutMap& om) const;
   static constexpr int64_t kMapElems = 1 << 23;
   static constexpr double kMapMacs = sizeof(T) == 8 ? 0x1p28 : 0x1p24;
@@ -278,6 +282,9 @@ class Executor {
   bool mapped_product(const Op& op, const std::string& a, const std::string& b, const std::string& c,
                       const std::string& Mc, const std::string& Nc, const std::string& Kx, const void* pa, int64_t ca,
                       const void* pb, int64_t cb, void* pc, int64_t cc, bool copies);
+  bool packed_product(const Op& op, const std::string& a, const std::string& b, const std::string& c,
+                      const std::string& Mc, const std::string& Nc, const std::string& Kx, const void* pa, int64_t ca,
+                      const void* pb, int64_t cb, void* pc, int64_t cc, bool a_ok, bool b_ok);
   int cached_permute(int id, const std::string& src, const std::string& dst, const void* p, int64_t cap);
   void* pack_scratch(int64_t M, int64_t N, int64_t K, SplitPlan& s);
   static constexpr int kPermSlot = 5, kPackSlot = 9;

@@ -130,3 +130,30 @@ def test_small_workflow_repeats_with_graphs(o, v):
     ref, got = workflow(False), workflow(True)
     for x in got:
         assert np.abs(x - ref[0]).max() <= 1e-12 * np.abs(ref[0]).max()
+
+
+@pytest.mark.parametrize("o,v,nb", [(9, 53, 20), (17, 37, 18)])
+def test_permuted_operands_packed_in_place(o, v, nb):
+    """Ring products (K = o v) and the o^2 products (K = o^2 >= 256) of batches
+    large enough to pack their operands, read through index maps with odd
+    extents.  FP32 against FP64 of the same context: 2^-24 per rounding, sums
+    of at most v^2 terms in chains, against the largest element."""
+    from paper_2503_23144_amd import lrcc
+    from paper_2503_23144_amd.synth import make_inputs
+    print(f"packed in place o={o} v={v} nb={nb}", flush=True)
+    inp = make_inputs(o, v, o + v, seed=o * v)
+    c = lrcc.Context(precision="mixed", tol=1e-9)
+    c.load_df(inp.o, inp.v, inp.B)
+    c.load_fock(inp.fock)
+    c.load_dipoles(inp.mu)
+    rng = np.random.default_rng(o + v)
+    t = 0.05 * (rng.standard_normal(c.n) + 1j * rng.standard_normal(c.n))
+    X = rng.standard_normal((nb, c.n)) + 1j * rng.standard_normal((nb, c.n))
+    c.sigma("residual", t)
+    c.set_amplitudes(lrcc.AMP_T, t)
+    for side in ("right", "left"):
+        ref = c.sigma(side, X, precision="fp64")
+        got = c.sigma(side, X, precision="mixed")
+        for r in range(nb):
+            assert np.abs(got[r] - ref[r]).max() <= 1e-5 * np.abs(ref[r]).max(), (side, r)
+    c.close()
