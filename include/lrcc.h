@@ -266,8 +266,12 @@ int lrcc_gemm(int precision, int transa, int transb, int64_t m, int64_t n, int64
    hipMalloc): it calls no hipMalloc, hipFree or other allocating routine.
    Same arguments, layout and results as lrcc_gemm (the same split over K and
    tile choice; a shape never seen before takes the size heuristic instead of
-   being timed).  The split-K partials of deep products live in a static
-   device array of 256 MiB per GPU, held from the first call on that GPU until
+   being timed), except that large FP32 products run on the BF16 matrix cores
+   as the library's own contractions do, each FP32 number as the exact sum of
+   three BF16 ones (lrcc_gemm, which holds no memory for the packed operands,
+   runs them on FP32 MFMA; both within FP32's rounding).  The split-K partials
+   of deep products and the packed operands live in a static device array of
+   256 MiB per GPU, held from the first call on that GPU until
    the process ends; a product whose partials would not fit returns
    LRCC_E_INVALID (the library caps its splits at that size, so none does
    today).  Fully asynchronous on `stream`.  Every call on one GPU uses the
@@ -278,18 +282,22 @@ int lrcc_gemm_noalloc(int precision, int transa, int transb, int64_t m, int64_t 
                       const double beta[2], void *C, int64_t ldc, void *stream);
 
 /* Workgroup tile of every later unsplit GEMM launch, process-wide:
-   -1 = automatic (the autotuner when a context enables it, else a size
-   heuristic; products at most 32 wide take tile 4); 0 = 64 x 64, 1 = 128 x
+   -1 = automatic: products with few tiles, narrow or shallow ones run on
+   wavefronts of their own, large FP32 products of a context on the BF16 matrix
+   cores, the others on a tile (the autotuner's when a context enables it,
+   else a size heuristic; products at most 32 wide take tile 4); 0 = 64 x 64, 1 = 128 x
    64, 2 = 128 x 128 with 4 wavefronts (FP32 only; FP64 runs tile 1), 3 =
    128 x 128 with 8 wavefronts, 4 = 128 x 32.  Every tile computes the same
    product (results agree to rounding); the choice only changes speed.
-   Products split over K ignore it.  Returns LRCC_E_INVALID outside -1..4.
+   Products split over K ignore it, and so do the small products of a context
+   that are launched in groups.  Returns LRCC_E_INVALID outside -1..4.
    The environment variable LRCC_GEMM_TILE gives the initial value. */
 int lrcc_gemm_set_tile(int tile);
 /* Tile (0..4 as above) the autotuner chose in this process for the product
    shape (precision LRCC_FP64 or LRCC_MIXED, op(A) m x k, op(B) k x n; ladder
    = 1 for the packed-vvvv ladder contraction of the Jacobian products, which
-   runs its own kernel variant), or -1 if that shape has not been timed.  For
+   runs its own kernel variant), or -1 if that shape has not been timed (as
+   products on the wavefront and BF16 kernels are not).  For
    profiles: it names the kernel a trace's or a counter's figures belong to.
    Shapes are timed per bucket (m, n, k above 64 rounded down to their top
    three bits, about 25 % wide), so the answer covers every shape of the
@@ -313,7 +321,8 @@ int lrcc_kernel_time(lrcc_ctx *ctx, int cls, double *ms, int64_t *launches, doub
 /* Enable (1) or disable (0) the per-launch event timing above.  With graph
    replay on (lrcc_config.graphs), GEMMs inside a replayed graph are not
    timed; the ladder GEMMs are then launched between graph segments so that
-   classes 0 and 1 stay complete. */
+   classes 0 and 1 stay complete.  While timing is on, small ops are launched
+   one by one. */
 int lrcc_set_timing(lrcc_ctx *ctx, int on);
 /* HIP graphs captured and replayed so far: program runs of the FP64 and
    FP32 executors (lrcc_sigma and the like) and whole solver iterations

@@ -246,7 +246,7 @@ static void wgo(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, d
 // once per workgroup into LDS.  What bounds such a product is the latency of
 // one pass (3-10 us by its depth, one or a few workgroups of 256 CUs busy), so
 // up to kMapTerms products independent of each other share a launch.  Right
-// product at o = 4, v = 16, FP64: 57 launches in 218 us alone, 33 in 162 in
+// product at o = 4, v = 16, FP64: 57 launches in 218 us alone, 33 in 161 in
 // groups; a term of depth 1024 takes 17 us, the matrix cores of one CU.
 template <typename T>
 struct MapTerm {
