@@ -247,7 +247,7 @@ static void wgo(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, d
 // one pass (3-10 us by its depth, one or a few workgroups of 256 CUs busy), so
 // up to kMapTerms products independent of each other share a launch.  Right
 // product at o = 4, v = 16, FP64: 57 launches in 218 us alone, 33 in 161 in
-// groups; a term of depth 1024 takes 17 us, the matrix cores of one CU.
+// groups.
 template <typename T>
 struct MapTerm {
   using V2 = typename cpx<T>::type;
@@ -273,7 +273,7 @@ struct MapTerm {
   const V2 *A, *B;
   V2* C;
   T are, aim, beta;
-  int M, N, K, nbm;
+  int M, N, K, nbm, k0;  // K depths from k0 on
   Side am, ak, bn, bk, cm, cn;
 };
 constexpr int kMapTerms = 8;
@@ -302,8 +302,8 @@ __global__ void __launch_bounds__(64 * NW) mgemm_kernel(MapGroup<T> g) {
   const int r16 = lane & 15, kq = lane >> 4;
   const int m0 = (bid % p.nbm) * 16, n0 = (bid / p.nbm) * 16;
   for (int k = tid; k < K; k += 64 * NW) {
-    ka[k] = (uint32_t)p.ak.off(k);
-    kb[k] = (uint32_t)p.bk.off(k);
+    ka[k] = (uint32_t)p.ak.off(p.k0 + k);
+    kb[k] = (uint32_t)p.bk.off(p.k0 + k);
   }
   // rows beyond M and columns beyond N feed outputs that are never stored
   const V2* pa = p.A + p.am.off(m0 + r16 < M ? m0 + r16 : M - 1);
@@ -381,8 +381,56 @@ __global__ void __launch_bounds__(64 * NW) mgemm_kernel(MapGroup<T> g) {
   }
 }
 
+// C = alpha sum_s P[s] + beta C for terms whose K was cut into p.K pieces;
+// their partials, M x N each, follow one another at p.A.
 template <typename T>
-void launch_mapped_gemm(const MappedProduct* p, int n, hipStream_t st) {
+__global__ void __launch_bounds__(256) mreduce_kernel(MapGroup<T> g) {
+  using V2 = typename cpx<T>::type;
+  int ti = 0;
+#pragma unroll
+  for (int i = 1; i < kMapTerms; ++i)
+    if (i < g.n && (int)blockIdx.x >= g.first[i]) ti = i;
+  const MapTerm<T>& p = g.t[ti];
+  const int mn = p.M * p.N, e = ((int)blockIdx.x - g.first[ti]) * 256 + (int)threadIdx.x;
+  if (e >= mn) return;
+  V2 s{0, 0};
+#pragma unroll 4
+  for (int q = 0; q < p.K; ++q) {
+    const V2 x = p.A[(int64_t)q * mn + e];
+    s.x += x.x;
+    s.y += x.y;
+  }
+  T cr = p.are * s.x - p.aim * s.y, ci = p.are * s.y + p.aim * s.x;
+  V2* c = p.C + p.cm.off(e / p.N) + p.cn.off(e % p.N);
+  if (p.beta != T(0)) {
+    const V2 y = *c;
+    cr += p.beta * y.x;
+    ci += p.beta * y.y;
+  }
+  *c = V2{cr, ci};
+}
+
+// A deep product of few tiles is cut along K into pieces of kMapPiece, summed
+// by a second launch: a workgroup works off 1024 depths in 17 us (its CU's
+// matrix cores, a 16 x 16 tile for 4 x 4 outputs), 256 in 7, and the sum takes
+// 2.4.  Right product at o = 4, v = 16, FP64, two levels of that depth: 151 ->
+// 138 us.  Beyond 32 tiles the products fill the launch by themselves.
+constexpr int64_t kMapPiece = 256;
+static int64_t map_pieces(const MappedProduct& p) {
+  const int64_t tiles = ((p.m + 15) / 16) * ((p.n + 15) / 16);
+  return p.k > 2 * kMapPiece && tiles <= 32 ? (p.k + kMapPiece - 1) / kMapPiece : 1;
+}
+
+template <typename T>
+size_t mapped_gemm_workspace(const MappedProduct* p, int n) {
+  int64_t e = 0;
+  for (int i = 0; i < n; ++i)
+    if (map_pieces(p[i]) > 1) e += map_pieces(p[i]) * p[i].m * p[i].n;
+  return (size_t)e * 2 * sizeof(T);
+}
+
+template <typename T>
+void launch_mapped_gemm(const MappedProduct* p, int n, void* ws, hipStream_t st) {
   using V2 = typename cpx<T>::type;
   auto side = [](int nd, const int64_t* dim, const int64_t* str) {
     const DevMap::Side d = DevMap::side(nd, dim, str);
@@ -394,45 +442,80 @@ void launch_mapped_gemm(const MappedProduct* p, int n, hipStream_t st) {
     }
     return s;
   };
-  for (int i0 = 0; i0 < n; i0 += kMapTerms) {
-    MapGroup<T> g{};
-    g.n = std::min(kMapTerms, n - i0);
-    int64_t nb = 0, depth = 0;
-    for (int i = 0; i < g.n; ++i) {
-      const MappedProduct& q = p[i0 + i];
-      LRCC_REQUIRE(q.m > 0 && q.n > 0 && q.k > 0 && q.k <= kMapDepth && DevMap::fits(q.ma) && DevMap::fits(q.mb) &&
-                       DevMap::fits(q.om) && q.ma.row(q.m - 1) + q.ma.col(q.k - 1) < INT32_MAX &&
-                       q.mb.row(q.n - 1) + q.mb.col(q.k - 1) < INT32_MAX &&
-                       q.om.row(q.m - 1) + q.om.col(q.n - 1) < INT32_MAX,
-                   LRCC_E_INTERNAL, "mapped product too large");
-      const int64_t nbm = (q.m + 15) / 16;
-      g.first[i] = (int)nb;
-      nb += nbm * ((q.n + 15) / 16);
-      LRCC_REQUIRE(nb < INT32_MAX / 1024, LRCC_E_INTERNAL, "mapped product too large");
-      depth = std::max(depth, q.k);
-      g.t[i] = MapTerm<T>{(const V2*)q.A,
-                          (const V2*)q.B,
-                          (V2*)q.C,
-                          (T)q.are,
-                          (T)q.aim,
-                          (T)q.beta,
-                          (int)q.m,
-                          (int)q.n,
-                          (int)q.k,
-                          (int)nbm,
-                          side(q.ma.nm, q.ma.mdim, q.ma.mstr),
-                          side(q.ma.nn, q.ma.ndim, q.ma.nstr),
-                          side(q.mb.nm, q.mb.mdim, q.mb.mstr),
-                          side(q.mb.nn, q.mb.ndim, q.mb.nstr),
-                          side(q.om.nm, q.om.mdim, q.om.mstr),
-                          side(q.om.nn, q.om.ndim, q.om.nstr)};
-    }
+  MapGroup<T> g{}, red{};
+  int64_t nb = 0, depth = 0, rb = 0;
+  auto launch = [&] {
+    if (g.n == 0) return;
     if (depth > 64 && nb < 512)
       hipLaunchKernelGGL((mgemm_kernel<T, 8>), dim3((unsigned)nb), dim3(64 * 8), 0, st, g);
     else
       hipLaunchKernelGGL((mgemm_kernel<T, 4>), dim3((unsigned)nb), dim3(64 * 4), 0, st, g);
     HIP_CHECK(hipGetLastError());
+    g.n = 0, nb = 0, depth = 0;
+  };
+  auto reduce = [&] {  // after the products whose partials it sums
+    if (red.n == 0) return;
+    launch();
+    hipLaunchKernelGGL(mreduce_kernel<T>, dim3((unsigned)rb), dim3(256), 0, st, red);
+    HIP_CHECK(hipGetLastError());
+    red.n = 0, rb = 0;
+  };
+  V2* part = (V2*)ws;
+  for (int i = 0; i < n; ++i) {
+    const MappedProduct& q = p[i];
+    LRCC_REQUIRE(q.m > 0 && q.n > 0 && q.k > 0 && q.k <= kMapDepth && DevMap::fits(q.ma) && DevMap::fits(q.mb) &&
+                     DevMap::fits(q.om) && q.ma.row(q.m - 1) + q.ma.col(q.k - 1) < INT32_MAX &&
+                     q.mb.row(q.n - 1) + q.mb.col(q.k - 1) < INT32_MAX &&
+                     q.om.row(q.m - 1) + q.om.col(q.n - 1) < INT32_MAX,
+                 LRCC_E_INTERNAL, "mapped product too large");
+    const int64_t nbm = (q.m + 15) / 16, tiles = nbm * ((q.n + 15) / 16);
+    LRCC_REQUIRE(tiles < INT32_MAX / 2048, LRCC_E_INTERNAL, "mapped product too large");
+    MapTerm<T> t{(const V2*)q.A,
+                 (const V2*)q.B,
+                 (V2*)q.C,
+                 (T)q.are,
+                 (T)q.aim,
+                 (T)q.beta,
+                 (int)q.m,
+                 (int)q.n,
+                 (int)q.k,
+                 (int)nbm,
+                 0,
+                 side(q.ma.nm, q.ma.mdim, q.ma.mstr),
+                 side(q.ma.nn, q.ma.ndim, q.ma.nstr),
+                 side(q.mb.nm, q.mb.mdim, q.mb.mstr),
+                 side(q.mb.nn, q.mb.ndim, q.mb.nstr),
+                 side(q.om.nm, q.om.mdim, q.om.mstr),
+                 side(q.om.nn, q.om.ndim, q.om.nstr)};
+    const int64_t pieces = ws ? map_pieces(q) : 1;
+    if (pieces > 1) {
+      if (red.n == kMapTerms) reduce();
+      MapTerm<T>& r = red.t[red.n];
+      red.first[red.n++] = (int)rb;
+      rb += (q.m * q.n + 255) / 256;
+      r = t;
+      r.A = part;
+      r.K = (int)pieces;
+      t.are = 1, t.aim = 0, t.beta = 0;
+      const OutMap plain = OutMap::plain(q.n);
+      t.cm = side(plain.nm, plain.mdim, plain.mstr), t.cn = side(plain.nn, plain.ndim, plain.nstr);
+    }
+    for (int64_t s = 0; s < pieces; ++s) {
+      if (pieces > 1) {
+        t.k0 = (int)(s * kMapPiece);
+        t.K = (int)std::min(kMapPiece, q.k - s * kMapPiece);
+        t.C = part;
+        part += q.m * q.n;
+      }
+      if (g.n == kMapTerms) launch();
+      g.t[g.n] = t;
+      g.first[g.n++] = (int)nb;
+      nb += tiles;
+      depth = std::max<int64_t>(depth, t.K);
+    }
   }
+  launch();
+  reduce();
 }
 
 // Variants: 0 and 1 share one 16 x 16 tile among 8 and 4 wavefronts, 2
@@ -529,7 +612,8 @@ WavePlan wave_plan(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bo
                                     const void*, int64_t, const void*, int64_t, double, double, void*,              \
                                     const OutMap&, int64_t, hipStream_t, bool);                                     \
   template WavePlan wave_plan<T>(int64_t, int64_t, int64_t, int64_t, int64_t, bool);                                \
-  template void launch_mapped_gemm<T>(const MappedProduct*, int, hipStream_t);
+  template size_t mapped_gemm_workspace<T>(const MappedProduct*, int);                                              \
+  template void launch_mapped_gemm<T>(const MappedProduct*, int, void*, hipStream_t);
 INST_(double)
 INST_(float)
 #undef INST_

@@ -171,9 +171,12 @@ struct MappedProduct {
   void* C;
   OutMap ma, mb, om;
 };
-// n products, none of which reads or writes what another one writes.
+// n products, none of which reads or writes what another one writes.  ws: the
+// partials of deep ones (mapped_gemm_workspace bytes), or null: none is cut.
 template <typename T>
-void launch_mapped_gemm(const MappedProduct* p, int n, hipStream_t st);
+size_t mapped_gemm_workspace(const MappedProduct* p, int n);
+template <typename T>
+void launch_mapped_gemm(const MappedProduct* p, int n, void* ws, hipStream_t st);
 
 // Large FP32 products on the BF16 matrix cores (gemm_split.hip): both
 // operands are packed into `bytes` of device memory, mc x nc of the output and

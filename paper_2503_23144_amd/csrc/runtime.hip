@@ -491,7 +491,9 @@ void Executor<T>::flush() {
         else
           group.push_back(d.product);
       }
-    if (!group.empty()) launch_mapped_gemm<T>(group.data(), (int)group.size(), st_);
+    if (group.empty()) continue;
+    const size_t wsb = mapped_gemm_workspace<T>(group.data(), (int)group.size());
+    launch_mapped_gemm<T>(group.data(), (int)group.size(), wsb ? scratch(4, wsb) : nullptr, st_);
   }
 }
 
@@ -537,7 +539,8 @@ bool Executor<T>::mapped_product(const Op& op, const std::string& a, const std::
     e0 = get_event();
     HIP_CHECK(hipEventRecord(e0, st_));
   }
-  launch_mapped_gemm<T>(&p, 1, st_);
+  const size_t wsb = mapped_gemm_workspace<T>(&p, 1);
+  launch_mapped_gemm<T>(&p, 1, wsb ? scratch(4, wsb) : nullptr, st_);
   if (!capturing_) {
     hipEvent_t e1 = get_event();
     HIP_CHECK(hipEventRecord(e1, st_));

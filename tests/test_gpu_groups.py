@@ -66,3 +66,10 @@ def test_summed_packs_match_oracle_at_tile_edges(o, v):
             ref = fn(P, torch.as_tensor(t), torch.as_tensor(X[r])).resolve_conj().numpy()
             assert np.abs(got[r] - ref).max() <= 1e-12 * np.abs(ref).max(), (side, r)
     c.close()
+
+
+@pytest.mark.parametrize("o,v", [(8, 9), (4, 16), (9, 15)])
+def test_deep_products_cut_along_k_match_oracle(o, v):
+    """Depths o^2 v and o v^2 of 576 to 2025 on a few tiles: pieces of 256, the
+    last one ragged.  The same check and bound."""
+    test_summed_packs_match_oracle_at_tile_edges(o, v)
