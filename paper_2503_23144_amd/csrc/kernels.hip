@@ -297,7 +297,7 @@ __global__ void __launch_bounds__(256) unpack_kernel(const typename cplx2<T>::ty
 // (blockIdx.y): the left program's first four at o = 10, v = 60, three
 // vectors, FP64, 55 us -> 22 us.
 constexpr int UT = 32;                     // tile edge
-constexpr int64_t kTailBlocks = 1 << 24;   // workgroups of a launch
+constexpr int64_t kTailBlocks = 1 << 23;   // workgroups of a launch: below 2^32 threads
 
 struct UnpackArgs {
   struct Term {

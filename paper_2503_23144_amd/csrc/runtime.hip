@@ -1712,12 +1712,12 @@ void Executor<T>::run(const OpList& ops, int nb, const std::vector<int>& keep) {
 
 template <typename T>
 bool Executor<T>::RunKey::operator<(const RunKey& o) const {
-  return std::tie(ops, nb, timing, keep, addr) < std::tie(o.ops, o.nb, o.timing, o.keep, o.addr);
+  return std::tie(ops, nb, timing, pinned, keep, addr) < std::tie(o.ops, o.nb, o.timing, o.pinned, o.keep, o.addr);
 }
 
 template <typename T>
 typename Executor<T>::RunKey Executor<T>::make_key(const OpList& ops, int nb, const std::vector<int>& keep) const {
-  RunKey k{&ops, nb, timing_, keep, {}};
+  RunKey k{&ops, nb, timing_, gemm_tile_forced(), keep, {}};
   k.addr.reserve(buf_.size() + scr_.size() + pool_.size());
   k.addr.insert(k.addr.end(), buf_.begin(), buf_.end());
   k.addr.insert(k.addr.end(), scr_.begin(), scr_.end());

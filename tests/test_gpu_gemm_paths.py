@@ -157,3 +157,33 @@ def test_permuted_operands_packed_in_place(o, v, nb):
         for r in range(nb):
             assert np.abs(got[r] - ref[r]).max() <= 1e-5 * np.abs(ref[r]).max(), (side, r)
     c.close()
+
+
+@pytest.mark.parametrize("o,v,nb,precision,tol", [(9, 53, 20, "mixed", 1e-5), (6, 40, 1, "fp64", 1e-12)])
+def test_tile_pinned_between_runs(o, v, nb, precision, tol):
+    """Pinning a tile after a program's eager run sends its products to other
+    kernels, with other scratch: that run is eager again, not a capture.  Both
+    sum the same terms in another order (2^-24 or 2^-53 per rounding)."""
+    from paper_2503_23144_amd import lrcc
+    from paper_2503_23144_amd.synth import make_inputs
+    print(f"pinned tile o={o} v={v} nb={nb} {precision}", flush=True)
+    inp = make_inputs(o, v, o + v, seed=o * v)
+    c = lrcc.Context(precision=precision, tol=1e-9)
+    c.load_df(inp.o, inp.v, inp.B)
+    c.load_fock(inp.fock)
+    c.load_dipoles(inp.mu)
+    rng = np.random.default_rng(o + v)
+    t = 0.05 * (rng.standard_normal(c.n) + 1j * rng.standard_normal(c.n))
+    X = rng.standard_normal((nb, c.n)) + 1j * rng.standard_normal((nb, c.n))
+    c.sigma("residual", t)
+    c.set_amplitudes(lrcc.AMP_T, t)
+    try:
+        for side in ("left", "right"):
+            ref = c.sigma(side, X, precision=precision)
+            for tile in (0, 0, 0, -1, -1, -1, 3, -1):
+                lrcc.gemm_set_tile(tile)
+                got = c.sigma(side, X, precision=precision)
+                assert np.abs(got - ref).max() <= tol * np.abs(ref).max(), (side, tile)
+    finally:
+        lrcc.gemm_set_tile(-1)
+    c.close()
