@@ -268,8 +268,11 @@ int lrcc_gemm(int precision, int transa, int transb, int64_t m, int64_t n, int64
    tile choice; a shape never seen before takes the size heuristic instead of
    being timed), except that large FP32 products run on the BF16 matrix cores
    as the library's own contractions do, each FP32 number as the exact sum of
-   three BF16 ones (lrcc_gemm, which holds no memory for the packed operands,
-   runs them on FP32 MFMA; both within FP32's rounding).  The split-K partials
+   three BF16 ones, of whose nine products the six above 2^-24 of the whole are
+   formed (lrcc_gemm, which holds no memory for the packed operands, runs them
+   on FP32 MFMA; the errors against 64 bits are alike).  A product with an
+   operand element of magnitude 2^32 or more, infinite or NaN runs on FP32 MFMA
+   there, too: the operands are looked through on the device.  The split-K partials
    of deep products and the packed operands live in a static device array of
    256 MiB per GPU, held from the first call on that GPU until
    the process ends; a product whose partials would not fit returns

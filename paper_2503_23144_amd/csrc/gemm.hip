@@ -99,14 +99,20 @@ struct Tile {
 //
 // Split-K: blockIdx.y selects the depth range [y * kchunk, (y + 1) * kchunk)
 // and the output C + y * cstride (partial products, reduced afterwards).
+//
+// The product may be the block of a larger one that starts at row om0 and
+// column on0 of the output map.  With a gate (two words) it runs only where
+// one of them is set (launch_gemm_if).
 template <typename T, bool TA, bool TB, int KIND, int BM, int BN, int WGM, int BK, int NW>
 __global__ void __launch_bounds__(64 * NW) zgemm_kernel(int64_t M, int64_t N, int64_t K, T are, T aim,
                                                   const typename cpx<T>::type* __restrict__ A, int64_t lda,
                                                   const typename cpx<T>::type* __restrict__ B, int64_t ldb, T bre,
                                                   T bim, typename cpx<T>::type* __restrict__ C, DevMap om,
-                                                  int64_t kchunk, int64_t cstride, T bsgn) {
+                                                  int64_t kchunk, int64_t cstride, T bsgn, int64_t om0,
+                                                  int64_t on0, const int* __restrict__ gate) {
   using V2 = typename cpx<T>::type;
   constexpr int NT = 64 * NW;
+  if (gate && !(gate[0] | gate[1])) return;
   {
     const int64_t kbeg = (int64_t)blockIdx.y * kchunk;
     K = (K < kbeg + kchunk ? K : kbeg + kchunk) - kbeg;
@@ -289,7 +295,7 @@ __global__ void __launch_bounds__(64 * NW) zgemm_kernel(int64_t M, int64_t N, in
 #pragma unroll
   for (int j = 0; j < TJ; ++j) {
     const int64_t gn = n0 + wn + j * 16 + r16;
-    coff[j] = gn < N ? om.col(gn) : -1;
+    coff[j] = gn < N ? om.col(on0 + gn) : -1;
   }
 #pragma unroll
   for (int i = 0; i < TI; ++i)
@@ -297,7 +303,7 @@ __global__ void __launch_bounds__(64 * NW) zgemm_kernel(int64_t M, int64_t N, in
     for (int r = 0; r < 4; ++r) {
       const int64_t gm = m0 + wm + i * 16 + cpx<T>::row(kq, r);
       if (gm >= M) continue;
-      const int64_t roff = om.row(gm);
+      const int64_t roff = om.row(om0 + gm);
 #pragma unroll
       for (int j = 0; j < TJ; ++j) {
         if (coff[j] < 0) continue;
@@ -416,7 +422,7 @@ static void go(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, do
   hipLaunchKernelGGL((zgemm_kernel<T, TA_, TB_, KIND, BM, BN, WGM, BK, NW>), dim3((unsigned)nb, (unsigned)splits), dim3(NT), \
                      0, st, m, n, k, (T)ar, (T)ai, (const V2*)A, lda, (const V2*)B, ldb, (T)br, (T)bi, (V2*)out, \
                      DevMap(mo), \
-                     kchunk, cstride, (T)(conjb ? -1.0 : 1.0))
+                     kchunk, cstride, (T)(conjb ? -1.0 : 1.0), int64_t(0), int64_t(0), (const int*)nullptr)
   if (!ta && !tb)
     GO_(false, false);
   else if (!ta && tb)
@@ -428,6 +434,32 @@ static void go(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, do
 #undef GO_
   HIP_CHECK(hipGetLastError());
   if (splits > 1) launch_splitk_reduce<T>(m, n, splits, ws, are, aim, bre, bim, C, om, st);
+}
+
+// One block of a large FP32 product, run where gate[0] or gate[1] is set:
+// rows om0.., columns on0.. of the output map; splits > 1 leaves partials
+// of kchunk depths at C + split * m * n.  The 64 x 64 tile, the fastest on most
+// large FP32 shapes.
+void launch_gemm_if(const int* gate, bool ta, bool tb, int64_t m, int64_t n, int64_t k, float are, float aim,
+                    const void* A, int64_t lda, const void* B, int64_t ldb, float bre, float bim, void* C,
+                    const OutMap& om, int64_t om0, int64_t on0, int splits, int64_t kchunk, bool conjb,
+                    hipStream_t st) {
+  const int64_t nb = ((m + 63) / 64) * ((n + 63) / 64);
+  LRCC_REQUIRE(nb < (int64_t(1) << 24), LRCC_E_INVALID, "gemm grid too large");
+#define IF_(TA_, TB_)                                                                                               \
+  hipLaunchKernelGGL((zgemm_kernel<float, TA_, TB_, 0, 64, 64, 2, 16, 4>), dim3((unsigned)nb, (unsigned)splits),     \
+                     dim3(256), 0, st, m, n, k, are, aim, (const float2*)A, lda, (const float2*)B, ldb, bre, bim,    \
+                     (float2*)C, DevMap(om), kchunk, m* n, conjb ? -1.0f : 1.0f, om0, on0, gate)
+  if (!ta && !tb)
+    IF_(false, false);
+  else if (!ta && tb)
+    IF_(false, true);
+  else if (ta && !tb)
+    IF_(true, false);
+  else
+    IF_(true, true);
+#undef IF_
+  HIP_CHECK(hipGetLastError());
 }
 
 // ---------------------------------------------------------------- tile choice

@@ -3,11 +3,13 @@
 // The FP32 MFMA rate bounds the tiled kernel (119 TFLOP/s of 157 in the 3M
 // count); BF16 runs at 16 times that rate.  An FP32 number is exactly the
 // sum of three BF16 numbers, x = h + m + l (8 significant bits each,
-// round to nearest), so a real FP32 product is six BF16 products,
-//   x y = h h + h m + m h + m m + h l + l h   (+ terms below 2^-25 |x y|),
+// round to nearest; G. Henry, P. T. P. Tang and A. Heinecke, ARITH 2019), so a
+// real FP32 product is six BF16 products,
+//   x y = h h + h m + m h + m m + h l + l h,
 // each exact in FP32 and added up in FP32 by the MFMA: 18 BF16 products for
 // one complex 3M product, 2.7 times fewer matrix-core cycles than the FP32
-// instruction needs.
+// instruction needs.  m l + l m + l l, left out, is below 2^-24 |x y| (|m| <=
+// 2^-8, |l| <= 2^-17 of x's binade; 2^-27.5 in the mean).
 //
 // split_pack_kernel writes both operands as the LDS image the product reads:
 // blocks of 128 rows x 16 depths, for each of re, im and re + im (the 3M
@@ -35,11 +37,18 @@
 // kChain bounds the depth of one accumulation chain, so that it stays below
 // that of the tiled kernel where that one splits K, too.
 //
-// Range: an input above BF16's largest finite value is truncated, not
-// rounded, into h, so finite inputs stay finite.  An infinite or NaN input
-// makes its row or column NaN (in the 3M scheme at least the imaginary part
-// is NaN already).  Inputs below 2^-109 lose low bits of l to BF16's
-// smallest subnormal, 2^-133.
+// Range: BF16 has FP32's exponents but not its significand's reach below
+// them, so the operands are packed 2^24 times larger.  FP32 numbers, the
+// subnormal ones among them, are multiples of 2^-149; scaled, h, m and l are
+// multiples of 2^-125, normal BF16 numbers or zero, and the split is exact.
+// Below 2^32 in magnitude the scaled values (2^56), their 3M sums (2^57) and
+// the sum of kChain products (2^126) stay finite.  An element of 2^32 or
+// more, an infinity or a NaN in either operand sets a flag, and that product
+// runs on the FP32 MFMA instead: the flag is read on the device, by the
+// product kernel, which then returns at once, and by a tiled launch behind it
+// (launch_gemm_if), which otherwise does.  The packing's check is hidden
+// behind its memory traffic; the launches that do nothing cost 0.4 % of a right
+// product (o = 20, v = 150, 24 vectors: 91.4 -> 91.8 ms).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -58,22 +67,16 @@ constexpr int kRB = 128;                       // rows of a packed block
 constexpr int kSlab = 16;                      // depths of a packed slab
 constexpr int kChunk = kRB * kSlab * 3 * 2;    // bytes of one block x slab x component (three BF16 terms)
 
+constexpr float kScale = 0x1p24f, kUnscale = 0x1p-48f;  // of an operand, of a product
+constexpr float kLargest = 0x1p32f;                     // magnitudes from here on take the FP32 MFMA
+constexpr size_t kFlagBytes = 256;
+
 __device__ inline uint16_t bits(__bf16 x) { return __builtin_bit_cast(uint16_t, x); }
 
-// x = h + m + l exactly
+// x = h + m + l exactly, for x a multiple of 2^-125 below 2^58
 __device__ inline void split3(float x, uint16_t& h, uint16_t& m, uint16_t& l) {
-  __bf16 bh = (__bf16)x;
-  float fh = (float)bh;
-  if (!(__builtin_fabsf(fh) < __builtin_inff())) {
-    if (__builtin_fabsf(x) < __builtin_inff()) {
-      fh = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & 0xffff0000u);
-      bh = (__bf16)fh;
-    } else {
-      h = bits(bh), m = 0, l = 0;
-      return;
-    }
-  }
-  const float r = x - fh;
+  const __bf16 bh = (__bf16)x;
+  const float r = x - (float)bh;
   const __bf16 bm = (__bf16)r;
   h = bits(bh);
   m = bits(bm);
@@ -85,13 +88,14 @@ __device__ inline void split3(float x, uint16_t& h, uint16_t& m, uint16_t& l) {
 // contiguous dimension (rows with KMAJ, else depths) and turned in LDS, so that
 // every thread splits eight consecutive depths of one row and writes 16 bytes
 // per component and term.  With MAP the element (r, k) lies at X + map.row(r0
-// + r) + map.col(k0 + k).  Bound by memory: 8 bytes read and 18 written per
-// element.
+// + r) + map.col(k0 + k).  *flag is set where an element is out of range.  Bound
+// by memory: 8 bytes read and 18 written per element.
 template <bool KMAJ, bool MAP>
 __global__ void __launch_bounds__(256)
     split_pack_kernel(int64_t rows, int64_t K, const float2* __restrict__ X, int64_t ld, DevMap map, int64_t rbase,
-                      int64_t kbase, float sgn, int64_t nslab, uint4* __restrict__ P) {
+                      int64_t kbase, float sgn, int64_t nslab, uint4* __restrict__ P, int* __restrict__ flag) {
   __shared__ float2 t[kRB][kSlab + 1];
+  bool bad = false;
   constexpr int NQ = kRB * kSlab / 256;
   const int tid = threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.x * kRB;
@@ -124,7 +128,8 @@ __global__ void __launch_bounds__(256)
       else
         at = roff[q] + koff;
       const float2 v = X[MAP || in ? at : 0];
-      t[row][kk] = in ? float2{v.x, v.y * sgn} : float2{0.0f, 0.0f};
+      bad |= in && !(__builtin_fabsf(v.x) < kLargest && __builtin_fabsf(v.y) < kLargest);
+      t[row][kk] = in ? float2{v.x * kScale, v.y * (sgn * kScale)} : float2{0.0f, 0.0f};
     }
     __syncthreads();
     const int row = tid & (kRB - 1), kg = tid >> 7;
@@ -151,13 +156,26 @@ __global__ void __launch_bounds__(256)
     }
     __syncthreads();
   }
+  if (bad) *flag = 1;
+}
+
+__global__ void split_clear_kernel(int* flags) { flags[threadIdx.x] = 0; }
+
+// A mapped operand as [row][k], for the FP32 MFMA: where a flag is set.
+__global__ void __launch_bounds__(256) split_copy_kernel(const int* __restrict__ flags, int64_t rows, int64_t K,
+                                                         const float2* __restrict__ X, DevMap map, int64_t rbase,
+                                                         int64_t kbase, float2* __restrict__ out) {
+  if (!(flags[0] | flags[1])) return;
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < rows * K; e += (int64_t)gridDim.x * 256)
+    out[e] = X[map.row(rbase + e / K) + map.col(kbase + e % K)];
 }
 
 template <int WGM, int WGN, int NS>  // NS slabs per stage
 __global__ void __launch_bounds__(64 * WGM * WGN, 2)
     split_gemm_kernel(int64_t M, int64_t N, int64_t nslab, const char* __restrict__ Ap, const char* __restrict__ Bp,
                       float are, float aim, float bre, float bim, float2* __restrict__ C, DevMap om, int64_t om0,
-                      int64_t on0, int64_t schunk, int64_t cstride) {
+                      int64_t on0, int64_t schunk, int64_t cstride, const int* __restrict__ flags) {
+  if (flags[0] | flags[1]) return;
   constexpr int NW = WGM * WGN, BM = 64 * WGM, BN = 64 * WGN;
   constexpr int RA = BM / kRB, RB = BN / kRB;
   constexpr int STAGE = (RA + RB) * NS * kChunk;
@@ -275,7 +293,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN, 2)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         if (coff[j] < 0) continue;
-        const float re = acc[0][i][j][r], im = acc[1][i][j][r];
+        const float re = acc[0][i][j][r] * kUnscale, im = acc[1][i][j][r] * kUnscale;
         float cr = are * re - aim * im, ci = are * im + aim * re;
         float2* c = C + roff + coff[j];
         if (use_beta) {
@@ -294,15 +312,15 @@ int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 int64_t slabs(int64_t k) { return cdiv(k, 2 * kSlab) * 2; }  // padded to whole stages
 size_t pack_bytes(int64_t rows, int64_t k) { return (size_t)(cdiv(rows, kRB) * 3 * slabs(k)) * kChunk; }
 
-void pack(bool kmaj, int64_t rows, int64_t k, const void* X, int64_t ld, bool conj, void* P, hipStream_t st,
-          const OutMap* map = nullptr, int64_t r0 = 0, int64_t k0 = 0) {
+void pack(bool kmaj, int64_t rows, int64_t k, const void* X, int64_t ld, bool conj, void* P, int* flag,
+          hipStream_t st, const OutMap* map = nullptr, int64_t r0 = 0, int64_t k0 = 0) {
   const int64_t ns = slabs(k);
   const dim3 grid((unsigned)cdiv(rows, kRB), (unsigned)std::min<int64_t>(ns, 4096));
   if (map) kmaj = map->mstr[map->nm - 1] == 1;
   const DevMap dm(map ? *map : OutMap::plain(ld));
 #define PACK_(KM, MP)                                                                                              \
   hipLaunchKernelGGL((split_pack_kernel<KM, MP>), grid, dim3(256), 0, st, rows, k, (const float2*)X, ld, dm, r0, k0, \
-                     conj ? -1.0f : 1.0f, ns, (uint4*)P)
+                     conj ? -1.0f : 1.0f, ns, (uint4*)P, flag)
   if (kmaj && map)
     PACK_(true, true);
   else if (kmaj)
@@ -362,14 +380,14 @@ SplitPlan split_plan(int64_t m, int64_t n, int64_t k, size_t budget) {
   const int64_t chain = cdiv(cdiv(k, chains), 2 * kSlab) * 2 * kSlab;
   p.kl = std::min(k, chain * p.splits);
   // row blocks of the larger operand until both fit beside the partials
-  const size_t packs = budget - (p.splits > 1 ? (size_t)p.splits * m * n * 8 : 0);
+  const size_t packs = budget - kFlagBytes - (p.splits > 1 ? (size_t)p.splits * m * n * 8 : 0);
   int64_t& big = m >= n ? p.mc : p.nc;
   for (int64_t parts = 2; big > 2048 && pack_bytes(p.mc, p.kl) + pack_bytes(p.nc, p.kl) > packs; ++parts)
     big = cdiv(cdiv(m >= n ? m : n, parts), 256) * 256;
   p.a_bytes = pack_bytes(p.mc, p.kl);
   p.b_bytes = pack_bytes(p.nc, p.kl);
-  p.bytes = p.a_bytes + p.b_bytes + (p.splits > 1 ? (size_t)p.splits * p.mc * p.nc * 8 : 0);
-  if (p.a_bytes + p.b_bytes > budget || (p.splits > 1 && p.bytes > budget)) p.use = false;
+  p.bytes = p.a_bytes + p.b_bytes + (p.splits > 1 ? (size_t)p.splits * p.mc * p.nc * 8 : 0) + kFlagBytes;
+  if (p.bytes > budget) p.use = false;
   return p;
 }
 
@@ -381,6 +399,16 @@ void launch_split_gemm(const SplitPlan& p, bool ta, bool tb, int64_t m, int64_t 
   char* Pa = (char*)ws;
   char* Pb = Pa + p.a_bytes;
   char* part = Pb + p.b_bytes;
+  // Set in one block of the product, a flag holds for the later ones, too.
+  int* flags = (int*)((char*)ws + p.bytes - kFlagBytes);
+  hipLaunchKernelGGL(split_clear_kernel, dim3(1), dim3(2), 0, st, flags);
+  HIP_CHECK(hipGetLastError());
+  auto copy = [&](int64_t rows, int64_t kl, const void* X, const OutMap& map, int64_t r0, int64_t k0, void* out) {
+    const unsigned blocks = (unsigned)std::min<int64_t>(cdiv(rows * kl, 256), 4096);
+    hipLaunchKernelGGL(split_copy_kernel, dim3(blocks), dim3(256), 0, st, flags, rows, kl, (const float2*)X,
+                       DevMap(map), r0, k0, (float2*)out);
+    HIP_CHECK(hipGetLastError());
+  };
   const int64_t bm = p.small ? 128 : 256;
   for (int64_t k0 = 0; k0 < k; k0 += p.kl) {
     const int64_t kl = std::min(p.kl, k - k0), ns = slabs(kl);
@@ -390,16 +418,18 @@ void launch_split_gemm(const SplitPlan& p, bool ta, bool tb, int64_t m, int64_t 
     bool a_packed = false;
     for (int64_t n0 = 0; n0 < n; n0 += p.nc) {
       const int64_t nc = std::min(p.nc, n - n0);
+      const char* Bx = (const char*)B + (tb ? n0 * ldb + k0 : k0 * ldb + n0) * 8;
       if (p.bmap)
-        pack(false, nc, kl, B, 0, conjb, Pb, st, &p.mb, n0, k0);
+        pack(false, nc, kl, B, 0, conjb, Pb, flags + 1, st, &p.mb, n0, k0);
       else
-        pack(!tb, nc, kl, (const char*)B + (tb ? n0 * ldb + k0 : k0 * ldb + n0) * 8, ldb, conjb, Pb, st);
+        pack(!tb, nc, kl, Bx, ldb, conjb, Pb, flags + 1, st);
       for (int64_t m0 = 0; m0 < m; m0 += p.mc) {
         const int64_t mc = std::min(p.mc, m - m0);
+        const char* Ax = (const char*)A + (ta ? k0 * lda + m0 : m0 * lda + k0) * 8;
         if ((!a_packed || p.mc < m) && p.amap)
-          pack(false, mc, kl, A, 0, false, Pa, st, &p.ma, m0, k0);
+          pack(false, mc, kl, A, 0, false, Pa, flags, st, &p.ma, m0, k0);
         else if (!a_packed || p.mc < m)
-          pack(ta, mc, kl, (const char*)A + (ta ? k0 * lda + m0 : m0 * lda + k0) * 8, lda, false, Pa, st);
+          pack(ta, mc, kl, Ax, lda, false, Pa, flags, st);
         a_packed = true;
         const int64_t nb = cdiv(mc, bm) * cdiv(nc, 128);
         LRCC_REQUIRE(nb < (int64_t(1) << 31), LRCC_E_INVALID, "gemm grid too large");
@@ -412,11 +442,16 @@ void launch_split_gemm(const SplitPlan& p, bool ta, bool tb, int64_t m, int64_t 
         const int64_t om0 = parts ? 0 : m0, on0 = parts ? 0 : n0;
         if (p.small)
           hipLaunchKernelGGL((split_gemm_kernel<2, 2, 1>), grid, dim3(256), 0, st, mc, nc, ns, Pa, Pb, al[0], al[1],
-                             be[0], be[1], out, DevMap(mo), om0, on0, sc, mc * nc);
+                             be[0], be[1], out, DevMap(mo), om0, on0, sc, mc * nc, flags);
         else
           hipLaunchKernelGGL((split_gemm_kernel<4, 2, 2>), grid, dim3(512), 0, st, mc, nc, ns, Pa, Pb, al[0], al[1],
-                             be[0], be[1], out, DevMap(mo), om0, on0, sc, mc * nc);
+                             be[0], be[1], out, DevMap(mo), om0, on0, sc, mc * nc, flags);
         HIP_CHECK(hipGetLastError());
+        if (p.amap) copy(mc, kl, A, p.ma, m0, k0, Pa);
+        if (p.bmap) copy(nc, kl, B, p.mb, n0, k0, Pb);
+        launch_gemm_if(flags, ta && !p.amap, tb || p.bmap, mc, nc, kl, al[0], al[1], p.amap ? Pa : Ax,
+                       p.amap ? kl : lda, p.bmap ? Pb : Bx, p.bmap ? kl : ldb, be[0], be[1], out, mo, om0, on0, splits,
+                       sc * kSlab, conjb, st);
         if (parts) launch_splitk_reduce_f32(mc, nc, splits, part, are, aim, br, bi, C, om, m0, n0, st);
       }
     }

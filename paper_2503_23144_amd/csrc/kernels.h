@@ -196,6 +196,11 @@ SplitPlan split_plan(int64_t m, int64_t n, int64_t k, size_t budget = kPackBudge
 void launch_split_gemm(const SplitPlan& p, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim,
                        const void* A, int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C,
                        const OutMap& om, void* ws, hipStream_t st, bool conjb);
+// A block of such a product on FP32 MFMA, where gate[0] or gate[1] is set (both on the device).
+void launch_gemm_if(const int* gate, bool ta, bool tb, int64_t m, int64_t n, int64_t k, float are, float aim,
+                    const void* A, int64_t lda, const void* B, int64_t ldb, float bre, float bim, void* C,
+                    const OutMap& om, int64_t om0, int64_t on0, int splits, int64_t kchunk, bool conjb,
+                    hipStream_t st);
 // C[m0.., n0..] = alpha sum_s P[s] + beta C over an m x n block of FP32 partials
 void launch_splitk_reduce_f32(int64_t m, int64_t n, int splits, const void* P, double are, double aim, double bre,
                               double bim, void* C, const OutMap& om, int64_t m0, int64_t n0, hipStream_t st);
