@@ -212,10 +212,10 @@ void* Executor<T>::scratch(int slot, size_t bytes) {
 // taken only while it stays below an eighth of the free memory, so that the
 // buffers a run cannot do without keep their room, and not while a graph is
 // captured (a run before the capture has taken it, or the product runs
-// without).  Null when there is none.
+// without), nor while a tile is pinned.  Null when there is none.
 template <typename T>
 void* Executor<T>::pack_scratch(int64_t M, int64_t N, int64_t K, SplitPlan& s) {
-  if (sizeof(T) == 8) return nullptr;
+  if (sizeof(T) == 8 || gemm_tile_forced()) return nullptr;
   s = split_plan(M, N, K);
   if (!s.use) return nullptr;
   if (scr_cap_[kPackSlot] < s.bytes) {

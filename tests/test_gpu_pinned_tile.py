@@ -1,0 +1,49 @@
+"""Products of a context while a tile is pinned (lrcc_gemm_set_tile)."""
+import ctypes
+import os
+import re
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+TRACED = """
+import numpy as np
+from paper_2503_23144_amd import lrcc
+from paper_2503_23144_amd.synth import make_inputs
+inp = make_inputs(12, 90, 60, seed=1)
+lrcc.gemm_set_tile(0)
+c = lrcc.Context(precision="mixed", tol=1e-9)
+c.load_df(inp.o, inp.v, inp.B)
+c.load_fock(inp.fock)
+rng = np.random.default_rng(2)
+t = 0.01 * (rng.standard_normal(c.n) + 1j * rng.standard_normal(c.n))
+c.set_amplitudes(lrcc.AMP_T, t)
+X = rng.standard_normal((24, c.n)) + 1j * rng.standard_normal((24, c.n))
+for side in ("right", "left"):
+    c.sigma(side, X, precision="mixed")
+c.close()
+"""
+
+
+def test_pinned_products_keep_their_split_over_k():
+    """A pinned tile takes the products off the BF16 kernel, whose memory they
+    need no more; the deep ones are split over K as without it."""
+    from paper_2503_23144_amd import lrcc
+    print("traced products with tile 0 pinned", flush=True)
+    r = subprocess.run([sys.executable, "-c", TRACED], capture_output=True, text=True, cwd=ROOT, timeout=100,
+                       env=dict(os.environ, LRCC_TRACE_GEMM="1"))
+    assert r.returncode == 0, r.stderr[-2000:]
+    splits = lrcc.lib._ZN4lrcc11gemm_splitsElllb  # int gemm_splits(int64, int64, int64, bool)
+    splits.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_bool]
+    seen = 0
+    for m, n, k, tile, s in re.findall(r"c64 .* m=(\d+) n=(\d+) k=(\d+) tile=(\w+) splits=(\d+)", r.stderr):
+        m, n, k, s = int(m), int(n), int(k), int(s)
+        assert tile.isdigit() and s == splits(m, n, k, False), (m, n, k, tile, s)
+        seen += s > 1 and m * n * k >= 2e9  # large enough for the BF16 kernel
+    assert seen > 0
