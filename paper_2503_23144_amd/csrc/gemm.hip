@@ -604,7 +604,7 @@ static int forced_tile() {
   return t;
 }
 
-bool gemm_tile_forced() { return forced_tile() >= 0; }
+int gemm_pinned_tile() { return forced_tile(); }
 void set_gemm_tile(int tile) { g_forced_tile.store(tile >= 0 && tile <= 4 ? tile : -1); }
 
 // Split-K for deep products whose tile grid (64 x 64, or 128 x 32 where

@@ -207,8 +207,8 @@ void launch_splitk_reduce_f32(int64_t m, int64_t n, int splits, const void* P, d
 
 // Per-shape tile autotuning of launch_gemm (process-wide).
 void set_gemm_autotune(bool on);
-bool gemm_tile_forced();
-void set_gemm_tile(int tile);  // -1: automatic (autotuner or size heuristic)
+int gemm_pinned_tile();         // -1: automatic
+void set_gemm_tile(int tile);   // -1: automatic (autotuner or size heuristic)
 int gemm_tuned_shapes();
 // Tile the autotuner chose for a shape (kind 1: the ladder kernel), or -1.
 int gemm_tuned_tile(int prec, bool ta, bool tb, int kind, int64_t m, int64_t n, int64_t k);

@@ -186,7 +186,7 @@ class Executor {
     const OpList* ops;
     int nb;
     bool timing;
-    bool pinned;  // a pinned tile takes other kernels, with other scratch
+    int tile;  // pinned (-1: none): another tile is another kernel, with other scratch
     std::vector<int> keep;
     std::vector<void*> addr;  // every tensor and scratch buffer
     bool operator<(const RunKey& o) const;

@@ -215,7 +215,7 @@ void* Executor<T>::scratch(int slot, size_t bytes) {
 // without), nor while a tile is pinned.  Null when there is none.
 template <typename T>
 void* Executor<T>::pack_scratch(int64_t M, int64_t N, int64_t K, SplitPlan& s) {
-  if (sizeof(T) == 8 || gemm_tile_forced()) return nullptr;
+  if (sizeof(T) == 8 || gemm_pinned_tile() >= 0) return nullptr;
   s = split_plan(M, N, K);
   if (!s.use) return nullptr;
   if (scr_cap_[kPackSlot] < s.bytes) {
@@ -559,7 +559,7 @@ template <typename T>
 bool Executor<T>::packed_product(const Op& op, const std::string& a, const std::string& b, const std::string& c,
                                  const std::string& Mc, const std::string& Nc, const std::string& Kx, const void* pa,
                                  int64_t ca, const void* pb, int64_t cb, void* pc, int64_t cc, bool a_ok, bool b_ok) {
-  if (sizeof(T) == 8 || gemm_tile_forced()) return false;
+  if (sizeof(T) == 8 || gemm_pinned_tile() >= 0) return false;
   auto size = [&](const std::string& s) {
     int64_t p = 1;
     for (char ch : s) p *= ch == '#' ? g_nb : dim(ch);
@@ -1712,12 +1712,12 @@ void Executor<T>::run(const OpList& ops, int nb, const std::vector<int>& keep) {
 
 template <typename T>
 bool Executor<T>::RunKey::operator<(const RunKey& o) const {
-  return std::tie(ops, nb, timing, pinned, keep, addr) < std::tie(o.ops, o.nb, o.timing, o.pinned, o.keep, o.addr);
+  return std::tie(ops, nb, timing, tile, keep, addr) < std::tie(o.ops, o.nb, o.timing, o.tile, o.keep, o.addr);
 }
 
 template <typename T>
 typename Executor<T>::RunKey Executor<T>::make_key(const OpList& ops, int nb, const std::vector<int>& keep) const {
-  RunKey k{&ops, nb, timing_, gemm_tile_forced(), keep, {}};
+  RunKey k{&ops, nb, timing_, gemm_pinned_tile(), keep, {}};
   k.addr.reserve(buf_.size() + scr_.size() + pool_.size());
   k.addr.insert(k.addr.end(), buf_.begin(), buf_.end());
   k.addr.insert(k.addr.end(), scr_.begin(), scr_.end());

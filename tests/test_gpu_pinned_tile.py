@@ -47,3 +47,29 @@ def test_pinned_products_keep_their_split_over_k():
         assert tile.isdigit() and s == splits(m, n, k, False), (m, n, k, tile, s)
         seen += s > 1 and m * n * k >= 2e9  # large enough for the BF16 kernel
     assert seen > 0
+
+
+def test_another_pinned_tile_is_another_recorded_run():
+    """A run recorded with one tile is not replayed once another is pinned."""
+    from paper_2503_23144_amd import lrcc
+    from paper_2503_23144_amd.synth import make_inputs
+    print("recorded runs per tile", flush=True)
+    inp = make_inputs(6, 40, 20, seed=1)
+    c = lrcc.Context(tol=1e-9)
+    c.load_df(inp.o, inp.v, inp.B)
+    c.load_fock(inp.fock)
+    rng = np.random.default_rng(2)
+    t = 0.01 * (rng.standard_normal(c.n) + 1j * rng.standard_normal(c.n))
+    c.set_amplitudes(lrcc.AMP_T, t)
+    X = rng.standard_normal((2, c.n)) + 1j * rng.standard_normal((2, c.n))
+    try:
+        for tile in (0, 3, 4, -1):
+            lrcc.gemm_set_tile(tile)
+            for step, (cap, rep) in enumerate([(0, 0), (1, 0), (0, 1), (0, 1)]):  # eager, captured, replayed
+                before = c.graph_stats()
+                c.sigma("right", X)
+                after = c.graph_stats()
+                assert (after[0] - before[0], after[1] - before[1]) == (cap, rep), (tile, step)
+    finally:
+        lrcc.gemm_set_tile(-1)
+    c.close()
