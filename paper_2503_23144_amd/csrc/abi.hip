@@ -382,12 +382,8 @@ int lrcc_gemm(int precision, int transa, int transb, int64_t m, int64_t n, int64
     LRCC_REQUIRE(precision == LRCC_FP64 || precision == LRCC_MIXED, LRCC_E_INVALID, "bad precision");
     LRCC_REQUIRE(m >= 0 && n >= 0 && k >= 0, LRCC_E_INVALID, "negative size");
     LRCC_REQUIRE(lda >= (transa ? m : k) && ldb >= (transb ? k : n) && ldc >= n, LRCC_E_INVALID, "leading dimension");
-    // deep products with few output tiles are split over K into a temporary
-    // workspace; the splits of shallower ones would not repay its allocation
-    const bool deep = lrcc::gemm_splits(m, n, k, precision == LRCC_FP64) > 1;
-    const size_t wsb = !deep ? 0
-                       : precision == LRCC_FP64 ? lrcc::gemm_workspace_bytes<double>(m, n, k, lda, ldb)
-                                                : lrcc::gemm_workspace_bytes<float>(m, n, k, lda, ldb);
+    // deep products with few output tiles are split over K into a temporary workspace
+    const size_t wsb = lrcc::gemm_call_workspace(precision == LRCC_FP64, m, n, k, lda, ldb);
     lrcc::DevBuf ws;
     if (wsb) ws.ensure(wsb);
     if (precision == LRCC_FP64)

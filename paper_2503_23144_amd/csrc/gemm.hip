@@ -651,6 +651,11 @@ size_t gemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int64_t lda, int64_
   return split_bytes<T>(m, n, gemm_splits(m, n, k, sizeof(T) == 8));
 }
 
+size_t gemm_call_workspace(bool fp64, int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb) {
+  if (gemm_splits(m, n, k, fp64) < 2) return 0;
+  return fp64 ? gemm_workspace_bytes<double>(m, n, k, lda, ldb) : gemm_workspace_bytes<float>(m, n, k, lda, ldb);
+}
+
 template <typename T>
 void launch_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim, const void* A,
                  int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C, int64_t ldc,

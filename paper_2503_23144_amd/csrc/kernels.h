@@ -145,6 +145,10 @@ void launch_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, 
 int gemm_splits(int64_t m, int64_t n, int64_t k, bool fp64);  // of the tiled kernel
 template <typename T>
 size_t gemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb);
+// What lrcc_gemm and lrcc_gemm_noalloc, which sum alike, give a product: none
+// where the tiled kernel would not split it either.  lrcc_gemm allocates it
+// and waits for the product, which the split of a shallower one would not repay.
+size_t gemm_call_workspace(bool fp64, int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb);
 
 // Products with few or narrow tiles (gemm_wave.hip): the variant that runs
 // one (-1: the tiled kernel does), its splits over K and their depth.
