@@ -100,10 +100,11 @@ struct Tile {
 // Split-K: blockIdx.y selects the depth range [y * kchunk, (y + 1) * kchunk)
 // and the output C + y * cstride (partial products, reduced afterwards).
 //
-// The product may be the block of a larger one that starts at row om0 and
-// column on0 of the output map.  With a gate (two words) it runs only where
-// one of them is set (launch_gemm_if).
-template <typename T, bool TA, bool TB, int KIND, int BM, int BN, int WGM, int BK, int NW>
+// GATED (launch_gemm_if): the product is the block of a larger one that starts at
+// row om0 and column on0 of the output map, and runs only where one of the gate's
+// two words is set.  A kernel of its own: the three more arguments cost the
+// others up to 5 % on small products.
+template <typename T, bool TA, bool TB, int KIND, int BM, int BN, int WGM, int BK, int NW, bool GATED = false>
 __global__ void __launch_bounds__(64 * NW) zgemm_kernel(int64_t M, int64_t N, int64_t K, T are, T aim,
                                                   const typename cpx<T>::type* __restrict__ A, int64_t lda,
                                                   const typename cpx<T>::type* __restrict__ B, int64_t ldb, T bre,
@@ -112,7 +113,9 @@ __global__ void __launch_bounds__(64 * NW) zgemm_kernel(int64_t M, int64_t N, in
                                                   int64_t on0, const int* __restrict__ gate) {
   using V2 = typename cpx<T>::type;
   constexpr int NT = 64 * NW;
-  if (gate && !(gate[0] | gate[1])) return;
+  if constexpr (GATED) {
+    if (!(gate[0] | gate[1])) return;
+  }
   {
     const int64_t kbeg = (int64_t)blockIdx.y * kchunk;
     K = (K < kbeg + kchunk ? K : kbeg + kchunk) - kbeg;
@@ -295,7 +298,7 @@ __global__ void __launch_bounds__(64 * NW) zgemm_kernel(int64_t M, int64_t N, in
 #pragma unroll
   for (int j = 0; j < TJ; ++j) {
     const int64_t gn = n0 + wn + j * 16 + r16;
-    coff[j] = gn < N ? om.col(on0 + gn) : -1;
+    coff[j] = gn < N ? om.col(GATED ? on0 + gn : gn) : -1;
   }
 #pragma unroll
   for (int i = 0; i < TI; ++i)
@@ -303,7 +306,7 @@ __global__ void __launch_bounds__(64 * NW) zgemm_kernel(int64_t M, int64_t N, in
     for (int r = 0; r < 4; ++r) {
       const int64_t gm = m0 + wm + i * 16 + cpx<T>::row(kq, r);
       if (gm >= M) continue;
-      const int64_t roff = om.row(om0 + gm);
+      const int64_t roff = om.row(GATED ? om0 + gm : gm);
 #pragma unroll
       for (int j = 0; j < TJ; ++j) {
         if (coff[j] < 0) continue;
@@ -447,7 +450,7 @@ void launch_gemm_if(const int* gate, bool ta, bool tb, int64_t m, int64_t n, int
   const int64_t nb = ((m + 63) / 64) * ((n + 63) / 64);
   LRCC_REQUIRE(nb < (int64_t(1) << 24), LRCC_E_INVALID, "gemm grid too large");
 #define IF_(TA_, TB_)                                                                                               \
-  hipLaunchKernelGGL((zgemm_kernel<float, TA_, TB_, 0, 64, 64, 2, 16, 4>), dim3((unsigned)nb, (unsigned)splits),     \
+  hipLaunchKernelGGL((zgemm_kernel<float, TA_, TB_, 0, 64, 64, 2, 16, 4, true>), dim3((unsigned)nb, (unsigned)splits),     \
                      dim3(256), 0, st, m, n, k, are, aim, (const float2*)A, lda, (const float2*)B, ldb, bre, bim,    \
                      (float2*)C, DevMap(om), kchunk, m* n, conjb ? -1.0f : 1.0f, om0, on0, gate)
   if (!ta && !tb)
