@@ -383,7 +383,7 @@ int lrcc_gemm(int precision, int transa, int transb, int64_t m, int64_t n, int64
     LRCC_REQUIRE(m >= 0 && n >= 0 && k >= 0, LRCC_E_INVALID, "negative size");
     LRCC_REQUIRE(lda >= (transa ? m : k) && ldb >= (transb ? k : n) && ldc >= n, LRCC_E_INVALID, "leading dimension");
     // deep products with few output tiles are split over K into a temporary workspace
-    const size_t wsb = lrcc::gemm_call_workspace(precision == LRCC_FP64, m, n, k, lda, ldb);
+    const size_t wsb = lrcc::gemm_call_workspace(precision == LRCC_FP64, transa != 0, transb != 0, m, n, k, lda, ldb);
     lrcc::DevBuf ws;
     if (wsb) ws.ensure(wsb);
     if (precision == LRCC_FP64)

@@ -541,6 +541,32 @@ void launch_wave_gemm(const WavePlan& p, bool ta, bool tb, int64_t m, int64_t n,
   throw Error(LRCC_E_INTERNAL, "unknown wavefront GEMM variant");
 }
 
+// This kernel's time: as tiled_us, with the depth in place of slabs.  sigma is
+// one depth of a layer of workgroups (variants 0 to 2: a 16 x 16 or 32 x 32 tile
+// each; 3 and 4: four tiles), by transposition (A, B: NN, NT, TN, TT); delta is a
+// depth's latency.  Fitted to the shapes of tiled_us that ran here; standard
+// deviation FP64 4, 3, 6 % (variants 2, 3, 4), FP32 8, 6, 5 %.
+namespace {
+struct WaveCost {
+  double call, f, reduce, tile, delta, sigma[4];
+};
+template <typename T>
+double wave_us(const WavePlan& p, bool ta, bool tb, int64_t m, int64_t n) {
+  static const WaveCost c64[3] = {{0.0, 0.07, 4.7, 4.4, 0.0026, {0.0326, 0.0332, 0.0323, 0.0327}},
+                                  {2.8, 0.34, 4.0, 2.2, 0.0, {0.0051, 0.0051, 0.0113, 0.0130}},
+                                  {3.0, 0.05, 4.0, 2.13, 0.0151, {0.0662, 0.0710, 0.0768, 0.0689}}};
+  static const WaveCost c32[3] = {{1.0, 0.02, 4.3, 3.0, 0.0026, {0.0180, 0.0135, 0.0184, 0.0177}},
+                                  {2.1, 0.20, 3.5, 0.96, 0.0331, {0.0134, 0.0101, 0.0186, 0.0157}},
+                                  {2.6, 0.18, 2.0, 1.53, 0.0156, {0.0308, 0.0291, 0.0327, 0.0310}}};
+  const WaveCost& c = (sizeof(T) == 8 ? c64 : c32)[p.variant - 2];
+  const int64_t rows = p.variant == 2 ? 32 : 16, cols = p.variant == 3 ? 16 : 32, per = p.variant == 2 ? 1 : 4;
+  const int64_t tiles = ((m + rows - 1) / rows) * ((n + cols - 1) / cols);
+  const double layers = gemm_layers((tiles + per - 1) / per * p.splits, c.f);
+  return c.call + layers * ((double)p.kchunk * c.sigma[ta * 2 + tb] + c.tile) + (double)p.kchunk * c.delta +
+         (p.splits > 1 ? c.reduce : 0.0);
+}
+}  // namespace
+
 // Which products run here, and how.  t16 and t32 count the 16 x 16 and
 // 32 x 32 tiles of the output; figures are tiled kernel / this kernel in us.
 //  * Addresses are 32-bit offsets from a tile's base: a leading dimension
@@ -555,15 +581,24 @@ void launch_wave_gemm(const WavePlan& p, bool ta, bool tb, int64_t m, int64_t n,
 //    62 / 73) and takes the tiled kernel from 4096 tiles on.
 //  * One 16 x 16 tile per workgroup where an extent is at most 16 or 32 x 32
 //    tiles are few (FP64 600^3 42 against 48 on 32 x 32); 8 wavefronts below
-//    512 tiles, 4 above.
+//    512 tiles, 4 above.  These gain 1.2 times at least (but for one of 866 shapes).
 //  * 32 x 32 tiles otherwise: in FP64 until 1024 tiles of 128 x 128 fill the
 //    chip at the tiled kernel's higher intensity (18000x3000x3000 runs at 62-66
 //    TFLOP/s there), in FP32 below 4e9 complex MACs or at most 96 wide
 //    (1728x576x57600 2862 / 3511, 72x240x518400 999 / 810).
 //  * Splits over K fill the chip's workgroup slots: at least 384 depths each
 //    for the 16 x 16 tile, 256 for 32 x 32 (partials of at most 64 MB).
+//  * A tile per wavefront and the 32 x 32 tiles only where their estimated time
+//    is 3 % below the tiled kernel's.  The two are close once the chip is full,
+//    and which one its last layer of tiles suits decides: FP64 NN 4000x3900x3000
+//    6740 / 6135, NN 4000x3900x600 1381 / 1410, NT 9000x1700x3000 6225 / 6970, TN
+//    9784x612x25 43 / 62; FP32 NN 388x4541x736 98 / 133, TT 1684x1374x1637 309 /
+//    169.  Of 765 (FP64, 260 of them above 4e9 complex MACs) and 517 (FP32)
+//    shapes run here without this line, 67 and 36 lost 3 % or more, up to 45 %;
+//    with it one and none, and the mean gain over all shapes is no less (2.733
+//    -> 2.740 and 2.562 -> 2.567 times, large FP64 ones 1.076 -> 1.075).
 template <typename T>
-WavePlan wave_plan(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bool can_split) {
+WavePlan wave_plan(bool ta, bool tb, int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bool can_split) {
   constexpr bool F64 = sizeof(T) == 8;
   WavePlan p;
   if (m <= 0 || n <= 0 || k <= 0) return p;
@@ -587,23 +622,25 @@ WavePlan wave_plan(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bo
     slots = F64 ? 256 : 512, mink = 256, tiles = t32;
   }
   p.kchunk = k;
-  if (!can_split || tiles == 0 || tiles >= 2 * slots) return p;
-  const int64_t part = m * n * (int64_t)(2 * sizeof(T));
-  const int64_t smax = std::min<int64_t>({64, k / mink, (int64_t(64) << 20) / part});
-  auto eff = [&](int64_t s) {
-    const int64_t w = tiles * s, rounds = cdiv(w, slots);
-    return (double)w / (double)(rounds * slots);
-  };
-  double best = 0;
-  for (int64_t s = 1; s <= smax; ++s) best = std::max(best, eff(s));
-  for (int64_t s = 1; s <= smax; ++s)
-    if (eff(s) >= 0.9 * best) {
-      if (s > 1 && eff(s) >= 1.15 * eff(1)) {
-        p.kchunk = cdiv(cdiv(k, s), 16) * 16;
-        p.splits = (int)cdiv(k, p.kchunk);
+  if (can_split && tiles > 0 && tiles < 2 * slots) {
+    const int64_t part = m * n * (int64_t)(2 * sizeof(T));
+    const int64_t smax = std::min<int64_t>({64, k / mink, (int64_t(64) << 20) / part});
+    auto eff = [&](int64_t s) {
+      const int64_t w = tiles * s, rounds = cdiv(w, slots);
+      return (double)w / (double)(rounds * slots);
+    };
+    double best = 0;
+    for (int64_t s = 1; s <= smax; ++s) best = std::max(best, eff(s));
+    for (int64_t s = 1; s <= smax; ++s)
+      if (eff(s) >= 0.9 * best) {
+        if (s > 1 && eff(s) >= 1.15 * eff(1)) {
+          p.kchunk = cdiv(cdiv(k, s), 16) * 16;
+          p.splits = (int)cdiv(k, p.kchunk);
+        }
+        break;
       }
-      break;
-    }
+  }
+  if (p.variant >= 2 && wave_us<T>(p, ta, tb, m, n) >= 0.97 * tiled_us(F64, ta, tb, m, n, k, can_split)) return WavePlan();
   return p;
 }
 
@@ -611,7 +648,7 @@ WavePlan wave_plan(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bo
   template void launch_wave_gemm<T>(const WavePlan&, bool, bool, int64_t, int64_t, int64_t, double, double,         \
                                     const void*, int64_t, const void*, int64_t, double, double, void*,              \
                                     const OutMap&, int64_t, hipStream_t, bool);                                     \
-  template WavePlan wave_plan<T>(int64_t, int64_t, int64_t, int64_t, int64_t, bool);                                \
+  template WavePlan wave_plan<T>(bool, bool, int64_t, int64_t, int64_t, int64_t, int64_t, bool);                    \
   template size_t mapped_gemm_workspace<T>(const MappedProduct*, int);                                              \
   template void launch_mapped_gemm<T>(const MappedProduct*, int, void*, hipStream_t);
 INST_(double)

@@ -143,12 +143,18 @@ void launch_gemm(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, 
                  bool allow_tune = true,   // false: never time candidate tiles (no device allocation)
                  const struct SplitPlan* sp = nullptr, void* pack_ws = nullptr);  // FP32: split_plan and its memory
 int gemm_splits(int64_t m, int64_t n, int64_t k, bool fp64);  // of the tiled kernel
+double tiled_us(bool fp64, bool ta, bool tb, int64_t m, int64_t n, int64_t k, bool can_split);  // estimate
+// Layers of w workgroups over 256 CUs, the last one counted between whole (f = 0) and by its share (f = 1).
+inline double gemm_layers(int64_t w, double f) {
+  const double l = (double)w / 256.0;
+  return (1.0 - f) * (double)((w + 255) / 256) + f * (l > 1.0 ? l : 1.0);
+}
 template <typename T>
-size_t gemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb);
+size_t gemm_workspace_bytes(bool ta, bool tb, int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb);
 // What lrcc_gemm and lrcc_gemm_noalloc, which sum alike, give a product: none
 // where the tiled kernel would not split it either.  lrcc_gemm allocates it
 // and waits for the product, which the split of a shallower one would not repay.
-size_t gemm_call_workspace(bool fp64, int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb);
+size_t gemm_call_workspace(bool fp64, bool ta, bool tb, int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb);
 
 // Products with few or narrow tiles (gemm_wave.hip): the variant that runs
 // one (-1: the tiled kernel does), its splits over K and their depth.
@@ -157,7 +163,7 @@ struct WavePlan {
   int64_t kchunk = 0;
 };
 template <typename T>
-WavePlan wave_plan(int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bool can_split);
+WavePlan wave_plan(bool ta, bool tb, int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bool can_split);
 // Partials go to C + split * cstride when the plan splits.
 template <typename T>
 void launch_wave_gemm(const WavePlan& p, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim,

@@ -64,7 +64,7 @@ extern "C" int lrcc_gemm_noalloc(int precision, int transa, int transb, int64_t 
     LRCC_REQUIRE(precision == LRCC_FP64 || precision == LRCC_MIXED, LRCC_E_INVALID, "bad precision");
     LRCC_REQUIRE(m >= 0 && n >= 0 && k >= 0, LRCC_E_INVALID, "negative size");
     LRCC_REQUIRE(lda >= (transa ? m : k) && ldb >= (transb ? k : n) && ldc >= n, LRCC_E_INVALID, "leading dimension");
-    const size_t wsb = gemm_call_workspace(precision == LRCC_FP64, m, n, k, lda, ldb);
+    const size_t wsb = gemm_call_workspace(precision == LRCC_FP64, transa != 0, transb != 0, m, n, k, lda, ldb);
     LRCC_REQUIRE(wsb <= kStaticScratchBytes, LRCC_E_INVALID,
                  "product needs " + std::to_string(wsb) + " bytes of split-K partials, above the " +
                      std::to_string(kStaticScratchBytes) + "-byte static scratch of lrcc_gemm_noalloc");

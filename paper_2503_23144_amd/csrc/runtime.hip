@@ -364,7 +364,7 @@ bool Executor<T>::gemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double
   if ((am || bm) && !pack) return false;
   if (am) sp.amap = true, sp.ma = *am;
   if (bm) sp.bmap = true, sp.mb = *bm;
-  const size_t wsb = pack ? 0 : gemm_workspace_bytes<T>(M, N, K, lda, ldb);
+  const size_t wsb = pack ? 0 : gemm_workspace_bytes<T>(ta, tb, M, N, K, lda, ldb);
   void* ws = wsb ? scratch(4, wsb) : nullptr;
   GemmArgs g{ta, tb, M,  N,   K,        are,           aim,   A,    lda,  B,
              ldb, bre, C, ldc, ladder, ws, wsb, OutMap(), om != nullptr, conjb, pack, sp};
