@@ -104,11 +104,12 @@ struct Tile {
 // row om0 and column on0 of the output map, and runs only where one of the gate's
 // two words is set.  A kernel of its own: the three more arguments cost the
 // others up to 5 % on small products.
-template <typename T, bool TA, bool TB, int KIND, int BM, int BN, int WGM, int BK, int NW, bool GATED = false>
+template <typename T, bool TA, bool TB, int KIND, int BM, int BN, int WGM, int BK, int NW, typename MAP,
+          bool GATED = false>
 __global__ void __launch_bounds__(64 * NW) zgemm_kernel(int64_t M, int64_t N, int64_t K, T are, T aim,
                                                   const typename cpx<T>::type* __restrict__ A, int64_t lda,
                                                   const typename cpx<T>::type* __restrict__ B, int64_t ldb, T bre,
-                                                  T bim, typename cpx<T>::type* __restrict__ C, DevMap om,
+                                                  T bim, typename cpx<T>::type* __restrict__ C, MAP om,
                                                   int64_t kchunk, int64_t cstride, T bsgn, int64_t om0,
                                                   int64_t on0, const int* __restrict__ gate) {
   using V2 = typename cpx<T>::type;
@@ -421,20 +422,27 @@ static void go(bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, do
     out = ws, mo = OutMap::plain(n), cstride = m * n;
     ar = 1, ai = 0, br = 0, bi = 0;
   }
-#define GO_(TA_, TB_)                                                                                        \
-  hipLaunchKernelGGL((zgemm_kernel<T, TA_, TB_, KIND, BM, BN, WGM, BK, NW>), dim3((unsigned)nb, (unsigned)splits), dim3(NT), \
-                     0, st, m, n, k, (T)ar, (T)ai, (const V2*)A, lda, (const V2*)B, ldb, (T)br, (T)bi, (V2*)out, \
-                     DevMap(mo), \
-                     kchunk, cstride, (T)(conjb ? -1.0 : 1.0), int64_t(0), int64_t(0), (const int*)nullptr)
-  if (!ta && !tb)
-    GO_(false, false);
-  else if (!ta && tb)
-    GO_(false, true);
-  else if (ta && !tb)
-    GO_(true, false);
-  else
-    GO_(true, true);
+  auto launch = [&](auto map) {
+    using MAP = decltype(map);
+#define GO_(TA_, TB_)                                                                                           \
+  hipLaunchKernelGGL((zgemm_kernel<T, TA_, TB_, KIND, BM, BN, WGM, BK, NW, MAP>),                                 \
+                     dim3((unsigned)nb, (unsigned)splits), dim3(NT), 0, st, m, n, k, (T)ar, (T)ai, (const V2*)A,   \
+                     lda, (const V2*)B, ldb, (T)br, (T)bi, (V2*)out, map, kchunk, cstride,                         \
+                     (T)(conjb ? -1.0 : 1.0), int64_t(0), int64_t(0), (const int*)nullptr)
+    if (!ta && !tb)
+      GO_(false, false);
+    else if (!ta && tb)
+      GO_(false, true);
+    else if (ta && !tb)
+      GO_(true, false);
+    else
+      GO_(true, true);
 #undef GO_
+  };
+  if (KIND >= 2 || mo.rows())  // probes write rows
+    launch(RowMap{mo.mstr[0]});
+  else if constexpr (KIND < 2)
+    launch(DevMap(mo));
   HIP_CHECK(hipGetLastError());
   if (splits > 1) launch_splitk_reduce<T>(m, n, splits, ws, are, aim, bre, bim, C, om, st);
 }
@@ -450,7 +458,7 @@ void launch_gemm_if(const int* gate, bool ta, bool tb, int64_t m, int64_t n, int
   const int64_t nb = ((m + 63) / 64) * ((n + 63) / 64);
   LRCC_REQUIRE(nb < (int64_t(1) << 24), LRCC_E_INVALID, "gemm grid too large");
 #define IF_(TA_, TB_)                                                                                               \
-  hipLaunchKernelGGL((zgemm_kernel<float, TA_, TB_, 0, 64, 64, 2, 16, 4, true>), dim3((unsigned)nb, (unsigned)splits),     \
+  hipLaunchKernelGGL((zgemm_kernel<float, TA_, TB_, 0, 64, 64, 2, 16, 4, DevMap, true>), dim3((unsigned)nb, (unsigned)splits),     \
                      dim3(256), 0, st, m, n, k, are, aim, (const float2*)A, lda, (const float2*)B, ldb, bre, bim,    \
                      (float2*)C, DevMap(om), kchunk, m* n, conjb ? -1.0f : 1.0f, om0, on0, gate)
   if (!ta && !tb)
