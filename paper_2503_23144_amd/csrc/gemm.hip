@@ -655,7 +655,8 @@ int gemm_splits(int64_t m, int64_t n, int64_t k, bool fp64) {
 // and its loads delta behind them.  A last, partly filled layer of workgroups
 // costs f of its share and 1 - f of a full one.  Fitted to 1450 (FP64) and 1200
 // (FP32) shapes of extents 16 to 12000 in all four transpositions (tau: NN, NT,
-// TN, TT); standard deviation 3.3 and 3.2 %.
+// TN, TT); standard deviation 3.3 and 3.2 %.  FP32 products beyond those come to
+// 118 TFLOP/s, 1 + 60 / k times that for a shallow tile (k = 150: 85).
 double tiled_us(bool fp64, bool ta, bool tb, int64_t m, int64_t n, int64_t k, bool can_split) {
   static const double tau64[4] = {2.20, 2.17, 2.20, 2.19}, tau32[4] = {0.831, 0.789, 0.866, 0.890};
   const double call = fp64 ? 2.7 : 3.7, tau = (fp64 ? tau64 : tau32)[ta * 2 + tb], delta = 0.42, f = fp64 ? 0.16 : 0.20,
@@ -666,7 +667,10 @@ double tiled_us(bool fp64, bool ta, bool tb, int64_t m, int64_t n, int64_t k, bo
   const int64_t slabs = ((k + s - 1) / s + 15) / 16;
   s = (k + slabs * 16 - 1) / (slabs * 16);
   const double layers = gemm_layers(tiles * s, f);
-  return call + (double)slabs * (tau * layers + delta) + tile * layers + (s > 1 ? reduce : 0.0);
+  const double us = call + (double)slabs * (tau * layers + delta) + tile * layers + (s > 1 ? reduce : 0.0);
+  if (fp64 || (double)m * n * k < 3e10) return us;
+  const double area = (double)tiles * (narrow ? 128 * 32 : 64 * 64);
+  return std::max(us, 6.0 / 118e6 * area * (double)(k + 60));
 }
 
 template <typename T>

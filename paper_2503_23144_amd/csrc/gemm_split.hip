@@ -334,61 +334,93 @@ void pack(bool kmaj, int64_t rows, int64_t k, const void* X, int64_t ld, bool co
 }
 }  // namespace
 
-// Both kernels' times are estimated and this one runs where it saves 8 %:
-// 6 MNK over 190 TFLOP/s here (177 with the 128 x 128 tile, which serves
-// extents that pad the 256-row tile more) and 118 on the tiled kernel, on
-// extents padded to each one's tiles, both 1 + 60 / k times that for the
-// fill and drain of a shallow tile (k = 150: 85 TFLOP/s tiled), and the
-// packing's 26 bytes per operand element at 4.9 TB/s.  Measured, tiled ->
-// here, us: 540000x400x400 5330 -> 4610, 8052x671x671 224 -> 205;
-// 9600x400x22500 (28 % padding) would stay at 4950.  Below a depth of 256 the
-// output's traffic is no longer hidden, one workgroup per CU (480x450000x150
-// 2460 -> 2670); below 2e9 MACs the wavefront kernel or the launches decide.
-// Where the tiles leave the chip's 256 slots (512 for the smaller tile)
-// badly filled, several chains of K run side by side into partials.
-// Operands larger than the budget are packed in row blocks of the larger one.
-SplitPlan split_plan(int64_t m, int64_t n, int64_t k, size_t budget) {
-  SplitPlan p;
-  if (m <= 0 || n <= 0 || k < 256 || (double)m * n * k < 2e9) return p;
-  auto padded = [](int64_t x, int64_t to) { return (double)(cdiv(x, to) * to); };
-  const double fill = 1.0 + 60.0 / (double)k;
-  const double big_s = padded(m, 256) / 190e12, small_s = padded(m, 128) / 177e12;
-  p.small = small_s < big_s;
-  const double here = 6.0 * std::min(big_s, small_s) * padded(n, 128) * (double)k * fill +
-                      26.0 / 4.9e12 * (double)(m + n) * (double)k + 10e-6;
-  const double tiled = 6.0 * padded(m, 64) * padded(n, 64) * (double)k / 118e12 * fill;
-  if (here > 0.92 * tiled) return p;
-  p.use = true;
-  p.mc = m, p.nc = n;
-  int64_t chains = cdiv(k, kChain);
-  const int64_t tiles = cdiv(m, p.small ? 128 : 256) * cdiv(n, 128), slots = p.small ? 512 : 256;
-  auto eff = [&](int64_t s) {
-    const int64_t w = tiles * s;
-    return (double)w / (double)(cdiv(w, slots) * slots);
-  };
-  if (tiles < 4 * slots) {
-    const int64_t smax = std::min<int64_t>({8, k / 512, (int64_t)(budget / 4) / (m * n * 8)});
-    double best = 0;
-    for (int64_t s = 1; s <= smax; ++s) best = std::max(best, eff(s));
-    for (int64_t s = 1; s <= smax; ++s)
-      if (eff(s) >= 0.95 * best) {
-        if (eff(s) >= 1.1 * eff(1)) p.splits = (int)s;
-        break;
-      }
+// This kernel's time with the plan p, as tiled_us: layers of workgroups, one per
+// CU of the 256 x 128 tile, sigma a depth and `tile` a tile for its fill, drain
+// and output; two of the 128 x 128 tile share a CU, so that a layer of half the
+// work overlaps the next one but for delta a depth.  Packing, output and partials
+// are traffic, in us per million elements.  Fitted to 308 products of 2e9 to 3e10
+// complex MACs, in one and in several blocks; standard deviation 4 % (6 % with
+// the smaller tile).  Those are over before the card's power limit tells: a
+// longer run comes to 195 TFLOP/s (180 with the smaller tile) on the padded
+// extents, which leaves 18000x3000x3000 at 5150 us (measured 4960) and
+// 540000x400x400 at 5030 (4610), packing included.
+namespace {
+double split_us(const SplitPlan& p, int64_t m, int64_t n, int64_t k) {
+  const double sigma = p.small ? 0.090 : 0.1815, delta = p.small ? 0.065 : 0.0, f = p.small ? 0.68 : 0.0,
+               tile = p.small ? 2.4 : 12.2, call = 5.0, packing = 6.5e-6, out = 1.2e-6, part = 1.8e-6;
+  const double sustained = 6.0 / (p.small ? 180e6 : 195e6);
+  const int64_t bm = p.small ? 128 : 256, nm = cdiv(m, p.mc), nn = cdiv(n, p.nc), nk = cdiv(k, p.kl);
+  double us = packing * (double)k * ((double)n + (double)m * (double)(nm > 1 ? nn : 1));
+  for (int e = 0; e < 8; ++e) {  // the full and the last block of rows, of columns, of depth
+    const int64_t cm = e & 1 ? 1 : nm - 1, cn = e & 2 ? 1 : nn - 1, ck = e & 4 ? 1 : nk - 1;
+    const int64_t mb = e & 1 ? m - (nm - 1) * p.mc : p.mc, nb = e & 2 ? n - (nn - 1) * p.nc : p.nc,
+                  kb = e & 4 ? k - (nk - 1) * p.kl : p.kl;
+    if (cm * cn * ck == 0) continue;
+    const double tiles = (double)(cdiv(mb, bm) * cdiv(nb, 128)), mn = (double)mb * (double)nb;
+    const double depth = (double)kb / p.splits;
+    const double layers = gemm_layers((int64_t)tiles * p.splits, f) * (depth * sigma + tile) + depth * delta;
+    const double power = sustained * tiles * (double)(bm * 128) * (double)kb;
+    us += (double)(cm * cn * ck) *
+          (call + std::max(layers, power) + out * mn + (p.splits > 1 ? part * mn * p.splits : 0.0));
   }
-  chains = cdiv(chains, p.splits) * p.splits;
-  const int64_t chain = cdiv(cdiv(k, chains), 2 * kSlab) * 2 * kSlab;
-  p.kl = std::min(k, chain * p.splits);
-  // row blocks of the larger operand until both fit beside the partials
-  const size_t packs = budget - kFlagBytes - (p.splits > 1 ? (size_t)p.splits * m * n * 8 : 0);
-  int64_t& big = m >= n ? p.mc : p.nc;
-  for (int64_t parts = 2; big > 2048 && pack_bytes(p.mc, p.kl) + pack_bytes(p.nc, p.kl) > packs; ++parts)
-    big = cdiv(cdiv(m >= n ? m : n, parts), 256) * 256;
-  p.a_bytes = pack_bytes(p.mc, p.kl);
-  p.b_bytes = pack_bytes(p.nc, p.kl);
-  p.bytes = p.a_bytes + p.b_bytes + (p.splits > 1 ? (size_t)p.splits * p.mc * p.nc * 8 : 0) + kFlagBytes;
-  if (p.bytes > budget) p.use = false;
-  return p;
+  return us;
+}
+}  // namespace
+
+// The plan of least estimated time that fits the budget: chains of K side by side
+// into partials, depth of a pass, row blocks of either operand, with the smaller
+// tile where the larger one pads the rows by 7 % more.  It is taken where it saves 5 % of the FP32 kernels' estimate.  Row blocks leave a
+// launch few tiles, shorter passes read and write the output once more: 9814 x
+// 374 x 3986 in 256 MiB, rows of one operand in five blocks, took 1976 us
+// (tiled 959).  Below a depth of 256 the output's traffic is no longer hidden,
+// one workgroup per CU (480x450000x150 2460 -> 2670); below 2e9 MACs the
+// wavefront kernel or the launches decide.  Measured, FP32 MFMA -> here, us:
+// 540000x400x400 5330 -> 4610, 8052x671x671 224 -> 205.
+SplitPlan split_plan(bool ta, bool tb, int64_t m, int64_t n, int64_t k, size_t budget) {
+  SplitPlan best;
+  if (m <= 0 || n <= 0 || k < 256 || (double)m * n * k < 2e9) return best;
+  const WavePlan w = wave_plan<float>(ta, tb, m, n, k, ta ? m : k, tb ? k : n, true);
+  if (w.variant == 0 || w.variant == 1) return best;  // an extent of at most 16
+  double least = 0.95 * (w.variant > 0 ? w.us : tiled_us(false, ta, tb, m, n, k, true));
+  auto consider = [&](const SplitPlan& q) {
+    const double us = split_us(q, m, n, k);
+    if (us >= least) return;
+    least = us;
+    best = q;
+    best.use = true;
+  };
+  const int64_t lesser = std::min(m, n), larger = std::max(m, n);
+  const bool small_tile = 195.0 * (double)cdiv(m, 128) < 180.0 * 2.0 * (double)cdiv(m, 256);
+  for (int64_t s = 1; s <= std::min<int64_t>(8, std::max<int64_t>(1, k / 512)); ++s)
+    for (int64_t c0 = cdiv(k, kChain * s), c = c0; c < c0 + 4; ++c) {  // c passes of s chains each
+      const int64_t chain = cdiv(cdiv(k, c * s), 2 * kSlab) * 2 * kSlab;
+      if (c > c0 && chain < 512) break;
+      SplitPlan q;
+      q.small = small_tile;
+      q.splits = (int)s;
+      q.kl = std::min(k, chain * s);
+      const size_t block = pack_bytes(kRB, q.kl), part = s > 1 ? (size_t)s * 8 : 0;
+      for (int64_t parts = 1; parts <= 16; ++parts) {
+        // blocks of the lesser extent, and the largest of the other one beside them
+        const int64_t lb = parts == 1 ? lesser : cdiv(cdiv(lesser, parts), 256) * 256;
+        const size_t held = pack_bytes(lb, q.kl) + kFlagBytes;
+        int64_t gb = held < budget ? (int64_t)((budget - held) / (block + part * lb * kRB)) * kRB : 0;
+        if (gb >= larger)
+          gb = larger;
+        else if (gb < 256)
+          continue;
+        else
+          gb = cdiv(cdiv(larger, cdiv(larger, gb / 256 * 256)), 256) * 256;
+        q.mc = m >= n ? gb : lb, q.nc = m >= n ? lb : gb;
+        q.a_bytes = pack_bytes(q.mc, q.kl);
+        q.b_bytes = pack_bytes(q.nc, q.kl);
+        q.bytes = q.a_bytes + q.b_bytes + part * q.mc * q.nc + kFlagBytes;
+        if (q.bytes <= budget) consider(q);
+        if (gb == larger) break;  // smaller blocks only cost more
+      }
+      if (q.mc == m && q.nc == n) break;  // and so do shorter passes
+    }
+  return best;
 }
 
 void launch_split_gemm(const SplitPlan& p, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim,

@@ -640,7 +640,8 @@ WavePlan wave_plan(bool ta, bool tb, int64_t m, int64_t n, int64_t k, int64_t ld
         break;
       }
   }
-  if (p.variant >= 2 && wave_us<T>(p, ta, tb, m, n) >= 0.97 * tiled_us(F64, ta, tb, m, n, k, can_split)) return WavePlan();
+  if (p.variant >= 2) p.us = wave_us<T>(p, ta, tb, m, n);
+  if (p.us >= 0.97 * tiled_us(F64, ta, tb, m, n, k, can_split)) return WavePlan();
   return p;
 }
 

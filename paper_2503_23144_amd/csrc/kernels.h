@@ -161,6 +161,7 @@ size_t gemm_call_workspace(bool fp64, bool ta, bool tb, int64_t m, int64_t n, in
 struct WavePlan {
   int variant = -1, splits = 1;
   int64_t kchunk = 0;
+  double us = 0;  // estimate, variants 2 to 4
 };
 template <typename T>
 WavePlan wave_plan(bool ta, bool tb, int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, bool can_split);
@@ -202,7 +203,7 @@ struct SplitPlan {
   OutMap ma, mb;
 };
 constexpr size_t kPackBudget = size_t(1280) << 20;  // most memory a plan asks for, unless told otherwise
-SplitPlan split_plan(int64_t m, int64_t n, int64_t k, size_t budget = kPackBudget);
+SplitPlan split_plan(bool ta, bool tb, int64_t m, int64_t n, int64_t k, size_t budget = kPackBudget);
 void launch_split_gemm(const SplitPlan& p, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double are, double aim,
                        const void* A, int64_t lda, const void* B, int64_t ldb, double bre, double bim, void* C,
                        const OutMap& om, void* ws, hipStream_t st, bool conjb);

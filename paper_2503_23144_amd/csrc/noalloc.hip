@@ -69,7 +69,7 @@ extern "C" int lrcc_gemm_noalloc(int precision, int transa, int transb, int64_t 
                  "product needs " + std::to_string(wsb) + " bytes of split-K partials, above the " +
                      std::to_string(kStaticScratchBytes) + "-byte static scratch of lrcc_gemm_noalloc");
     SplitPlan sp;  // large FP32 products: packed operands in the same array
-    if (precision == LRCC_MIXED) sp = split_plan(m, n, k, kStaticScratchBytes);
+    if (precision == LRCC_MIXED) sp = split_plan(transa != 0, transb != 0, m, n, k, kStaticScratchBytes);
     void* ws = wsb || sp.use ? scratch_on_current_device() : nullptr;
     const hipStream_t st = (hipStream_t)stream;
     if (precision == LRCC_FP64)

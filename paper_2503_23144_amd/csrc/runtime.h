@@ -287,7 +287,7 @@ class Executor {
                       const std::string& Mc, const std::string& Nc, const std::string& Kx, const void* pa, int64_t ca,
                       const void* pb, int64_t cb, void* pc, int64_t cc, bool a_ok, bool b_ok);
   int cached_permute(int id, const std::string& src, const std::string& dst, const void* p, int64_t cap);
-  void* pack_scratch(int64_t M, int64_t N, int64_t K, SplitPlan& s);
+  void* pack_scratch(bool ta, bool tb, int64_t M, int64_t N, int64_t K, SplitPlan& s);
   static constexpr int kPermSlot = 5, kPackSlot = 9;
   struct PermEntry {
     int tensor = -1;

@@ -214,9 +214,9 @@ void* Executor<T>::scratch(int slot, size_t bytes) {
 // captured (a run before the capture has taken it, or the product runs
 // without), nor while a tile is pinned.  Null when there is none.
 template <typename T>
-void* Executor<T>::pack_scratch(int64_t M, int64_t N, int64_t K, SplitPlan& s) {
+void* Executor<T>::pack_scratch(bool ta, bool tb, int64_t M, int64_t N, int64_t K, SplitPlan& s) {
   if (sizeof(T) == 8 || gemm_pinned_tile() >= 0) return nullptr;
-  s = split_plan(M, N, K);
+  s = split_plan(ta, tb, M, N, K);
   if (!s.use) return nullptr;
   if (scr_cap_[kPackSlot] < s.bytes) {
     if (capturing_ || outer_ || 8 * s.bytes > (size_t)dev_available()) return nullptr;
@@ -360,7 +360,7 @@ bool Executor<T>::gemm(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double
                  LRCC_E_INTERNAL, "gemm operands exceed their buffers");
   }
   SplitPlan sp;
-  void* pack = pack_scratch(M, N, K, sp);
+  void* pack = pack_scratch(ta, tb, M, N, K, sp);
   if ((am || bm) && !pack) return false;
   if (am) sp.amap = true, sp.ma = *am;
   if (bm) sp.bmap = true, sp.mb = *bm;

@@ -1,5 +1,6 @@
 // Prints the library's GEMM plans for the products on stdin (test_gemm_plans.py).
 //   w fp64 ta tb m n k         wavefront kernel: variant and splits with and without workspace
+//   s ta tb m n k budget       BF16 kernel: use, splits, block rows, columns and depth, bytes
 #include <cstdio>
 
 #include "common.h"
@@ -20,6 +21,12 @@ int main() {
         printf("%d %d ", p.variant, p.splits);
       }
       printf("\n");
+    } else if (what == 's') {
+      int ta, tb;
+      long m, n, k, budget;
+      if (scanf("%d %d %ld %ld %ld %ld", &ta, &tb, &m, &n, &k, &budget) != 6) return 1;
+      const SplitPlan p = split_plan(ta, tb, m, n, k, (size_t)budget);
+      printf("%d %d %ld %ld %ld %ld\n", p.use, p.splits, (long)p.mc, (long)p.nc, (long)p.kl, (long)p.bytes);
     } else {
       return 1;
     }

@@ -36,3 +36,30 @@ def test_both_calls_give_the_same_bits(dtype, ta, tb, m, n, k):
 def test_allocating_call_matches_host(dtype, ta, tb, m, n, k):
     """The few-tile shapes through lrcc_gemm."""
     _check(dtype, ta, tb, m, n, k, noalloc=False)
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("m,n,k", [(12500, 12600, 1100), (8100, 8200, 3072), (9814, 374, 3986), (5000, 5000, 3000)])
+def test_blocks_of_the_operands_match_64_bits(ta, tb, m, n, k):
+    """Large FP32 products whose packed operands exceed the static scratch:
+    blocks of either extent and of the depth.  No further from 64 bits, row by
+    row, than the FP32 matrix cores."""
+    from paper_2503_23144_amd import lrcc
+    print(f"blocked product m={m} n={n} k={k} ta={ta} tb={tb}", flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(m + n + k)
+    rand = lambda *s: torch.randn(*s, dtype=torch.complex64, device="cuda:0", generator=g)  # noqa: E731
+    A, B, C0 = rand(*((k, m) if ta else (m, k))), rand(*((n, k) if tb else (k, n))), rand(m, n)
+    al, be = 0.6 - 0.2j, -0.3 + 0.7j
+    D = torch.complex128
+    ref = al * ((A.T if ta else A).to(D) @ (B.T if tb else B).to(D)) + be * C0.to(D)
+    rel = []
+    for tile in (-1, 0):
+        C = C0.clone()
+        lrcc.gemm_set_tile(tile)
+        try:
+            lrcc.gemm(A, B, C, transa=bool(ta), transb=bool(tb), alpha=al, beta=be, noalloc=True)
+            torch.cuda.synchronize()
+        finally:
+            lrcc.gemm_set_tile(-1)
+        rel.append(float(((C - ref).abs() ** 2).sum(1).div((ref.abs() ** 2).sum(1)).sqrt().max()))
+    assert rel[0] <= 1.1 * rel[1], rel
