@@ -89,7 +89,8 @@ void* Executor<T>::ptr(int id) {
     if (buf_[id]) {
       HIP_CHECK(hipStreamSynchronize(st_));
       dev_free(buf_[id]);
-      buf_[id] = nullptr;
+      buf_[id] = nullptr;  // the request below may fail
+      cap_[id] = 0;
     }
     buf_[id] = dev_alloc(std::max<int64_t>(need, 1) * sizeof(T) * 2);
     cap_[id] = need;
@@ -197,11 +198,13 @@ template <typename T>
 void* Executor<T>::scratch(int slot, size_t bytes) {
   if (scr_cap_[slot] < bytes) {
     on_realloc();
+    const size_t b = std::max(bytes, scr_cap_[slot] + scr_cap_[slot] / 4);
     if (scr_[slot]) {
       HIP_CHECK(hipStreamSynchronize(st_));
       dev_free(scr_[slot]);
+      scr_[slot] = nullptr;  // the request below may fail
+      scr_cap_[slot] = 0;
     }
-    size_t b = std::max(bytes, scr_cap_[slot] + scr_cap_[slot] / 4);
     scr_[slot] = dev_alloc(b);
     scr_cap_[slot] = b;
   }
@@ -224,8 +227,6 @@ void* Executor<T>::pack_scratch(bool ta, bool tb, int64_t M, int64_t N, int64_t 
       scratch(kPackSlot, s.bytes);
     } catch (const Error& e) {
       if (e.code != LRCC_E_NOMEM) throw;
-      scr_[kPackSlot] = nullptr;  // freed before the failed request
-      scr_cap_[kPackSlot] = 0;
       return nullptr;
     }
   }
@@ -1617,7 +1618,10 @@ void Executor<T>::prepare(const OpList& ops, int nb, const std::vector<int>& kee
       if (pool_[s]) {
         HIP_CHECK(hipStreamSynchronize(st_));
         dev_free(pool_[s]);
+        for (size_t k = 0; k < buf_.size(); ++k)  // the request below may fail: no tensor keeps the freed slot
+          if (pooled_[k] && buf_[k] == pool_[s]) buf_[k] = nullptr, cap_[k] = 0, pooled_[k] = 0;
         pool_[s] = nullptr;
+        pool_cap_[s] = 0;
       }
       pool_[s] = dev_alloc(pl.slot_elems[s] * sizeof(T) * 2);
       pool_cap_[s] = pl.slot_elems[s];
