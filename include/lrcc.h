@@ -344,7 +344,12 @@ int lrcc_graph_stats(lrcc_ctx *ctx, int64_t *captures, int64_t *replays);
    (LRCC_E_STATE otherwise).  From then on every allocation of the context
    is carved from that buffer and nothing is taken from the device; batch
    sizes adapt to what is free in it, and an allocation that does not fit
-   fails with LRCC_E_NOMEM.  The buffer stays owned by the caller, who frees
+   fails with LRCC_E_NOMEM.  Memory for the packed operands of large FP32
+   products (up to 1.6 GiB) comes on top of the estimate: it is taken only while
+   it stays below an eighth of what is free, and given back when another
+   allocation of the context needs it.  Such a product then runs on FP32 MFMA
+   instead, so its last bits depend on the memory that was free (here and on
+   the device).  The buffer stays owned by the caller, who frees
    it after lrcc_destroy.  lrcc_workspace_peak returns the most of it in use
    at any time so far (0 without a workspace). */
 size_t lrcc_workspace_bytes(const lrcc_config *cfg, int nocc, int nvir, int naux, int nrhs);

@@ -32,6 +32,7 @@ template <typename F>
 static int guard(lrcc_ctx* ctx, F&& f) {
   if (!ctx || !ctx->impl) return LRCC_E_INVALID;
   lrcc::ArenaScope scope(ctx->arena.get());  // every allocation of this call comes from the workspace
+  lrcc::YieldScope yields(ctx->impl.get());
   try {
     HIP_CHECK(hipSetDevice(ctx->impl->cfg.device));
     f(*ctx->impl);

@@ -59,9 +59,10 @@ size_t workspace_estimate(const lrcc_config& cfg, int o, int v, int naux, int nr
 // terms (lrcc_config.ring_factored; automatic by the size of Z1).
 bool ring_factored_for(const lrcc_config& cfg, int o, int v, int prec);
 
-struct Context {
+struct Context : Yields {
   explicit Context(const lrcc_config& cfg);
-  ~Context();
+  ~Context() override;
+  bool yield() override { return x32 && x32->yield_packs(); }  // the packed GEMM operands
 
   lrcc_config cfg;
   hipStream_t st = nullptr;

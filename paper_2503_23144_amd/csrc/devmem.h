@@ -37,6 +37,23 @@ class ArenaScope {
 };
 Arena* current_arena();
 
+// Memory that its holder can do without.  While a YieldScope is active on this
+// thread, an allocation that does not fit asks for it once (yield returns
+// whether it gave any back) and tries again.
+class Yields {
+ public:
+  virtual ~Yields() = default;
+  virtual bool yield() = 0;
+};
+class YieldScope {
+ public:
+  explicit YieldScope(Yields* y);  // null: none while it lasts
+  ~YieldScope();
+
+ private:
+  Yields* prev_;
+};
+
 void* dev_alloc(size_t bytes);  // on the current device (or the current arena); throws Error on failure
 void dev_free(void* p);         // arena blocks return to the arena; others are cached after a device sync
 void dev_trim();                // return every cached block to its device

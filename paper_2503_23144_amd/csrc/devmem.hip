@@ -60,6 +60,7 @@ void trim_device(int dev) {  // caller holds g_mu
 }
 
 thread_local Arena* t_arena = nullptr;
+thread_local Yields* t_yields = nullptr;
 
 }  // namespace
 
@@ -121,8 +122,11 @@ ArenaScope::ArenaScope(Arena* a) : prev_(t_arena) { t_arena = a; }
 ArenaScope::~ArenaScope() { t_arena = prev_; }
 Arena* current_arena() { return t_arena; }
 
+YieldScope::YieldScope(Yields* y) : prev_(t_yields) { t_yields = y; }
+YieldScope::~YieldScope() { t_yields = prev_; }
+
 // ---------------------------------------------------------------- device memory
-void* dev_alloc(size_t bytes) {
+static void* alloc_once(size_t bytes) {
   if (t_arena) return t_arena->alloc(bytes);
   int dev = 0;
   HIP_CHECK(hipGetDevice(&dev));
@@ -151,6 +155,19 @@ void* dev_alloc(size_t bytes) {
   }
   g_live[p] = Block{b, dev};
   return p;
+}
+
+void* dev_alloc(size_t bytes) {
+  if (!t_yields) return alloc_once(bytes);
+  try {
+    return alloc_once(bytes);
+  } catch (const Error& e) {
+    if (e.code != LRCC_E_NOMEM) throw;
+    Yields* y = t_yields;
+    YieldScope once(nullptr);
+    if (!y->yield()) throw;
+  }
+  return alloc_once(bytes);
 }
 
 void dev_free(void* p) {

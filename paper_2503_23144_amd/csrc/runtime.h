@@ -76,6 +76,9 @@ class Executor {
   size_t batched_bytes() const;
   // Free all batch-dependent storage (it is re-allocated on the next run).
   void release_batched();
+  // Gives back the memory of packed GEMM operands, which products take where
+  // there is plenty; false if there is none or a graph is being captured.
+  bool yield_packs();
   // Free the private storage of the unbatched tensors `ops` writes (its
   // results; they are formed again by the next run of `ops`).
   void release_results(const OpList& ops);
@@ -287,6 +290,7 @@ class Executor {
                       const std::string& Mc, const std::string& Nc, const std::string& Kx, const void* pa, int64_t ca,
                       const void* pb, int64_t cb, void* pc, int64_t cc, bool a_ok, bool b_ok);
   int cached_permute(int id, const std::string& src, const std::string& dst, const void* p, int64_t cap);
+  bool packs_yielded_ = false;  // since the current eager run began
   void* pack_scratch(bool ta, bool tb, int64_t M, int64_t N, int64_t K, SplitPlan& s);
   static constexpr int kPermSlot = 5, kPackSlot = 9;
   struct PermEntry {

@@ -211,11 +211,12 @@ void* Executor<T>::scratch(int slot, size_t bytes) {
   return scr_[slot];
 }
 
-// Scratch for the packed operands of a large FP32 product (split_plan):
-// taken only while it stays below an eighth of the free memory, so that the
-// buffers a run cannot do without keep their room, and not while a graph is
-// captured (a run before the capture has taken it, or the product runs
-// without), nor while a tile is pinned.  Null when there is none.
+// Scratch for the packed operands of a large FP32 product (split_plan): taken
+// only while it stays below an eighth of the free memory, given back when
+// another allocation fails (yield_packs), so that the buffers a run cannot do
+// without keep their room, and not taken while a graph is captured (a run
+// before the capture has taken it, or the product runs without), nor while a
+// tile is pinned.  Null when there is none.
 template <typename T>
 void* Executor<T>::pack_scratch(bool ta, bool tb, int64_t M, int64_t N, int64_t K, SplitPlan& s) {
   if (sizeof(T) == 8 || gemm_pinned_tile() >= 0) return nullptr;
@@ -223,14 +224,36 @@ void* Executor<T>::pack_scratch(bool ta, bool tb, int64_t M, int64_t N, int64_t 
   if (!s.use) return nullptr;
   if (scr_cap_[kPackSlot] < s.bytes) {
     if (capturing_ || outer_ || 8 * s.bytes > (size_t)dev_available()) return nullptr;
+    const size_t b = std::max(s.bytes, scr_cap_[kPackSlot] + scr_cap_[kPackSlot] / 4);
+    on_realloc();
+    void* p = nullptr;
     try {
-      scratch(kPackSlot, s.bytes);
+      YieldScope none(nullptr);
+      p = dev_alloc(b);  // beside the smaller one, which stays if this fails
     } catch (const Error& e) {
       if (e.code != LRCC_E_NOMEM) throw;
       return nullptr;
     }
+    if (scr_[kPackSlot]) {
+      HIP_CHECK(hipStreamSynchronize(st_));
+      dev_free(scr_[kPackSlot]);
+    }
+    scr_[kPackSlot] = p;
+    scr_cap_[kPackSlot] = b;
   }
   return scr_[kPackSlot];
+}
+
+template <typename T>
+bool Executor<T>::yield_packs() {
+  if (!scr_[kPackSlot] || capturing_ || outer_) return false;
+  on_realloc();
+  HIP_CHECK(hipStreamSynchronize(st_));
+  dev_free(scr_[kPackSlot]);
+  scr_[kPackSlot] = nullptr;
+  scr_cap_[kPackSlot] = 0;
+  packs_yielded_ = true;
+  return true;
 }
 
 // current batch of the op being executed (dims of '#')
@@ -1685,7 +1708,11 @@ void Executor<T>::run(const OpList& ops, int nb, const std::vector<int>& keep) {
   }
   auto it = graphs_.find(make_key(ops, nb, keep));
   if (it == graphs_.end()) {
+    packs_yielded_ = false;
     run_ops(ops, nb);  // eager: lazy allocations and GEMM tile tuning happen here
+    // one that lost its packed operands' memory on the way may need other scratch
+    // next time: that run is eager again
+    if (packs_yielded_) return;
     if (graphs_.size() >= 64) clear_graphs();
     graphs_.emplace(make_key(ops, nb, keep), Recorded());
     return;

@@ -1,6 +1,7 @@
 """The rules that choose a GEMM kernel, on the host: the shapes that were
 measured on both sides of a rule go to the faster one, and the shapes of the
-GPU tests to the kernels that those tests are for."""
+GPU tests to the kernels that those tests are for; and the memory that its
+packed operands give back."""
 import os
 import subprocess
 
@@ -100,3 +101,7 @@ def test_gpu_test_shapes_take_the_bf16_kernel(plans):
         assert all(p[0] for p in got)
         kinds = {(p[2] < m, p[3] < n, p[4] < k) for p, (m, n, k) in zip(got, shapes + blocked)}
         assert {(True, True, False), (True, False, True), (False, False, False)} <= kinds, kinds
+
+
+def test_a_failing_allocation_asks_once_for_what_can_yield(plans):
+    assert plans(["y"]) == [[1.0]]

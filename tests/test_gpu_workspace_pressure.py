@@ -61,3 +61,38 @@ def test_calls_after_a_failed_allocation(system):
                 assert float(d) <= 1e-5 * float(ref.abs().max())
         c.close()
     assert failed > 0
+
+
+def test_packed_operands_yield_to_larger_batches(system):
+    """Memory that a product took for packed operands is no obstacle to a
+    later one: a workspace that holds the large batch on its own, with 6 % to
+    spare for the holes that growing buffers leave, holds it after a smaller one,
+    too, and again from a recorded graph."""
+    from paper_2503_23144_amd import lrcc
+    X = system[2]
+    c = _context(system, 24 << 30)
+    ref = c.sigma("right", X, precision="mixed")
+    size = 2 * c.workspace_peak()
+    c.close()
+
+    def runs(size, calls):
+        c = _context(system, size)
+        try:
+            for vecs in calls:
+                got = c.sigma("right", vecs, precision="mixed")
+                assert float((got - ref[:len(vecs)]).abs().max()) <= 1e-5 * float(ref.abs().max())
+            return True
+        except lrcc.LrccError as e:
+            assert e.code == lrcc.E_NOMEM
+            return False
+        finally:
+            c.close()
+
+    tight = []
+    while runs(size, [X]):
+        tight.append(size)
+        size = int(size * 0.97)
+    assert tight
+    for size in [s for s in tight if s >= 1.06 * tight[-1]][-3:]:
+        print(f"workspace of {size} bytes", flush=True)
+        assert runs(size, [X[:40], X, X, X, X[:40], X]), size
