@@ -42,7 +42,7 @@ static bool yields() {
   }
   dev_alloc(100 << 10);  // fits
   if (h.asked != 0) return false;
-  dev_alloc(700 << 10);  // fits in what is given back
+  dev_alloc(550 << 10);  // fits in what is given back
   if (h.asked != 1 || h.p) return false;
   return fails(500 << 10) && h.asked == 2;  // nothing left to give
 }
