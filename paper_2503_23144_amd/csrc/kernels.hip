@@ -1225,8 +1225,6 @@ void launch_copy_rows(int64_t rows, int64_t w, const void* src, int64_t sld, voi
 }
 template void launch_copy_rows<double, double>(int64_t, int64_t, const void*, int64_t, void*, int64_t, hipStream_t);
 template void launch_copy_rows<double, float>(int64_t, int64_t, const void*, int64_t, void*, int64_t, hipStream_t);
-template void launch_copy_rows<float, float>(int64_t, int64_t, const void*, int64_t, void*, int64_t, hipStream_t);
-template void launch_copy_rows<float, double>(int64_t, int64_t, const void*, int64_t, void*, int64_t, hipStream_t);
 
 // Amplitude vectors x[r] = (x1 [n1], x2 [n2]) against their two parts as
 // program tensors, one launch for both (each part of a small vector is a
