@@ -13,7 +13,7 @@
 //   !KSPLIT  every wavefront owns a tile of its own (shallow products).
 // Measured (us, tiled kernel -> this one): FP64 4x4x1024 170 -> 7, 3x600x600
 // 102 -> 8, 180x10x6000 205 -> 15, 30x60x36000 190 -> 37, 135x1770x1770
-// 295 -> 82, 1200^3 347 -> 257, 3000^3 3819 -> 3429, 20x450000x150 1141 ->
+// 295 -> 82, 1200^3 347 -> 257, 3000^3 3820 -> 3585, 20x450000x150 1141 ->
 // 378, 1x22500x3000 859 -> 196 (5.5 TB/s); FP32 12x671x671 53 -> 7,
 // 660x1830x1830 219 -> 150, 24x3000x3000 121 -> 34, 36000x1x3000 289 -> 155.
 // Without LDS every operand element is read from L2 once per 32 rows or
